@@ -89,6 +89,11 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
 int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
                     const int32_t *seg_offsets, const void *W_down, void *y, void *ws,
                     hipStream_t st);
+int launch_ffn_f32_gate_up(const float *xp, int64_t M, int64_t H, int64_t F, int E_local, const int32_t *seg_offsets,
+                           const float *W_gate, const float *W_up, float *a, const int32_t *gather_rows, int K,
+                           hipStream_t st);
+int launch_ffn_f32_down(const float *a, int64_t M, int64_t H, int64_t F, int E_local, const int32_t *seg_offsets,
+                        const float *W_down, float *y, hipStream_t st);
 int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int E_local, const void *W_gate,
                             const void *W_up, const void *W_down, void *y, void *ws, int64_t wait_limit,
                             hipStream_t st);

@@ -211,73 +211,6 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
 }
 
 // ------------------------------------------------------------------------
-// bf16 matrix-core grouped GEMM
-// ------------------------------------------------------------------------
-// ------------------------------------------------------------------------
-// fp32 path (small, correctness-oriented): one thread per output element
-// ------------------------------------------------------------------------
-__device__ __forceinline__ int expert_of_row(const int32_t *seg, int E_local, int64_t m)
-{
-    int lo = 0, hi = E_local; // last e with seg[e] <= m
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (seg[mid] <= m)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return (m >= seg[lo] && m < seg[lo + 1]) ? lo : -1;
-}
-
-// gather_rows != nullptr: row m of xp is row gather_rows[m] / gather_div of `xp`
-__global__ __launch_bounds__(256) void ffn_f32_gate_up(const float *__restrict__ xp, int64_t M, int H,
-                                                     int F, int E_local,
-                                                     const int32_t *__restrict__ seg,
-                                                     const float *__restrict__ Wg,
-                                                     const float *__restrict__ Wu,
-                                                     float *__restrict__ a,
-                                                     const int32_t *__restrict__ gather_rows, int gather_div)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * F)
-        return;
-    const int64_t m = i / F;
-    const int f = (int)(i % F);
-    const int e = expert_of_row(seg, E_local, m);
-    if (e < 0)
-        return;
-    const float *xr = xp + (gather_rows ? (int64_t)(gather_rows[m] / gather_div) : m) * H;
-    const float *g = Wg + ((int64_t)e * F + f) * H;
-    const float *u = Wu + ((int64_t)e * F + f) * H;
-    float sg = 0.0f, su = 0.0f;
-    for (int h = 0; h < H; ++h) {
-        sg = fmaf(xr[h], g[h], sg);
-        su = fmaf(xr[h], u[h], su);
-    }
-    a[i] = sg / (1.0f + expf(-sg)) * su;
-}
-
-__global__ __launch_bounds__(256) void ffn_f32_down(const float *__restrict__ a, int64_t M, int H, int F,
-                                                  int E_local, const int32_t *__restrict__ seg,
-                                                  const float *__restrict__ Wd, float *__restrict__ y)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * H)
-        return;
-    const int64_t m = i / H;
-    const int c = (int)(i % H);
-    const int e = expert_of_row(seg, E_local, m);
-    if (e < 0)
-        return;
-    const float *ar = a + m * F;
-    const float *w = Wd + ((int64_t)e * H + c) * F;
-    float s = 0.0f;
-    for (int f = 0; f < F; ++f)
-        s = fmaf(ar[f], w[f], s);
-    y[i] = s;
-}
-
-// ------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------
 // Geometries.  Big: 256x256x64 tile, ring of 5 units (all 160 KiB of LDS); per window the 8 B loads
@@ -499,11 +432,9 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
                        hipStream_t st, const int32_t *gather_rows, int K, int64_t N)
 {
     if (dtype == MOE_F32) {
-        hipLaunchKernelGGL(ffn_f32_gate_up, dim3((unsigned)ceil_div(M * F, 256)), dim3(256), 0, st,
-                           static_cast<const float *>(xp), M, (int)H, (int)F, E_local, seg_offsets,
-                           static_cast<const float *>(W_gate), static_cast<const float *>(W_up),
-                           static_cast<float *>(ws), gather_rows, K);
-        return check_launch("moe_ffn_gate_up(f32)");
+        return launch_ffn_f32_gate_up(static_cast<const float *>(xp), M, H, F, E_local, seg_offsets,
+                                      static_cast<const float *>(W_gate), static_cast<const float *>(W_up),
+                                      static_cast<float *>(ws), gather_rows, K, st);
     }
     const FfnPlan p = make_plan(M, H, F, E_local);
     const FfnWorkspace k = carve(p, ws);
@@ -521,10 +452,8 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
                     const int32_t *seg_offsets, const void *W_down, void *y, void *ws, hipStream_t st)
 {
     if (dtype == MOE_F32) {
-        hipLaunchKernelGGL(ffn_f32_down, dim3((unsigned)ceil_div(M * H, 256)), dim3(256), 0, st,
-                           static_cast<const float *>(ws), M, (int)H, (int)F, E_local, seg_offsets,
-                           static_cast<const float *>(W_down), static_cast<float *>(y));
-        return check_launch("moe_ffn_down(f32)");
+        return launch_ffn_f32_down(static_cast<const float *>(ws), M, H, F, E_local, seg_offsets,
+                                   static_cast<const float *>(W_down), static_cast<float *>(y), st);
     }
     const FfnPlan p = make_plan(M, H, F, E_local);
     const FfnWorkspace k = carve(p, ws);
