@@ -182,9 +182,10 @@ __global__ __launch_bounds__(kF32Threads, (kStages > 3 ? 2 : 4)) void ffn_f32_ti
         constexpr int kInFlight = (kStages - 2) * kLoads; // the loads of the K tiles after kt
         int stage = 0;
         for (int kt = 0; kt < KT; ++kt) {
-            __builtin_amdgcn_s_waitcnt(0x0F70 | (kInFlight & 15) | (kInFlight >> 4 << 14)); // my part of K tile kt is there
+            // my part of K tile kt is there (vmcnt), my reads of K tile kt - 1 are done (lgkmcnt) ...
+            __builtin_amdgcn_s_waitcnt(0x0070 | (kInFlight & 15) | (kInFlight >> 4 << 14));
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();       // ... and everyone's; nobody reads K tile kt - 1 any more
+            __builtin_amdgcn_s_barrier(); // ... and everyone's
             asm volatile("" ::: "memory");
             issue(kt + kStages - 1, stage == 0 ? kStages - 1 : stage - 1); // (past the last K tile: zeros, the count stays)
             const unsigned char *st = lds + stage * kStage;

@@ -4,490 +4,101 @@
 // Order of the logit sum ("R64"): 64 partial sums, partial l takes
 // h = l, l+64, ... ascending with one fused multiply-add per term; the partials
 // are folded in six pairwise rounds s = 32,...,1 (p[l] + p[l^s]); bias last.
-// A wavefront maps onto it directly: lane l owns partial l.  Each wavefront
-// carries a kTok x kExp register tile of (token, expert) pairs so that every
-// x and W_r value fetched is used kExp resp. kTok times.  The six rounds are done
-// as a halving exchange: in round s a lane keeps the half of its values chosen by
-// its own bit s and receives the partner's copy of that half, so 63 exchanges
-// fold all 64 values and lane i ends with value i - the same additions, pair by
-// pair, as folding every value separately.
 //
-// This step runs on the plain vector ALUs: matrix-core accumulation order is not
-// exposed, so it could not be matched on a CPU.
+// The products run on the matrix cores without giving up that order.  v_mfma_f32_16x16x1_4B_f32 multiplies
+// four independent 16x1 by 1x16 pairs: with a reduction length of ONE every output is exactly one fused
+// multiply-add, d = fma(a, b, c) (checked bit for bit against fmaf, signed zeros and subnormal products
+// included), so nothing about the summation order is left to the hardware.  The four blocks of an
+// instruction are four different partials; sixteen instructions cover all 64 for 16 tokens x 16 experts:
+//   a operand, lane (blk = lane / 16, c = lane % 16):  x[token c, h]       h = 64 step + l
+//   b operand:                                         W_r[h, expert c]
+//   result register 4 b + t of lane (q, c):            partial of block b, token 4 q + t, expert c
+// A wavefront takes a share of the partials (64 / kSplit of them, kG = 16 / kSplit instructions per step of
+// 64 columns): wavefront `ps` of a group of kSplit has l = 4 kG ps + kG blk + g.  The rounds of the fold that
+// pair partials of different wavefronts (the high bits of l) come first and go through LDS; all the others
+// pair registers of one lane.
+//
+// Tokens past N and experts past E repeat the last one (their results are not stored).  Rows of W_r past H
+// count as zeros, and columns of x past H as any finite value: adding a zero product never changes a partial
+// sum (partials start at +0 and can never become -0), so a ragged last step gives the R64 sum bit for bit.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.h"
 
 namespace moe {
 
-constexpr int kTok = 8;
-constexpr int kExp = 8;
-constexpr int kRouteWaves = 4;
+constexpr int kRouteWaves = 4; // wavefronts per workgroup of the selection kernel
+constexpr int kRtExp = 16, kRtTok = 16;
 
-template <bool kBf16>
-__device__ __forceinline__ float load_x(const void *x, int64_t i)
+// Four columns of x (bf16: two per register) or fewer, as fetched; see x_value.
+template <bool kBf16, int kG>
+struct XChunk {
+    static constexpr int kRegs = kBf16 ? kG / 2 : kG;
+    uint32_t r[kRegs];
+};
+template <bool kBf16, int kG>
+__device__ __forceinline__ float x_value(const XChunk<kBf16, kG> &c, int g)
 {
     if (kBf16)
-        return bf16_bits_to_f32(static_cast<const uint16_t *>(x)[i]);
-    return static_cast<const float *>(x)[i];
+        return __uint_as_float(g & 1 ? c.r[g / 2] & 0xFFFF0000u : c.r[g / 2] << 16);
+    return __uint_as_float(c.r[g]);
 }
-
-template <int kHalf>
-__device__ __forceinline__ void fold_round(float *v, bool upper)
+template <bool kBf16, int kG>
+__device__ __forceinline__ XChunk<kBf16, kG> load_chunk(const unsigned char *p)
 {
+    XChunk<kBf16, kG> c;
+    constexpr int n = XChunk<kBf16, kG>::kRegs;
+    if constexpr (n % 4 == 0) {
 #pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-        float keep = upper ? v[i + kHalf] : v[i];
-        float send = upper ? v[i] : v[i + kHalf];
-        v[i] = keep + __shfl_xor(send, kHalf);
-    }
-}
-
-template <bool kBf16>
-__global__ __launch_bounds__(kWave *kRouteWaves) void router_logits(
-    const void *__restrict__ x, int64_t N, int64_t H, const float *__restrict__ W_r,
-    const float *__restrict__ bias, int E, float *__restrict__ logits)
-{
-    const int lane = threadIdx.x % kWave;
-    const int64_t n0 = ((int64_t)blockIdx.x * kRouteWaves + threadIdx.x / kWave) * kTok;
-    const int e0 = blockIdx.y * kExp;
-    if (n0 >= N)
-        return;
-
-    int64_t xrow[kTok];
+        for (int i = 0; i < n / 4; ++i) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(p + 16 * i);
 #pragma unroll
-    for (int t = 0; t < kTok; ++t) {
-        int64_t n = n0 + t;
-        xrow[t] = (n < N ? n : N - 1) * H;
-    }
-    int ecol[kExp];
-#pragma unroll
-    for (int j = 0; j < kExp; ++j)
-        ecol[j] = (e0 + j < E) ? e0 + j : E - 1;
-
-    float acc[kTok * kExp];
-#pragma unroll
-    for (int i = 0; i < kTok * kExp; ++i)
-        acc[i] = 0.0f;
-
-    const bool full = (e0 + kExp <= E) && (E % 4 == 0);
-    if (full) {
-        for (int64_t h = lane; h < H; h += kWave) {
-            const f32x4 *wp = reinterpret_cast<const f32x4 *>(W_r + h * E + e0);
-            f32x4 w0 = wp[0], w1 = wp[1];
-            float wv[kExp] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
-            float xv[kTok];
-#pragma unroll
-            for (int t = 0; t < kTok; ++t)
-                xv[t] = load_x<kBf16>(x, xrow[t] + h);
-#pragma unroll
-            for (int t = 0; t < kTok; ++t)
-#pragma unroll
-                for (int j = 0; j < kExp; ++j)
-                    acc[t * kExp + j] = fmaf(xv[t], wv[j], acc[t * kExp + j]);
+            for (int j = 0; j < 4; ++j)
+                c.r[4 * i + j] = v[j];
         }
+    } else if constexpr (n == 2) {
+        const u32x2 v = *reinterpret_cast<const u32x2 *>(p);
+        c.r[0] = v[0], c.r[1] = v[1];
     } else {
-        for (int64_t h = lane; h < H; h += kWave) {
-            float wv[kExp], xv[kTok];
-#pragma unroll
-            for (int j = 0; j < kExp; ++j)
-                wv[j] = W_r[h * E + ecol[j]];
-#pragma unroll
-            for (int t = 0; t < kTok; ++t)
-                xv[t] = load_x<kBf16>(x, xrow[t] + h);
-#pragma unroll
-            for (int t = 0; t < kTok; ++t)
-#pragma unroll
-                for (int j = 0; j < kExp; ++j)
-                    acc[t * kExp + j] = fmaf(xv[t], wv[j], acc[t * kExp + j]);
-        }
+        static_assert(n == 1, "chunk of one, two or a multiple of four registers");
+        c.r[0] = *reinterpret_cast<const uint32_t *>(p);
     }
-
-    fold_round<32>(acc, lane & 32);
-    fold_round<16>(acc, lane & 16);
-    fold_round<8>(acc, lane & 8);
-    fold_round<4>(acc, lane & 4);
-    fold_round<2>(acc, lane & 2);
-    fold_round<1>(acc, lane & 1);
-
-    // lane i now holds pair i = t * kExp + j
-    const int t = lane / kExp, j = lane % kExp;
-    const int64_t n = n0 + t;
-    const int e = e0 + j;
-    if (n < N && e < E) {
-        float v = acc[0];
-        if (bias)
-            v = v + bias[e];
-        logits[n * E + e] = v;
-    }
+    return c;
 }
 
-// ------------------------------------------------------------------------
-// Tiled variant of the same sum for E % 4 == 0 (the benchmark shapes): a workgroup of four
-// wavefronts computes 32 tokens x 16 experts.  Every wavefront owns 8 tokens and all 16
-// experts (128 accumulators per lane, lane l = partial l of R64 as above).  K tiles of 128
-// columns are staged in LDS by buffer_load ... lds: the W_r tile (128 rows x 16 experts, shared
-// by the four wavefronts, 16-byte chunks XOR-swizzled so that the per-row reads are conflict
-// free) and each wavefront's own 8 x 128 slice of x.  Two stages; the loads of tile kt+1 run
-// under the multiply-adds of tile kt.  Rows past H and tokens past N come back as zeros from
-// the buffer bounds check; adding a zero product never changes a partial sum (partials start
-// at +0 and can never become -0), so the result is the R64 sum bit for bit.
-// ------------------------------------------------------------------------
-// MOE_ROUTER_MFMA: 1 = the tile is computed on the matrix cores (router_logits_mfma), 0 = on the vector
-// ALUs (router_logits_tiled); same bits either way.
-#ifndef MOE_ROUTER_MFMA
-#define MOE_ROUTER_MFMA 1
-#endif
-constexpr int kRtTok = 8;        // tokens per wavefront
-constexpr int kRtExp = 16;       // experts per workgroup
-constexpr int kRtK = 128;        // K tile
-#ifndef MOE_RT_WAVES
-#define MOE_RT_WAVES 4
-#endif
-constexpr int kRtWaves = MOE_RT_WAVES;
-// K tile of the matrix-core form: 128; 256 where a launch has one or two expert tiles only (E <= 32): few
-// workgroups, each with a long reduction, and half as many barriers pay there (E = 8: -11 %), while with
-// many expert tiles the larger LDS footprint costs more than that (E = 256: +7 %).
-constexpr int kRtKShort = 128, kRtKLong = 256;
-#ifndef MOE_RT_STAGES
-#define MOE_RT_STAGES 2
-#endif
-
-__device__ __forceinline__ int rt_key(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | ((r >> 1) & 2); }
-
-template <bool kBf16>
-__global__ __launch_bounds__(kWave *kRtWaves) void router_logits_tiled(
-    const void *__restrict__ x, int64_t N, int H, const float *__restrict__ W_r,
-    const float *__restrict__ bias, int E, float *__restrict__ logits)
+// Rounds of the fold inside a lane: v[b * kG + g] over blocks b (two bits, high first), then g.
+template <int kG>
+__device__ __forceinline__ float fold_in_lane(float *v)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int kXb = kBf16 ? 2 : 4;                  // bytes per x element
-    constexpr int kXRow = kRtK * kXb;                   // bytes of one token row in a tile
-    constexpr int kXTile = kRtTok * kXRow;              // per wavefront
-    constexpr int kWTile = kRtK * kRtExp * 4;           // 8 KiB
-    constexpr int kStage = kWTile + kRtWaves * kXTile;
-    constexpr int kXLoads = kXTile / 1024;              // per wavefront per tile
-    constexpr int kWLoads = kWTile / 1024 / kRtWaves;   // per wavefront per tile
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStage];
-    const int lane = threadIdx.x % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int e0 = blockIdx.x * kRtExp;
-    const int64_t n0 = ((int64_t)blockIdx.y * kRtWaves + wave) * kRtTok;
-
-    // W_r tile rows are 64 bytes (16 experts); a load instruction fills 16 rows
-    int w_off[kWLoads];
 #pragma unroll
-    for (int g = 0; g < kWLoads; ++g) {
-        const int r = (wave * kWLoads + g) * 16 + lane / 4; // row inside the tile
-        w_off[g] = (r * E + ((lane % 4) ^ rt_key(r)) * 4) * 4;
-    }
-    // x: this wavefront's 8 token rows; a load instruction fills 1024 / kXRow token rows
-    const int64_t n_left = N - n0; // may be <= 0 for the last workgroup: then nothing is in range
-    constexpr int kLanesPerRow = kXRow / 16;
-    int x_off[kXLoads];
+    for (int s = 2 * kG; s >= 1; s >>= 1)
 #pragma unroll
-    for (int g = 0; g < kXLoads; ++g) {
-        const int t = g * (kWave / kLanesPerRow) + lane / kLanesPerRow;
-        x_off[g] = (t * H + (lane % kLanesPerRow) * (16 / kXb)) * kXb;
-    }
-    // The position of a K tile goes into the base address and the byte count of the buffer
-    // resources, never into the loads' scalar offset: the range check covers the per-lane offset
-    // only, and what has to come back as zeros (rows of W_r past H, tokens past N) is decided by
-    // that check.  A column range [k0, k0 + 128) that crosses H makes the x loads of every token
-    // but the last read the start of the next token's row: finite values that meet W_r rows of
-    // zeros.
-    auto clamp32 = [](int64_t b) { return (unsigned)(b < 0 ? 0 : (b > 0xFFFFFFFFll ? 0xFFFFFFFFll : b)); };
-    auto issue = [&](int kt) {
-        unsigned char *st = lds + (kt & 1) * kStage;
-        const int k0 = kt * kRtK;
-        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(W_r + (int64_t)k0 * E + e0), 0, clamp32(((int64_t)(H - k0) * E - e0) * 4),
-            0x00020000);
-        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<unsigned char *>(static_cast<const unsigned char *>(x) + (n0 * H + k0) * kXb), 0,
-            clamp32(n_left > 0 ? (n_left * H - k0) * kXb : 0), 0x00020000);
-#pragma unroll
-        for (int g = 0; g < kWLoads; ++g)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rs_w, (__attribute__((address_space(3))) void *)(st + (wave * kWLoads + g) * 1024), 16,
-                w_off[g], 0, 0, 0);
-#pragma unroll
-        for (int g = 0; g < kXLoads; ++g)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rs_x, (__attribute__((address_space(3))) void *)(st + kWTile + wave * kXTile + g * 1024), 16,
-                x_off[g], 0, 0, 0);
-    };
-
-    float acc[kRtTok * kRtExp];
-#pragma unroll
-    for (int i = 0; i < kRtTok * kRtExp; ++i)
-        acc[i] = 0.0f;
-
-    const int KT = (H + kRtK - 1) / kRtK;
-    const int key = rt_key(lane); // rows lane and lane + 64 of a tile share the key bits
-    issue(0);
-    for (int kt = 0; kt < KT; ++kt) {
-        __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): tile kt has landed (own loads)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();       // ... and everyone's; tile kt-1 is no longer read
-        asm volatile("" ::: "memory");
-        if (kt + 1 < KT)
-            issue(kt + 1);
-        const unsigned char *st = lds + (kt & 1) * kStage;
-        const unsigned char *xs = st + kWTile + wave * kXTile;
-#pragma unroll
-        for (int sub = 0; sub < kRtK / kWave; ++sub) {
-            const int row = sub * kWave + lane; // tile row = column h of this lane
-            float wv[kRtExp];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const f32x4 w4 = *reinterpret_cast<const f32x4 *>(st + row * 64 + ((c ^ key) << 4));
-                wv[4 * c] = w4[0];
-                wv[4 * c + 1] = w4[1];
-                wv[4 * c + 2] = w4[2];
-                wv[4 * c + 3] = w4[3];
-            }
-            float xv[kRtTok];
-#pragma unroll
-            for (int t = 0; t < kRtTok; ++t) {
-                if (kBf16)
-                    xv[t] = bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(xs + t * kXRow + row * 2));
-                else
-                    xv[t] = *reinterpret_cast<const float *>(xs + t * kXRow + row * 4);
-            }
-            // columns past H: W_r came back as zeros (x may hold the next row's values): the
-            // products are +-0
-#pragma unroll
-            for (int t = 0; t < kRtTok; ++t)
-#pragma unroll
-                for (int j = 0; j < kRtExp; ++j)
-                    acc[t * kRtExp + j] = fmaf(xv[t], wv[j], acc[t * kRtExp + j]);
-        }
-    }
-
-    // fold the 64 partials of every (token, expert) pair: two groups of 64 pairs (experts 0-7, 8-15)
-    float lo[64], hi[64];
-#pragma unroll
-    for (int t = 0; t < kRtTok; ++t)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            lo[t * 8 + j] = acc[t * kRtExp + j];
-            hi[t * 8 + j] = acc[t * kRtExp + 8 + j];
-        }
-    fold_round<32>(lo, lane & 32);
-    fold_round<32>(hi, lane & 32);
-    fold_round<16>(lo, lane & 16);
-    fold_round<16>(hi, lane & 16);
-    fold_round<8>(lo, lane & 8);
-    fold_round<8>(hi, lane & 8);
-    fold_round<4>(lo, lane & 4);
-    fold_round<4>(hi, lane & 4);
-    fold_round<2>(lo, lane & 2);
-    fold_round<2>(hi, lane & 2);
-    fold_round<1>(lo, lane & 1);
-    fold_round<1>(hi, lane & 1);
-    const int t = lane / 8, j = lane % 8;
-    const int64_t n = n0 + t;
-    if (n < N) {
-        const int ea = e0 + j, eb = e0 + 8 + j;
-        if (ea < E) {
-            float v = lo[0];
-            if (bias)
-                v = v + bias[ea];
-            logits[n * E + ea] = v;
-        }
-        if (eb < E) {
-            float v = hi[0];
-            if (bias)
-                v = v + bias[eb];
-            logits[n * E + eb] = v;
-        }
-    }
-#endif
+        for (int i = 0; i < s; ++i)
+            v[i] = v[i] + v[i + s];
+    return v[0];
 }
 
-// ------------------------------------------------------------------------
-// The same tile on the matrix cores, without giving up the order of the sum.  v_mfma_f32_4x4x1_16B_f32
-// multiplies sixteen independent 4x1 by 1x4 pairs: with a reduction length of ONE every output is
-// exactly one fused multiply-add, d = fma(a, b, c) (checked bit for bit against fmaf, signed zeros and
-// subnormal products included), so nothing about the summation order is left to the hardware - and
-// the instruction retires 256 of them in 8 cycles, twice what the vector ALU does without packed
-// arithmetic.  The sixteen blocks of an instruction are sixteen different partial sums of R64:
-//   lane (blk = lane / 4, c = lane % 4), instruction (p, q, g):   partial l = 4 blk + g
-//     a operand: x[token 4p + c, h]          h = 64 step + l
-//     b operand: W_r[h, expert 4c + q]
-//     result register r:  partial l of (token 4p + r, expert 4c + q)
-// so a lane carries the same 128 accumulators as in the vector form, but now for all 8 tokens x 16
-// experts x 4 partials (g), and every K step of 64 columns is 32 instructions instead of 128.
-// LDS: the W_r tile keeps row h = 64 sub + 4 blk + g at row slot 64 sub + 16 g + blk (the loads
-// gather it that way), so the 16-byte read of lane (blk, c) for a given g - experts 4c .. 4c + 3, the
-// four q - is linear in the lane number; the x values of a lane for the four g are 4 consecutive
-// elements of one token row.  The folding rounds s = 32, 16, 8, 4 run between lanes (blk bits), as a
-// halving exchange; s = 2, 1 (g bits) inside the lane.
-// ------------------------------------------------------------------------
-template <int kHalf, int kXor>
-__device__ __forceinline__ void fold_lanes(float *v, bool upper)
+// Value of the lane `kRor` places away inside a row of sixteen lanes.
+template <int kRor, class T>
+__device__ __forceinline__ T row_ror(T v)
 {
-#pragma unroll
-    for (int i = 0; i < kHalf; ++i) {
-        float keep = upper ? v[i + kHalf] : v[i];
-        float send = upper ? v[i] : v[i + kHalf];
-        v[i] = keep + __shfl_xor(send, kXor);
-    }
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + kRor, 0xf, 0xf, true));
 }
-
-template <bool kBf16, int kRtKm>
-__global__ __launch_bounds__(kWave *kRtWaves, 2) void router_logits_mfma(
-    const void *__restrict__ x, int64_t N, int H, const float *__restrict__ W_r,
-    const float *__restrict__ bias, int E, float *__restrict__ logits)
+__device__ __forceinline__ float row_max16(float v)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int kXb = kBf16 ? 2 : 4;                  // bytes per x element
-    constexpr int kXRow = kRtKm * kXb;                   // bytes of one token row in a tile
-    constexpr int kXTile = kRtTok * kXRow;              // per wavefront
-    constexpr int kWTile = kRtKm * kRtExp * 4;           // 8 KiB
-    constexpr int kStage = kWTile + kRtWaves * kXTile;
-    constexpr int kXLoads = kXTile / 1024;              // per wavefront per tile
-    constexpr int kWLoads = kWTile / 1024 / kRtWaves;   // per wavefront per tile
-    static_assert(kRtTok == 8 && kRtExp == 16 && kRtKm % 64 == 0, "the index arithmetic below");
-    constexpr int kStages = MOE_RT_STAGES;               // LDS ring: the loads run kStages - 1 tiles ahead
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kStages * kStage];
-    const int lane = threadIdx.x % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int e0 = blockIdx.x * kRtExp;
-    const int64_t n0 = ((int64_t)blockIdx.y * kRtWaves + wave) * kRtTok;
-    const int blk = lane / 4, c = lane % 4;
-
-    // W_r: load instruction k of a tile fills row slots 16k .. 16k + 15, i.e. (sub, g) = (k / 4, k % 4):
-    // lane (blk', chunk) fetches chunk `chunk` of row 64 sub + 4 blk' + g
-    int w_off[kWLoads];
-#pragma unroll
-    for (int gl = 0; gl < kWLoads; ++gl) {
-        const int k = wave * kWLoads + gl;
-        const int r = 64 * (k / 4) + 4 * blk + (k % 4);
-        w_off[gl] = (r * E + c * 4) * 4;
-    }
-    const int64_t n_left = N - n0;
-    constexpr int kLanesPerRow = kXRow / 16;
-    int x_off[kXLoads];
-#pragma unroll
-    for (int gl = 0; gl < kXLoads; ++gl) {
-        const int t = gl * (kWave / kLanesPerRow) + lane / kLanesPerRow;
-        // 16-byte chunk j of token row t sits at chunk slot j ^ 4 (t % 4): the four rows a read below
-        // touches then fall into different quarters of the banks
-        x_off[gl] = (t * H + ((lane % kLanesPerRow) ^ ((t & 3) * 4)) * (16 / kXb)) * kXb;
-    }
-    // (the K tile's position goes into the resources, see router_logits_tiled)
-    auto clamp32 = [](int64_t b) { return (unsigned)(b < 0 ? 0 : (b > 0xFFFFFFFFll ? 0xFFFFFFFFll : b)); };
-    auto issue = [&](int kt) {
-        unsigned char *st = lds + (kt % kStages) * kStage;
-        const int k0 = kt * kRtKm;
-        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(W_r + (int64_t)k0 * E + e0), 0, clamp32(k0 < H ? ((int64_t)(H - k0) * E - e0) * 4 : 0),
-            0x00020000);
-        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<unsigned char *>(static_cast<const unsigned char *>(x) + (n0 * H + k0) * kXb), 0,
-            clamp32(n_left > 0 && k0 < H ? (n_left * H - k0) * kXb : 0), 0x00020000);
-#pragma unroll
-        for (int gl = 0; gl < kWLoads; ++gl)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rs_w, (__attribute__((address_space(3))) void *)(st + (wave * kWLoads + gl) * 1024), 16,
-                w_off[gl], 0, 0, 0);
-#pragma unroll
-        for (int gl = 0; gl < kXLoads; ++gl)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rs_x, (__attribute__((address_space(3))) void *)(st + kWTile + wave * kXTile + gl * 1024), 16,
-                x_off[gl], 0, 0, 0);
-    };
-
-    // acc[((p * 4 + q) * 4 + g)][r]
-    f32x4 acc[2 * 4 * 4];
-#pragma unroll
-    for (int i = 0; i < 32; ++i)
-        acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    const int KT = (H + kRtKm - 1) / kRtKm;
-    // (tiles past the last one are issued too: their resources hold no bytes, so they fetch nothing and
-    // the number of loads in flight stays what the wait below counts on)
-#pragma unroll
-    for (int t = 0; t + 1 < kStages; ++t)
-        issue(t);
-    for (int kt = 0; kt < KT; ++kt) {
-        // all but the loads of the kStages - 2 tiles after kt have landed (own loads)
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (((kStages - 2) * (kWLoads + kXLoads)) & 15) |
-                                   ((((kStages - 2) * (kWLoads + kXLoads)) >> 4) << 14));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();       // ... and everyone's; tile kt-1 is no longer read
-        asm volatile("" ::: "memory");
-        issue(kt + kStages - 1);
-        const unsigned char *st = lds + (kt % kStages) * kStage;
-        const unsigned char *xs = st + kWTile + wave * kXTile;
-#pragma unroll
-        for (int sub = 0; sub < kRtKm / kWave; ++sub) {
-            // b operands: for every g the four q of this lane's expert chunk
-            f32x4 wv[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                wv[g] = *reinterpret_cast<const f32x4 *>(st + (64 * sub + 16 * g + blk) * 64 + c * 16);
-            // a operands: for p = 0, 1 the four g of token 4p + c
-            float xv[2][4];
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const unsigned char *px = xs + (4 * p + c) * kXRow + (((64 * sub + 4 * blk) * kXb) ^ (c * 64));
-                if (kBf16) {
-                    const u32x2 raw = *reinterpret_cast<const u32x2 *>(px);
-                    xv[p][0] = __uint_as_float(raw[0] << 16);
-                    xv[p][1] = __uint_as_float(raw[0] & 0xFFFF0000u);
-                    xv[p][2] = __uint_as_float(raw[1] << 16);
-                    xv[p][3] = __uint_as_float(raw[1] & 0xFFFF0000u);
-                } else {
-                    const f32x4 raw = *reinterpret_cast<const f32x4 *>(px);
-                    xv[p][0] = raw[0], xv[p][1] = raw[1], xv[p][2] = raw[2], xv[p][3] = raw[3];
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        acc[(p * 4 + q) * 4 + g] =
-                            __builtin_amdgcn_mfma_f32_4x4x1f32(xv[p][g], wv[g][q], acc[(p * 4 + q) * 4 + g], 0, 0, 0);
-        }
-    }
-
-    // Fold.  v index bits, most significant first: p, q (2), r (2), g (2).  The rounds s = 32, 16, 8, 4
-    // of R64 pair partials that differ in a blk bit, i.e. lanes that differ in bit 5, 4, 3, 2; each
-    // halves what a lane keeps (by p, q.hi, q.lo, r.hi).  Left: r.lo x g, and s = 2, 1 pair g.
-    float v[128];
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    v[((p * 4 + q) * 4 + r) * 4 + g] = acc[(p * 4 + q) * 4 + g][r];
-    fold_lanes<64, 32>(v, lane & 32);
-    fold_lanes<32, 16>(v, lane & 16);
-    fold_lanes<16, 8>(v, lane & 8);
-    fold_lanes<8, 4>(v, lane & 4);
-    const int p_keep = (lane >> 5) & 1, q_keep = (lane >> 3) & 3, r_hi = (lane >> 2) & 1;
-#pragma unroll
-    for (int rl = 0; rl < 2; ++rl) {
-        const float *u = v + rl * 4;
-        const float w0 = u[0] + u[2], w1 = u[1] + u[3]; // s = 2
-        float val = w0 + w1;                             // s = 1
-        const int64_t n = n0 + 4 * p_keep + 2 * r_hi + rl;
-        const int e = e0 + 4 * c + q_keep;
-        if (n < N && e < E) {
-            if (bias)
-                val = val + bias[e];
-            logits[n * E + e] = val;
-        }
-    }
-#endif
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    return fmaxf(v, row_ror<1>(v));
+}
+__device__ __forceinline__ float row_sum16(float v)
+{
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    return v + row_ror<1>(v);
 }
 
 // (value, index) order of the selection: larger logit first, equal logits to the lower index.
@@ -496,13 +107,465 @@ __device__ __forceinline__ bool better(float va, int ia, float vb, int ib)
     return (va > vb) || (va == vb && ia < ib);
 }
 
-constexpr int kMaxPerLane = MOE_MAX_EXPERTS / kWave;
+__device__ __forceinline__ float score(float logit, float top, int score_mode)
+{
+    return score_mode == MOE_SCORE_SOFTMAX_TOPK ? expf(logit - top) : 1.0f / (1.0f + expf(-logit));
+}
 
-// One wavefront per token.  Lane l holds experts l, l+64, ...
+template <int kStep>
+__device__ __forceinline__ int count_better(float v, int e, int rank)
+{
+    if constexpr (kStep == 16) {
+        return rank;
+    } else {
+        if (better(row_ror<kStep>(v), row_ror<kStep>(e), v, e))
+            ++rank;
+        return count_better<kStep + 1>(v, e, rank);
+    }
+}
+
+// ------------------------------------------------------------------------
+// Small launches (and any E): a workgroup of eight wavefronts computes 16 tokens x 16 experts, every
+// wavefront an eighth of the partials (two instructions per step).  What bounds it is latency, so operands are
+// fetched three batches of kBatch steps ahead.  A wavefront's rows of W_r are its own and go straight to
+// registers; x goes through LDS (loaded there directly): in the operand layout neighbouring lanes hold different
+// tokens, and fetching it like that costs the vector cache one access per lane instead of one per 64 bytes.
+// With at most 16 experts a row of sixteen lanes holds all logits of a token and selects its top K at once
+// (kSelect): no second launch.
+// Routing with selection, 4x4x1 instructions on 32 tokens per workgroup before -> now: 1 token, H = 7168, 256
+// experts 45 -> 21 us; 37 tokens, H = 2880, 128 experts 24 -> 13; 128 / 4096 tokens, H = 4096, 8 experts 26 / 28 ->
+// 12 / 13; 4096 tokens, H = 1024, 30 experts 28 -> 13.
+// ------------------------------------------------------------------------
+template <bool kBf16, bool kSelect>
+__global__ __launch_bounds__(512, 2) void router_logits_small(
+    const void *__restrict__ x, int64_t N, int64_t H, const float *__restrict__ W_r, const float *__restrict__ bias,
+    int E, float *__restrict__ logits, int K, int score_mode, int32_t *__restrict__ topk_idx,
+    float *__restrict__ topk_w)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kSplit = 8, kG = 2, kXb = kBf16 ? 2 : 4, kBatch = 8, kSets = 4;
+    constexpr int kCols = kBatch * kWave;            // columns of a batch
+    constexpr int kXRow = kCols * kXb;               // bytes of a token's columns: 1 or 2 KiB
+    constexpr int kXStage = kRtTok * kXRow;
+    constexpr int kXLoads = kXStage / 1024 / kSplit; // per wavefront and batch
+    constexpr int kFold = kSplit * kG * 16 * kWave * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kSets * kXStage > kFold ? kSets * kXStage : kFold];
+    const int lane = threadIdx.x % kWave;
+    const int ps = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int blk = lane / 16, c = lane % 16;
+    const int e_tiles = (E + kRtExp - 1) / kRtExp;
+    const int e0 = (int)(blockIdx.x % e_tiles) * kRtExp;
+    const int64_t n0 = (int64_t)(blockIdx.x / e_tiles) * kRtTok;
+    const int l0 = 4 * kG * ps + kG * blk; // first of the lane's kG partials
+    const float *pw = W_r + (int64_t)l0 * E + (e0 + c < E ? e0 + c : E - 1);
+
+    // x: a load instruction of a wavefront fills 1 KiB; the 16-byte chunk at position p of token row r is chunk
+    // p ^ r, so that the operand reads (sixteen rows at one column) spread over the banks
+    const unsigned char *px[kXLoads];
+    int x_col[kXLoads]; // first column of the lane's chunk inside a batch
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i) {
+        const int at = (ps * kXLoads + i) * 1024 + lane * 16, r = at / kXRow;
+        x_col[i] = (((at % kXRow) / 16) ^ r) * (16 / kXb);
+        const int64_t tok = n0 + r < N ? n0 + r : N - 1;
+        px[i] = static_cast<const unsigned char *>(x) + (tok * H + x_col[i]) * kXb;
+    }
+    struct Weights {
+        float w[kBatch][kG];
+    };
+    // batch i: x into LDS stage `set`, W_r into registers.  Chunks of x past H: the row's first one (any values).
+    auto fetch = [&](Weights &b, int64_t i, int set) {
+        const int64_t h0 = i * kCols;
+        const bool whole = h0 + kCols <= H;
+#pragma unroll
+        for (int j = 0; j < kXLoads; ++j) {
+            const int64_t off = whole || h0 + x_col[j] < H ? h0 : -(int64_t)x_col[j];
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(px[j] + off * kXb),
+                (__attribute__((address_space(3))) void *)(lds + set * kXStage + (ps * kXLoads + j) * 1024), 16, 0, 0);
+        }
+        if (whole) {
+#pragma unroll
+            for (int s = 0; s < kBatch; ++s)
+#pragma unroll
+                for (int g = 0; g < kG; ++g)
+                    b.w[s][g] = pw[(h0 + s * kWave + g) * E];
+        } else {
+#pragma unroll
+            for (int s = 0; s < kBatch; ++s)
+#pragma unroll
+                for (int g = 0; g < kG; ++g) { // (H is even: both of the lane's columns or none)
+                    const bool in = h0 + s * kWave + l0 < H;
+                    const float v = pw[(in ? h0 + s * kWave + g : -(int64_t)l0) * E];
+                    b.w[s][g] = in ? v : 0.0f;
+                }
+        }
+    };
+
+    f32x16 acc[kG];
+#pragma unroll
+    for (int g = 0; g < kG; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            acc[g][r] = 0.0f;
+    auto multiply = [&](const Weights &b, int set) {
+        const unsigned char *row = lds + set * kXStage + c * kXRow;
+        XChunk<kBf16, kG> xv[kBatch];
+#pragma unroll
+        for (int s = 0; s < kBatch; ++s) {
+            const int byte = (s * kWave + l0) * kXb;
+            xv[s] = load_chunk<kBf16, kG>(row + (((byte / 16) ^ c) * 16 + byte % 16));
+        }
+#pragma unroll
+        for (int s = 0; s < kBatch; ++s)
+#pragma unroll
+            for (int g = 0; g < kG; ++g)
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x1f32(x_value(xv[s], g), b.w[s][g], acc[g], 0, 0, 0);
+    };
+    const int64_t batches = (H + kCols - 1) / kCols;
+    // batch i has landed (own loads: all but the ones of the two batches after it; everyone's: the barrier)
+    auto turn = [&](int64_t i, int set, const Weights &now, Weights &later) {
+        constexpr int kInFlight = 2 * (kXLoads + kBatch * kG);
+        __builtin_amdgcn_s_waitcnt(0x0070 | (kInFlight & 15) | (kInFlight >> 4 << 14)); // (and my reads of i - 1)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        fetch(later, i + 3 < batches ? i + 3 : batches - 1, (set + 3) % kSets); // (past the last: once more, unused)
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(now, set);
+    };
+    Weights w0, w1, w2, w3;
+    fetch(w0, 0, 0);
+    fetch(w1, 1 < batches ? 1 : batches - 1, 1);
+    fetch(w2, 2 < batches ? 2 : batches - 1, 2);
+    int64_t i = 0;
+    for (; i + 3 < batches; i += 4) {
+        turn(i, 0, w0, w3);
+        turn(i + 1, 1, w1, w0);
+        turn(i + 2, 2, w2, w1);
+        turn(i + 3, 3, w3, w2);
+    }
+    if (i < batches)
+        turn(i, 0, w0, w3);
+    if (i + 1 < batches)
+        turn(i + 1, 1, w1, w0);
+    if (i + 2 < batches)
+        turn(i + 2, 2, w2, w1);
+    __builtin_amdgcn_s_waitcnt(0x0F70); // the loads past the last batch (they write LDS too)
+    __syncthreads();
+
+    // fold: rounds 32, 16, 8 pair wavefronts ps and ps ^ 4, ^ 2, ^ 1
+    float *const part = reinterpret_cast<float *>(lds); // [wavefront][kG * 16][lane]
+#pragma unroll
+    for (int g = 0; g < kG; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            part[(ps * kG * 16 + g * 16 + r) * kWave + lane] = acc[g][r];
+    __syncthreads();
+    if (ps >= 4)
+        return;
+    const int t = ps; // this wavefront finishes tokens 4 q + t
+    float v[4 * kG];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int g = 0; g < kG; ++g) {
+            float p[kSplit];
+#pragma unroll
+            for (int w = 0; w < kSplit; ++w)
+                p[w] = part[(w * kG * 16 + g * 16 + 4 * b + t) * kWave + lane];
+#pragma unroll
+            for (int s = 4; s >= 1; s >>= 1)
+#pragma unroll
+                for (int w = 0; w < s; ++w)
+                    p[w] = p[w] + p[w + s];
+            v[b * kG + g] = p[0];
+        }
+    float val = fold_in_lane<kG>(v);
+    const int64_t n = n0 + 4 * blk + t;
+    const int e = e0 + c;
+    const bool there = n < N && e < E;
+    if (bias && there)
+        val = val + bias[e];
+    if (there && logits)
+        logits[n * E + e] = val;
+    if constexpr (kSelect) {
+        const float key = e < E ? val : -INFINITY;
+        const int rank = count_better<1>(key, e, 0);
+        const float top = row_max16(key);
+        const bool chosen = e < E && rank < K;
+        const float s = chosen ? score(val, top, score_mode) : 0.0f;
+        const float sum = row_sum16(s);
+        if (chosen && n < N) {
+            topk_idx[n * K + rank] = e;
+            topk_w[n * K + rank] = s / sum;
+        }
+    }
+#endif
+}
+
+// ------------------------------------------------------------------------
+// Large launches (E % 4 == 0): tiles of 32 tokens x 32 experts, a persistent workgroup of eight wavefronts per
+// compute unit.  A wavefront has 16 tokens x 16 experts and half of the partials (128 accumulators per lane, eight
+// instructions per step of 64 columns, two wavefronts per SIMD).  Operands go through LDS in K tiles of 128
+// columns, five stages (fp32: four), by loads that write LDS directly; the K tiles of a workgroup's successive
+// tiles are one stream, so that a tile starts with its operands in LDS and the fold runs under the next tile's
+// loads.  x chunks are XOR-placed by token, rows of W_r so that the operand reads of an instruction are linear in
+// the lane number: no bank conflicts.  The operands of step s + 1 are read under the multiplications of step s; the
+// barrier of a K tile stands before its last step's multiplications, and the loads that refill its stage go out
+// under them, with running addresses: both wavefronts of a SIMD are at the barrier together, and what they do
+// between it and the next multiplication leaves the matrix pipe idle.
+// 16384 tokens, H = 7168, 256 experts (60 GFLOP), selection included: 785 us with 4x4x1 instructions on tiles of
+// 32 x 16, two workgroups per compute unit -> 607 us, 99 of 157 TFLOP/s.  Those smaller tiles with the instruction
+// used here: 735 us, bound by their loads from L2 (14 TB/s, 550 us by themselves in a timing build; this tile asks
+// for half as much).  This form with the addresses worked out per K tile and a register shared by all values of x:
+// 822 us.
+// ------------------------------------------------------------------------
+constexpr int kRbTok = 32, kRbExp = 32, kRbWaves = 8;
+
+template <bool kBf16>
+__global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
+    const void *__restrict__ x, int64_t N, int H, const float *__restrict__ W_r, const float *__restrict__ bias,
+    int E, float *__restrict__ logits)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kG = 8, kXb = kBf16 ? 2 : 4;
+    constexpr int kTile = 128, kXRow = kTile * kXb;     // columns of a K tile
+    constexpr int kXPart = kRbTok * kXRow, kWPart = kTile * kRbExp * 4, kStage = kXPart + kWPart;
+    constexpr int kStages = kBf16 ? 5 : 4;              // 120 or 128 KiB
+    constexpr int kXLoads = kXPart / 1024 / kRbWaves, kWLoads = kWPart / 1024 / kRbWaves; // per wavefront and K tile
+    constexpr int kBox = kRbWaves * 2 * kG * kWave * 4; // the fold's exchange, 32 KiB
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kStages * kStage + kBox];
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int ps = wave % 2, tg = wave / 2 % 2, eg = wave / 4;
+    const int blk = lane / 16, c = lane % 16;
+
+    // ---- tiles.  Workgroup ids are dealt round-robin to the XCDs: an XCD takes all expert tiles of a token tile,
+    //      next to each other, so the tokens' rows are fetched once into its L2.
+    const int e_tiles = (E + kRbExp - 1) / kRbExp, xcd = blockIdx.x % 8, per_xcd = gridDim.x / 8;
+    const int64_t tok_tiles = (N + kRbTok - 1) / kRbTok;
+    struct Place { // tile i of this XCD is expert tile i % e_tiles of its token tile i / e_tiles
+        int64_t t;
+        int e;
+    };
+    const Place step = {per_xcd / e_tiles, per_xcd % e_tiles};
+    const Place first = {blockIdx.x / 8 / e_tiles, (int)(blockIdx.x / 8) % e_tiles};
+    auto advance = [&](Place &p) { // by per_xcd tiles
+        p.t += step.t;
+        p.e += step.e;
+        if (p.e >= e_tiles)
+            p.e -= e_tiles, ++p.t;
+    };
+    const int64_t my_tokens = tok_tiles > xcd ? (tok_tiles - 1 - xcd) / 8 + 1 : 0; // token tiles of this XCD
+    auto token_of = [&](const Place &p) { return (p.t * 8 + xcd) * kRbTok; };
+
+    // ---- loads of a K tile
+    int x_off[kXLoads], w_off[kWLoads];
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i) {
+        constexpr int kChunks = kXRow / 16;
+        const int r = (wave * kXLoads + i) * (kWave / kChunks) + lane / kChunks;
+        x_off[i] = r * H * kXb + (((lane % kChunks) ^ (r & 15)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < kWLoads; ++i) {
+        // block of 1 KiB = [expert half][eight slots][16 experts]; slot 4 u + b of block 8 s + 4 p + v holds row
+        // 64 s + 32 p + 8 b + 2 v + u
+        const int block = wave * kWLoads + i, slot = lane % 32 / 4;
+        const int row = (block / 8) * 64 + (block / 4 % 2) * 32 + (slot % 4) * 8 + (block % 4) * 2 + slot / 4;
+        w_off[i] = (row * E + (lane / 32) * kRtExp + (lane % 4) * 4) * 4;
+    }
+    // The position of a K tile goes into the base addresses and the byte counts of the resources: the range check
+    // covers the per-lane offset, and rows of W_r past H and tokens past N have to come back as zeros.  Columns past
+    // H of any token but the tile's last are the start of the next token's row: finite values that meet zeros.
+    // Kept as running values: little scalar work per K tile.
+    const int KT = (H + kTile - 1) / kTile;
+    Place load = first; // of the stream's next K tile: its tile ...
+    int load_kt = 0;    // ... and its position there
+    const unsigned char *x_at, *w_at;
+    int x_bytes, w_bytes;
+    auto load_from = [&]() { // (past the last tile: no bytes, so that the number of loads in flight stays)
+        const bool there = load.t < my_tokens;
+        const int64_t n = there ? token_of(load) : 0;
+        x_at = static_cast<const unsigned char *>(x) + n * H * kXb;
+        w_at = reinterpret_cast<const unsigned char *>(W_r + load.e * kRbExp);
+        x_bytes = there ? (int)(N - n < kRbTok ? N - n : kRbTok) * H * kXb : 0;
+        w_bytes = there ? (H * E - load.e * kRbExp) * 4 : 0;
+    };
+    load_from();
+    auto issue = [&](int stage) {
+        const __amdgpu_buffer_rsrc_t rs_x =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(x_at), 0, x_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs_w =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(w_at), 0, w_bytes, 0x00020000);
+        __attribute__((address_space(3))) unsigned char *const st =
+            (__attribute__((address_space(3))) unsigned char *)lds + stage * kStage;
+#pragma unroll
+        for (int i = 0; i < kXLoads; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs_x, (__attribute__((address_space(3))) void *)(st + (wave * kXLoads + i) * 1024), 16, x_off[i], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kWLoads; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs_w, (__attribute__((address_space(3))) void *)(st + kXPart + (wave * kWLoads + i) * 1024), 16, w_off[i], 0,
+                0, 0);
+        x_at += kTile * kXb;
+        x_bytes = x_bytes > kTile * kXb ? x_bytes - kTile * kXb : 0;
+        w_at += kTile * E * 4;
+        w_bytes = w_bytes > kTile * E * 4 ? w_bytes - kTile * E * 4 : 0;
+        if (++load_kt == KT) {
+            load_kt = 0;
+            advance(load);
+            load_from();
+        }
+    };
+
+    // ---- operands of a step
+    struct Operands {
+        XChunk<kBf16, kG> x;
+        float w[kG];
+    };
+    auto read = [&](Operands &o, int stage, int s) {
+        const unsigned char *st = lds + stage * kStage;
+        const unsigned char *row = st + (tg * kRtTok + c) * kXRow;
+        const int chunk = (64 * s + 32 * ps + 8 * blk) * kXb / 16; // one (bf16) or two (fp32) neighbouring chunks
+        if constexpr (kBf16) {
+            o.x = load_chunk<kBf16, kG>(row + ((chunk ^ c) << 4));
+        } else {
+            const u32x4 lo = *reinterpret_cast<const u32x4 *>(row + ((chunk ^ c) << 4));
+            const u32x4 hi = *reinterpret_cast<const u32x4 *>(row + (((chunk + 1) ^ c) << 4));
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                o.x.r[t] = lo[t], o.x.r[kG / 2 + t] = hi[t];
+        }
+        const unsigned char *pw = st + kXPart + ps * 4096 + eg * 512 + lane * 4;
+#pragma unroll
+        for (int g = 0; g < kG; ++g)
+            o.w[g] = *reinterpret_cast<const float *>(pw + s * 8192 + (g / 2) * 1024 + (g % 2) * 256);
+    };
+    f32x16 acc[kG];
+    float xv[kG];
+    auto unpack = [&](const Operands &o) {
+        // all eight values before the first multiplication: one register for all of them would make every
+        // instruction wait for the one before it
+#pragma unroll
+        for (int g = 0; g < kG; ++g)
+            xv[g] = x_value(o.x, g);
+        asm volatile("" : "+v"(xv[0]), "+v"(xv[1]), "+v"(xv[2]), "+v"(xv[3]), "+v"(xv[4]), "+v"(xv[5]), "+v"(xv[6]), "+v"(xv[7]));
+    };
+    auto multiply = [&](const Operands &o, auto lo, auto hi) {
+#pragma unroll
+        for (int g = decltype(lo)::value; g < decltype(hi)::value; ++g)
+            acc[g] = __builtin_amdgcn_mfma_f32_16x16x1f32(xv[g], o.w[g], acc[g], 0, 0, 0);
+    };
+    using from0 = std::integral_constant<int, 0>;
+    using from4 = std::integral_constant<int, kG / 2>;
+    using to8 = std::integral_constant<int, kG>;
+    auto barrier = [&]() { // (not __syncthreads, whose fence would wait for the loads in flight)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // my loads of the next K tile have landed (those of the tiles after it may be in flight), my reads are done
+    auto tile_barrier = [&]() {
+        constexpr int kInFlight = (kStages - 2) * (kXLoads + kWLoads);
+        __builtin_amdgcn_s_waitcnt(0x0070 | (kInFlight & 15) | (kInFlight >> 4 << 14));
+        barrier();
+    };
+    Operands o0, o1;
+#pragma unroll
+    for (int t = 0; t + 1 < kStages; ++t)
+        issue(t);
+    tile_barrier();
+    issue(kStages - 1);
+    read(o0, 0, 0);
+    int stage = 0;
+    float *const box = reinterpret_cast<float *>(lds + kStages * kStage); // [wavefront][2 * kG][lane]
+    for (Place at = first; at.t < my_tokens; advance(at)) {
+#pragma unroll
+        for (int g = 0; g < kG; ++g)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[g][r] = 0.0f;
+        for (int kt = 0; kt < KT; ++kt) {
+            read(o1, stage, 1); // (under the multiplications of the step before)
+            unpack(o0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(o0, from0{}, to8{});
+            __builtin_amdgcn_sched_barrier(0);
+            unpack(o1);
+            tile_barrier();
+            multiply(o1, from0{}, from4{});
+            __builtin_amdgcn_sched_barrier(0);
+            issue(stage); // all of this K tile is read: its stage takes another
+            stage = stage == kStages - 1 ? 0 : stage + 1;
+            read(o0, stage, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(o1, from4{}, to8{});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+        // Round 32 pairs the two wavefronts ps: each keeps tokens 4 q + 2 ps, + 1 of a block of 16 and sends the other
+        // two rows' partials, a block of partials at a time.
+        float v[2][4 * kG];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+#pragma unroll
+            for (int g = 0; g < kG; ++g)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    box[((wave ^ 1) * 2 * kG + 2 * g + u) * kWave + lane] = ps ? acc[g][4 * b + u] : acc[g][4 * b + 2 + u];
+            __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0)
+            barrier();
+#pragma unroll
+            for (int g = 0; g < kG; ++g)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    v[u][b * kG + g] = (ps ? acc[g][4 * b + 2 + u] : acc[g][4 * b + u]) +
+                                       box[(wave * 2 * kG + 2 * g + u) * kWave + lane];
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            barrier();
+        }
+        const int64_t n_tile = token_of(at);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float val = fold_in_lane<kG>(v[u]);
+            const int64_t n = n_tile + tg * kRtTok + 4 * blk + 2 * ps + u;
+            const int e = at.e * kRbExp + eg * kRtExp + c;
+            if (n < N && e < E) {
+                if (bias)
+                    val = val + bias[e];
+                logits[n * E + e] = val;
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070); // the loads past the last K tile (they write LDS too)
+#endif
+}
+
+// ------------------------------------------------------------------------
+// Selection.  One wavefront per token, lane l holds experts l, l+64, ... (kPer of them).  A round takes the
+// largest value over the wavefront by data-parallel-primitive moves (no LDS), then the lowest index that has it
+// (experts in ascending order are ballots of ascending i, lanes from the lowest).
 // kTakeRows: every routed row also takes its local row id from its expert's row pointer as it is
 // produced (Section IV-A3: the allocation unit hands out the next free row of a region on arrival);
 // rank[n*K + k] receives it, and the pointers end up as the experts' counts.
-template <bool kTakeRows>
+// ------------------------------------------------------------------------
+// lane 63's copy after folding all rows into it, for every lane
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = row_max16(v);
+    auto move = [](float f, auto ctrl, auto rows) { // rows that do not take part keep their own value
+        const int i = __builtin_bit_cast(int, f);
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+    };
+    v = fmaxf(v, move(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{})); // row_bcast:15
+    v = fmaxf(v, move(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{})); // row_bcast:31
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+}
+
+template <int kPer, bool kTakeRows>
 __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
     const float *__restrict__ logits, int64_t N, int E, int K, int score_mode,
     int32_t *__restrict__ topk_idx, float *__restrict__ topk_w, int32_t *__restrict__ row_pointer,
@@ -513,61 +576,42 @@ __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
     if (n >= N)
         return;
     const float *row = logits + n * E;
-    const int per = (E + kWave - 1) / kWave;
-    float val[kMaxPerLane];
+    float val[kPer]; // -infinity: not there, or taken
 #pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i) {
-        int e = i * kWave + lane;
-        val[i] = (i < per && e < E) ? row[e] : 0.0f;
+    for (int i = 0; i < kPer; ++i) {
+        const int e = i * kWave + lane;
+        val[i] = e < E ? row[e] : -INFINITY;
     }
-    uint32_t taken = 0;
-#pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i)
-        if (!(i < per && i * kWave + lane < E))
-            taken |= 1u << i; // slots past E never compete
-
-    float my_logit = 0.0f; // lane k keeps the k-th pick
+    float my_logit = 0.0f, top = 0.0f; // lane k keeps the k-th pick
     int my_pick = 0;
     for (int k = 0; k < K; ++k) {
-        float bv = 0.0f;
-        int bi = -1;
+        float best = val[0];
 #pragma unroll
-        for (int i = 0; i < kMaxPerLane; ++i) {
-            if (i < per && !(taken & (1u << i))) {
-                int e = i * kWave + lane;
-                if (bi < 0 || better(val[i], e, bv, bi)) {
-                    bv = val[i];
-                    bi = e;
-                }
+        for (int i = 1; i < kPer; ++i)
+            best = fmaxf(best, val[i]);
+        best = wave_max(best);
+        int pick = -1;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint64_t m = __ballot(val[i] == best);
+            if (pick < 0 && m != 0) {
+                const int at = __builtin_ctzll(m);
+                pick = i * kWave + at;
+                if (lane == at)
+                    val[i] = -INFINITY;
             }
         }
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) {
-            float ov = __shfl_xor(bv, s);
-            int oi = __shfl_xor(bi, s);
-            if (oi >= 0 && (bi < 0 || better(ov, oi, bv, bi))) {
-                bv = ov;
-                bi = oi;
-            }
-        }
-        // every lane agrees on (bv, bi); its owner retires it
-        if ((bi % kWave) == lane)
-            taken |= 1u << (bi / kWave);
+        if (k == 0)
+            top = best;
         if (lane == k) {
-            my_logit = bv;
-            my_pick = bi;
+            my_logit = best;
+            my_pick = pick;
         }
     }
-
-    const float top = __shfl(my_logit, 0);
-    float s = 0.0f;
-    if (lane < K)
-        s = (score_mode == MOE_SCORE_SOFTMAX_TOPK) ? expf(my_logit - top)
-                                                   : 1.0f / (1.0f + expf(-my_logit));
-    float sum = s;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1)
-        sum += __shfl_xor(sum, d);
+    const float s = lane < K ? score(my_logit, top, score_mode) : 0.0f;
+    float sum = row_sum16(s); // K <= 32: the first two rows of sixteen lanes
+    sum = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum), 0)) +
+          __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum), 16));
     if (lane < K) {
         topk_idx[n * K + lane] = my_pick;
         topk_w[n * K + lane] = s / sum;
@@ -576,45 +620,54 @@ __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
     }
 }
 
+template <bool kTakeRows>
+static void launch_topk(const float *logits, int64_t N, int E, int K, int score_mode, int32_t *topk_idx,
+                        float *topk_w, int32_t *row_pointer, int32_t *rank, hipStream_t st)
+{
+    auto kern = E <= kWave       ? router_topk<1, kTakeRows>
+                : E <= 2 * kWave ? router_topk<2, kTakeRows>
+                : E <= 4 * kWave ? router_topk<4, kTakeRows>
+                                 : router_topk<MOE_MAX_EXPERTS / kWave, kTakeRows>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(N, kRouteWaves)), dim3(kWave * kRouteWaves), 0, st, logits, N, E, K,
+                       score_mode, topk_idx, topk_w, row_pointer, rank);
+}
+
+template <bool kBf16>
+static void launch_logits(const void *x, int64_t N, int64_t H, const float *W_r, const float *bias, int E, int K,
+                          int score_mode, int32_t *topk_idx, float *topk_w, float *logits, bool select, hipStream_t st)
+{
+    const int64_t e_tiles = ceil_div(E, kRtExp);
+    // The large form once it has a tile for half of the compute units (512 tokens, H = 7168, 256 experts: 45 us
+    // against 49) and its 16-byte loads of W_r are aligned; below that the small form spreads over more of them.
+    const int64_t tiles = ceil_div(N, kRbTok) * ceil_div(E, kRbExp);
+    if (!select && E % 4 == 0 && tiles >= 128 && H * kRbTok * 4 < ((int64_t)1 << 31) && H * (int64_t)E * 4 < ((int64_t)1 << 31)) {
+        const int64_t groups = ceil_div(ceil_div(N, kRbTok), 8) * 8 * ceil_div(E, kRbExp);
+        hipLaunchKernelGGL(router_logits_large<kBf16>, dim3((unsigned)(groups < 256 ? groups : 256)), dim3(kWave * kRbWaves), 0,
+                           st, x, N, (int)H, W_r, bias, E, logits);
+        return;
+    }
+    const dim3 grid((unsigned)(ceil_div(N, kRtTok) * e_tiles));
+    if (select)
+        hipLaunchKernelGGL((router_logits_small<kBf16, true>), grid, dim3(512), 0, st, x, N, H, W_r, bias, E, logits, K,
+                           score_mode, topk_idx, topk_w);
+    else
+        hipLaunchKernelGGL((router_logits_small<kBf16, false>), grid, dim3(512), 0, st, x, N, H, W_r, bias, E, logits, K,
+                           score_mode, topk_idx, topk_w);
+}
+
 int launch_route(const void *x, int dtype, int64_t N, int64_t H, const float *W_r,
                  const float *bias, int E, int K, int score_mode, int32_t *topk_idx,
                  float *topk_w, float *logits, hipStream_t st, int32_t *row_pointer, int32_t *rank)
 {
-    const dim3 block(kWave * kRouteWaves);
-    if (E % 4 == 0 && H * (int64_t)E * 4 < ((int64_t)1 << 31) && H * 8 * 4 < ((int64_t)1 << 31)) {
-        const dim3 grid((unsigned)ceil_div(E, kRtExp), (unsigned)ceil_div(N, (int64_t)kRtTok * kRtWaves));
-#if MOE_ROUTER_MFMA
-        if (dtype == MOE_BF16 && E <= 2 * kRtExp)
-            hipLaunchKernelGGL((router_logits_mfma<true, kRtKLong>), grid, dim3(kWave * kRtWaves), 0, st, x, N, (int)H,
-                               W_r, bias, E, logits);
-        else if (dtype == MOE_BF16)
-            hipLaunchKernelGGL((router_logits_mfma<true, kRtKShort>), grid, dim3(kWave * kRtWaves), 0, st, x, N, (int)H,
-                               W_r, bias, E, logits);
-        else
-            hipLaunchKernelGGL((router_logits_mfma<false, kRtKShort>), grid, dim3(kWave * kRtWaves), 0, st, x, N, (int)H,
-                               W_r, bias, E, logits);
-#else
-        if (dtype == MOE_BF16)
-            hipLaunchKernelGGL(router_logits_tiled<true>, grid, dim3(kWave * kRtWaves), 0, st, x, N, (int)H, W_r,
-                               bias, E, logits);
-        else
-            hipLaunchKernelGGL(router_logits_tiled<false>, grid, dim3(kWave * kRtWaves), 0, st, x, N, (int)H, W_r,
-                               bias, E, logits);
-#endif
-    } else {
-        const dim3 grid1((unsigned)ceil_div(N, (int64_t)kTok * kRouteWaves), (unsigned)ceil_div(E, kExp));
-        if (dtype == MOE_BF16)
-            hipLaunchKernelGGL(router_logits<true>, grid1, block, 0, st, x, N, H, W_r, bias, E, logits);
-        else
-            hipLaunchKernelGGL(router_logits<false>, grid1, block, 0, st, x, N, H, W_r, bias, E, logits);
-    }
-    const dim3 grid2((unsigned)ceil_div(N, kRouteWaves));
-    if (row_pointer)
-        hipLaunchKernelGGL(router_topk<true>, grid2, block, 0, st, logits, N, E, K, score_mode, topk_idx, topk_w,
-                           row_pointer, rank);
+    const bool select = E <= kRtExp && !row_pointer; // the logits kernel selects as well
+    if (dtype == MOE_BF16)
+        launch_logits<true>(x, N, H, W_r, bias, E, K, score_mode, topk_idx, topk_w, logits, select, st);
     else
-        hipLaunchKernelGGL(router_topk<false>, grid2, block, 0, st, logits, N, E, K, score_mode, topk_idx, topk_w,
-                           (int32_t *)nullptr, (int32_t *)nullptr);
+        launch_logits<false>(x, N, H, W_r, bias, E, K, score_mode, topk_idx, topk_w, logits, select, st);
+    if (row_pointer)
+        launch_topk<true>(logits, N, E, K, score_mode, topk_idx, topk_w, row_pointer, rank, st);
+    else if (!select)
+        launch_topk<false>(logits, N, E, K, score_mode, topk_idx, topk_w, nullptr, nullptr, st);
     return check_launch("moe_route");
 }
 
