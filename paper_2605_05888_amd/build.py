@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe_hub.so")
-SOURCES = ["api.hip", "route.hip", "layout.hip", "rowmove.hip", "ffn.hip", "ffn_f32.hip"]
+SOURCES = ["api.hip", "route.hip", "layout.hip", "rowmove.hip", "ffn.hip", "ffn_f32.hip", "ffn_thin.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -19,6 +19,7 @@
 #include <atomic>
 
 #include "common.h"
+#include "ffn_thin.h"
 #include "grouped_gemm.h"
 
 namespace moe {
@@ -64,20 +65,21 @@ __device__ __forceinline__ int32_t clamped_rows(const int32_t *seg_offsets, int 
 
 // One launch builds the tables of both GEMMs: blockIdx.y picks the set of arguments.
 struct TableArgs {
+    int BM, extra; // rows of a tile; rows beyond them that the last full one may take
     int n_tiles, max_tiles, out_cols;
     TileTableHeader *hdr;
     TileEntry *table;
 };
 
 __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
-    const int32_t *__restrict__ seg_offsets, int E_local, int64_t M, int BM, int extra, int light_rows,
+    const int32_t *__restrict__ seg_offsets, int E_local, int64_t M, int light_rows,
     TableArgs gemm1, TableArgs gemm2, int32_t *__restrict__ ready)
 {
     const TableArgs &args = blockIdx.y == 0 ? gemm1 : gemm2;
     if (blockIdx.y == 0) // arrival counters of the row tiles start at zero with every schedule
         for (int64_t i = (int64_t)blockIdx.x * kSchedThreads + threadIdx.x; i < M; i += (int64_t)gridDim.x * kSchedThreads)
             ready[i] = 0;
-    const int n_tiles = args.n_tiles, max_tiles = args.max_tiles;
+    const int n_tiles = args.n_tiles, max_tiles = args.max_tiles, BM = args.BM, extra = args.extra;
     TileTableHeader *__restrict__ hdr = args.hdr;
     TileEntry *__restrict__ table = args.table;
     __shared__ int32_t start[2][MOE_MAX_EXPERTS + 1]; // first tile of each expert in the heavy [0] / light [1] stream
@@ -243,11 +245,30 @@ template <bool kSwiglu> using NarrowShallow = GemmCfg<64, 128, 1, 4, kSwiglu, 64
 constexpr int kNarrowTileBound = MOE_NARROW_TILE_BOUND;
 
 struct FfnPlan {
+    bool thin1, thin2; // GEMM1 / GEMM2 by ffn_thin.hip: that table holds row tiles only
     bool narrow2; // the down projection runs with NarrowBig / NarrowShallow
     int BM, out_cols1, out_cols2;
-    int n_tiles1, n_tiles2, max_m_tiles;
+    int n_tiles1, n_tiles2, max_m_tiles1, max_m_tiles2;
     size_t off_a, off_hdr1, off_tab1, off_hdr2, off_tab2, off_ready, total;
 };
+
+// Few rows per expert and fewer of the tiled kernel's tiles than compute units: ffn_thin.hip.  GEMM1 / GEMM2, rows per
+// expert given, tiled -> thin, us:
+//   4 experts, H 2048, F 1408 (44 / 32 tiles):   1: 40 / 23 -> 16 / 12    16: 42 / 25 -> 17 / 12    32: 46 / 28 -> 20 / 12
+//   8 experts, H 7168, F 2048 (128 / 224 tiles): 1: 136 / 63 -> 91 / 49   16: 135 / 63 -> 102 / 56  32: 140 / 64 -> 114 / 64
+//   2 experts, H 4096, F 14336 (224 / 32 tiles): 1: 91 / 104 -> 85 / 49   16: 96 / 110 -> 101 / 59  32: 98 / 112 -> 116 / 67
+// With many experts (64, H 2048, F 1408: 704 / 512 tiles) 151 / 74 -> 138 / 74, and 128 of H = F = 2880 642 / 334 ->
+// 830 / 405: workgroups that live this shortly spend too much of their time starting.  The bound on M keeps the worst case,
+// all rows with one expert, at a few passes over its weights, all but the first from the caches.
+constexpr int kThinMaxTiles = 224, kThinMaxTilesMany = 128, kThinMaxRows = 256;
+// From this many workgroups of four blocks of weight rows on, those instead of two blocks: rows of A are read half as
+// often (8 experts, H 7168, F 2048, 16 rows each: 114 -> 102 us), but with fewer the launch is too coarse (128: 49 -> 81).
+constexpr int kThinWideTiles = 384;
+static bool use_thin(int64_t M, int64_t experts, int64_t cols, int cols_per_tile)
+{
+    const int64_t tiles = experts * ceil_div(cols, cols_per_tile);
+    return M <= kThinMaxRows && (M <= 16 * experts ? tiles <= kThinMaxTiles : M <= 32 * experts && tiles <= kThinMaxTilesMany);
+}
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -260,21 +281,34 @@ static FfnPlan make_plan(int64_t M, int64_t H, int64_t F, int E_local)
     p.out_cols2 = p.narrow2 ? NarrowBig<false>::kOutCols : BigTile<false>::kOutCols;
     p.n_tiles1 = (int)ceil_div(F, p.out_cols1);
     p.n_tiles2 = (int)ceil_div(H, p.out_cols2);
-    p.max_m_tiles = (int)(M / p.BM) + E_local;
+    p.max_m_tiles1 = p.max_m_tiles2 = (int)(M / p.BM) + E_local;
     size_t o = 0;
     p.off_a = o;
     o = align_up(o + (size_t)M * F * 2, 256);
     p.off_hdr1 = o;
     o += kTileTableHeaderBytes;
     p.off_tab1 = o;
-    o = align_up(o + (size_t)p.max_m_tiles * p.n_tiles1 * sizeof(TileEntry), 256);
+    o = align_up(o + (size_t)p.max_m_tiles1 * p.n_tiles1 * sizeof(TileEntry), 256);
     p.off_hdr2 = o;
     o += kTileTableHeaderBytes;
     p.off_tab2 = o;
-    o = align_up(o + (size_t)p.max_m_tiles * p.n_tiles2 * sizeof(TileEntry), 256);
+    o = align_up(o + (size_t)p.max_m_tiles2 * p.n_tiles2 * sizeof(TileEntry), 256);
     p.off_ready = o; // per row: arrival counter of the row tile that starts there (dependency-driven launches)
     o = align_up(o + (size_t)M * sizeof(int32_t), 256);
     p.total = o;
+    // (the workspace's layout is the tiled form's, so that its size keeps growing with M)
+    const int thin_tiles = (int)(M / kThinRows + E_local < M ? M / kThinRows + E_local : M);
+    const int64_t experts = E_local < M ? E_local : M;
+    p.thin1 = use_thin(M, experts, F, BigTile<true>::kOutCols) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
+    p.thin2 = use_thin(M, experts, H, BigTile<false>::kOutCols) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
+    if (p.thin1) {
+        p.max_m_tiles1 = thin_tiles, p.n_tiles1 = 1;
+        p.out_cols1 = experts * ceil_div(F, 32) >= kThinWideTiles ? 32 : 16;
+    }
+    if (p.thin2) {
+        p.max_m_tiles2 = thin_tiles, p.n_tiles2 = 1;
+        p.out_cols2 = experts * ceil_div(H, 64) >= kThinWideTiles ? 64 : 32;
+    }
     return p;
 }
 
@@ -403,8 +437,8 @@ static FfnWorkspace carve(const FfnPlan &p, void *ws)
     k.tab1 = reinterpret_cast<TileEntry *>(w + p.off_tab1);
     k.hdr2 = reinterpret_cast<TileTableHeader *>(w + p.off_hdr2);
     k.tab2 = reinterpret_cast<TileEntry *>(w + p.off_tab2);
-    k.max1 = p.max_m_tiles * p.n_tiles1;
-    k.max2 = p.max_m_tiles * p.n_tiles2;
+    k.max1 = p.max_m_tiles1 * p.n_tiles1;
+    k.max2 = p.max_m_tiles2 * p.n_tiles2;
     k.ready = reinterpret_cast<int32_t *>(w + p.off_ready);
     return k;
 }
@@ -419,9 +453,9 @@ int launch_ffn_schedule(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     const FfnWorkspace k = carve(p, ws);
     const int max_both = k.max1 > k.max2 ? k.max1 : k.max2;
     hipLaunchKernelGGL(build_tile_table, dim3((unsigned)ceil_div(max_both, kSchedThreads), 2),
-                       dim3(kSchedThreads), 0, st, seg_offsets, E_local, M, p.BM, BigTile<true>::kExtra, kLightRows,
-                       TableArgs{p.n_tiles1, k.max1, p.out_cols1, k.hdr1, k.tab1},
-                       TableArgs{p.n_tiles2, k.max2, p.out_cols2, k.hdr2, k.tab2},
+                       dim3(kSchedThreads), 0, st, seg_offsets, E_local, M, kLightRows,
+                       TableArgs{p.thin1 ? kThinRows : p.BM, p.thin1 ? 0 : BigTile<true>::kExtra, p.n_tiles1, k.max1, p.out_cols1, k.hdr1, k.tab1},
+                       TableArgs{p.thin2 ? kThinRows : p.BM, p.thin2 ? 0 : BigTile<false>::kExtra, p.n_tiles2, k.max2, p.out_cols2, k.hdr2, k.tab2},
                        k.ready);
     return check_launch("moe_ffn_schedule");
 }
@@ -440,7 +474,9 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
     const FfnWorkspace k = carve(p, ws);
     const uint16_t *xpb = static_cast<const uint16_t *>(xp);
     const uint16_t *wg = static_cast<const uint16_t *>(W_gate), *wu = static_cast<const uint16_t *>(W_up);
-    if (gather_rows)
+    if (p.thin1)
+        launch_thin_gate_up(xpb, M, H, F, wg, wu, k.a, k.hdr1, k.tab1, p.max_m_tiles1, p.out_cols1, gather_rows, K, (uint32_t)(N * H * 2), st);
+    else if (gather_rows)
         launch_gemm<BigTile<true>, ShallowTile<true>, true, true>(xpb, M, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1,
                                                                   kPatch, st, gather_rows, K, (uint32_t)(N * H * 2));
     else
@@ -459,7 +495,9 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     const FfnWorkspace k = carve(p, ws);
     const uint16_t *wd = static_cast<const uint16_t *>(W_down);
     uint16_t *yb = static_cast<uint16_t *>(y);
-    if (p.narrow2)
+    if (p.thin2)
+        launch_thin_down(k.a, M, H, F, wd, yb, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, nullptr, 1, nullptr, st);
+    else if (p.narrow2)
         launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
     else
         launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
@@ -496,6 +534,10 @@ int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int
 {
     const FfnPlan p = make_plan(M, H, F, E_local);
     const FfnWorkspace k = carve(p, ws);
+    if (p.thin1 || p.thin2) { // a table of another form: two launches
+        const int rc = launch_ffn_gate_up(xp, MOE_BF16, M, H, F, E_local, nullptr, W_gate, W_up, ws, st, nullptr, 1, 0);
+        return rc != MOE_OK ? rc : launch_ffn_down(MOE_BF16, M, H, F, E_local, nullptr, W_down, y, ws, st);
+    }
     if (p.narrow2)
         launch_both<NarrowBig<false>, NarrowShallow<false>>(p, k, xp, M, H, F, W_gate, W_up, W_down, y, wait_limit, st);
     else
@@ -560,7 +602,10 @@ int launch_ffn_down_combine(int64_t N, int K, int64_t H, int64_t F, int E_local,
     const int64_t n16 = N * H / 4, n8 = N * H / 8;
     hipLaunchKernelGGL(fill_zero_16B, dim3((unsigned)ceil_div(n16, 256)), dim3(256), 0, st,
                        reinterpret_cast<u32x4 *>(sums), n16);
-    if (p.narrow2)
+    if (p.thin2)
+        launch_thin_down(k.a, M, H, F, static_cast<const uint16_t *>(W_down), sums, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, row_of_slot,
+                         K, topk_w, st);
+    else if (p.narrow2)
         launch_gemm<NarrowBig<false>, NarrowShallow<false>, false, false, true>(
             k.a, M, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
             reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, kPatch, st, row_of_slot, K, 0u, topk_w);

@@ -1,0 +1,81 @@
+"""The expert FFN's form for few rows (csrc/ffn_thin.hip) and the rule that picks it, against float64."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# H and F in K lines of 64 columns: one, fewer than the wavefronts, a remainder over the turns, and enough columns for
+# the wide form (E * F / 32 >= 384 and E * H / 64 >= 384)
+CASES = [
+    # rows per expert, H, F
+    ([1], 64, 64),
+    ([0, 1, 0, 15], 192, 128),
+    ([3, 0, 13, 16], 320, 576),
+    ([16, 17, 32, 1, 0, 30], 448, 64),          # M > 16: blocks of 16, 32 and 64 rows in one launch
+    ([33, 64, 2, 0, 1], 128, 1088),
+    ([65, 0, 1, 62, 0, 0, 0, 0], 576, 320),     # an expert with two row tiles
+    ([200] + [0] * 12 + [8, 1, 0], 256, 192),   # most rows with one expert
+    ([5] * 16, 1536, 896),                      # wide tiles in both GEMMs
+    ([64] + [0] * 30 + [1], 832, 448),          # wide tiles, row blocks of four
+    ([32] * 8, 256, 256),                       # the rule's last rows ...
+    ([33] * 8, 256, 256),                       # ... and the tiled kernel
+    ([16] * 16, 2048 + 64, 256),                # down projection tiled (more column tiles than the rule takes)
+]
+
+
+@pytest.mark.parametrize("rows,H,F", CASES, ids=[f"{len(r)}x{max(r)}-{h}-{f}" for r, h, f in CASES])
+def test_few_rows(rows, H, F):
+    import torch
+    import paper_2605_05888_amd as hub
+    print("few rows", rows, H, F, flush=True)
+    E, M = len(rows), sum(rows)
+    seg = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator().manual_seed(7)
+    normal = lambda shape, std: (torch.randn(shape, generator=g) * std).to(torch.bfloat16)
+    xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    want = torch.zeros(M, H, dtype=torch.float64)
+    for e in range(E):
+        x = xp[seg[e]:seg[e + 1]].double()
+        a = torch.nn.functional.silu(x @ Wg[e].double().T) * (x @ Wu[e].double().T)
+        want[seg[e]:seg[e + 1]] = a.to(torch.bfloat16).double() @ Wd[e].double().T
+    dev = lambda t: t.cuda()
+    dx, dg, du, dd, dseg = dev(xp), dev(Wg), dev(Wu), dev(Wd), dev(torch.from_numpy(seg))
+    ws = torch.empty(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    y = torch.full((M, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hub.moe_grouped_ffn(dx, dseg, dg, du, dd, y, ws)
+    hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+    got = y.cpu().double()
+    # one rounding of y (2^-9 at most), and the bf16 steps of `a` that fp32 and fp64 sums round to different sides:
+    # one in about sqrt(H) * 2^-24 / 2^-9 of its elements, far below the first
+    assert torch.isfinite(got).all()
+    assert float((got - want).norm() / want.norm()) < 2.0 ** -9
+    # rows fetched from x through a map, top-1: bit for bit the same
+    perm = torch.randperm(M, generator=g)
+    x = torch.empty_like(xp)
+    x[perm] = xp
+    y2 = torch.full_like(y, float("nan"))
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+    hub.moe_ffn_gate_up_gather(dev(x), 1, dseg, dev(perm.to(torch.int32)), dg, du, ws)
+    hub.moe_ffn_down(dseg, dd, y2, ws)
+    assert torch.equal(y, y2)
+    # ... both GEMMs in one call, and the down projection with the combine in it (top-1, weight 2: exact doubles)
+    y3 = torch.full_like(y, float("nan"))
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+    hub.moe_ffn_gate_up_down(dx, dseg, dg, du, dd, y3, ws)
+    assert torch.equal(y, y3)
+    sums, out = torch.empty(M, H, device="cuda"), torch.empty(M, H, dtype=torch.bfloat16, device="cuda")
+    weight = torch.full((M, 1), 2.0, device="cuda")
+    hub.moe_ffn_down_combine(1, dseg, dd, dev(perm.to(torch.int32)), weight, sums, out, ws)
+    assert torch.equal(out.cpu()[perm], (2.0 * y.float()).to(torch.bfloat16).cpu())
+
+
+def test_few_rows_need_their_schedule():
+    import torch
+    import paper_2605_05888_amd as hub
+    M, H, F, E = 4, 128, 128, 4
+    ws = torch.zeros(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    w = torch.zeros(E, F, H, dtype=torch.bfloat16, device="cuda")
+    seg = torch.arange(E + 1, dtype=torch.int32, device="cuda")
+    hub.moe_ffn_gate_up(torch.zeros(M, H, dtype=torch.bfloat16, device="cuda"), seg, w, w, ws)
+    with pytest.raises(hub.MoEHubError, match="MOE_ERR_STATE"):
+        hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
