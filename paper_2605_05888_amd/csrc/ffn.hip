@@ -30,14 +30,9 @@ namespace moe {
 constexpr int kSchedThreads = 256;
 // relative cost of a tile of a one-row-tile expert and of a full tile, for sharing out the workgroup slots
 constexpr int kLightCost = 3, kHeavyCost = 7;
-#ifndef MOE_ORDER_ROWS
-#define MOE_ORDER_ROWS 4
-#define MOE_ORDER_COLS 8
-#endif
 #ifndef MOE_ORDER_LONG_FIRST
 #define MOE_ORDER_LONG_FIRST 1
 #endif
-constexpr int kOrderRows = MOE_ORDER_ROWS, kOrderCols = MOE_ORDER_COLS; // block of the tile order inside an expert
 // experts with at most this many rows go through the shallow tile geometry
 constexpr int kLightRows = 64;
 
@@ -252,23 +247,26 @@ struct FfnPlan {
     size_t off_a, off_hdr1, off_tab1, off_hdr2, off_tab2, off_ready, total;
 };
 
-// Few rows per expert and fewer of the tiled kernel's tiles than compute units: ffn_thin.hip.  GEMM1 / GEMM2, rows per
-// expert given, tiled -> thin, us:
-//   4 experts, H 2048, F 1408 (44 / 32 tiles):   1: 40 / 23 -> 16 / 12    16: 42 / 25 -> 17 / 12    32: 46 / 28 -> 20 / 12
-//   8 experts, H 7168, F 2048 (128 / 224 tiles): 1: 136 / 63 -> 91 / 49   16: 135 / 63 -> 102 / 56  32: 140 / 64 -> 114 / 64
-//   2 experts, H 4096, F 14336 (224 / 32 tiles): 1: 91 / 104 -> 85 / 49   16: 96 / 110 -> 101 / 59  32: 98 / 112 -> 116 / 67
-// With many experts (64, H 2048, F 1408: 704 / 512 tiles) 151 / 74 -> 138 / 74, and 128 of H = F = 2880 642 / 334 ->
-// 830 / 405: workgroups that live this shortly spend too much of their time starting.  The bound on M keeps the worst case,
-// all rows with one expert, at a few passes over its weights, all but the first from the caches.
-constexpr int kThinMaxTiles = 224, kThinMaxTilesMany = 128, kThinMaxRows = 256;
-// From this many workgroups of four blocks of weight rows on, those instead of two blocks: rows of A are read half as
-// often (8 experts, H 7168, F 2048, 16 rows each: 114 -> 102 us), but with fewer the launch is too coarse (128: 49 -> 81).
-constexpr int kThinWideTiles = 384;
-static bool use_thin(int64_t M, int64_t experts, int64_t cols, int cols_per_tile)
+// Few rows per expert, and so few of the tiled kernel's tiles that compute units stay idle: ffn_thin.hip.  GEMM1 / GEMM2,
+// rows per expert given, tiled -> thin, us:
+//   4 experts, H 2048, F 1408 (44 / 64 tiles):   1: 40 / 23 -> 16 / 12    16: 42 / 25 -> 17 / 12    32: 46 / 28 -> 20 / 12
+//   8 experts, H 7168, F 2048 (128 / 448 tiles): 1: 136 / 63 -> 91 / 49   16: 135 / 63 -> 102 / 56  32: 140 / 64 -> 114 / 64
+//   2 experts, H 4096, F 14336 (224 / 64 tiles): 1: 91 / 104 -> 85 / 49   16: 96 / 110 -> 101 / 59  32: 98 / 112 -> 116 / 67
+//   8 experts, H 4096, F 14336 (896 / 256 tiles): 1: 352 / 159 -> 323 / 176                         32: 372 / 167 -> 415 / 220
+// A tile of a short reduction is mostly start and end, hence the higher limit there.  With many experts (128 of H = F =
+// 2880: 642 / 334 -> 830 / 405) thin workgroups are too short-lived themselves.  The bound on M keeps the worst case, all
+// rows with one expert, at a few passes over its weights, all but the first from the caches.
+constexpr int kThinMaxRows = 256;
+static bool use_thin(int64_t M, int64_t experts, int64_t tiles, int64_t Kdim)
 {
-    const int64_t tiles = experts * ceil_div(cols, cols_per_tile);
-    return M <= kThinMaxRows && (M <= 16 * experts ? tiles <= kThinMaxTiles : M <= 32 * experts && tiles <= kThinMaxTilesMany);
+    if (M > kThinMaxRows || M > 32 * experts)
+        return false;
+    return tiles <= 128 || (tiles <= 224 && M <= 4 * experts) || (tiles <= 448 && M <= 16 * experts && Kdim <= 2048);
 }
+// Workgroups of four blocks of weight rows instead of two read the rows of A half as often: better once there are some
+// rows and enough workgroups (8 experts, H 7168, F 2048, 16 rows each, 512 of them: 114 -> 102 us; one row: 91 -> 91; 2
+// experts, F 14336, 1 row: 85 -> 92; 128 of them, K 14336: 49 -> 81).
+static bool wide_thin(int64_t M, int64_t experts, int64_t workgroups) { return M > 4 * experts && workgroups >= 384; }
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -299,15 +297,15 @@ static FfnPlan make_plan(int64_t M, int64_t H, int64_t F, int E_local)
     // (the workspace's layout is the tiled form's, so that its size keeps growing with M)
     const int thin_tiles = (int)(M / kThinRows + E_local < M ? M / kThinRows + E_local : M);
     const int64_t experts = E_local < M ? E_local : M;
-    p.thin1 = use_thin(M, experts, F, BigTile<true>::kOutCols) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
-    p.thin2 = use_thin(M, experts, H, BigTile<false>::kOutCols) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
+    p.thin1 = use_thin(M, experts, experts * p.n_tiles1, H) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
+    p.thin2 = use_thin(M, experts, experts * p.n_tiles2, F) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
     if (p.thin1) {
         p.max_m_tiles1 = thin_tiles, p.n_tiles1 = 1;
-        p.out_cols1 = experts * ceil_div(F, 32) >= kThinWideTiles ? 32 : 16;
+        p.out_cols1 = wide_thin(M, experts, experts * ceil_div(F, 32)) ? 32 : 16;
     }
     if (p.thin2) {
         p.max_m_tiles2 = thin_tiles, p.n_tiles2 = 1;
-        p.out_cols2 = experts * ceil_div(H, 64) >= kThinWideTiles ? 64 : 32;
+        p.out_cols2 = wide_thin(M, experts, experts * ceil_div(H, 64)) ? 64 : 32;
     }
     return p;
 }
@@ -376,17 +374,28 @@ static size_t lds_bytes_of()
     return b;
 }
 
-static GemmArgs gemm_args(const uint16_t *A, int64_t M, int Kdim, int Ndim, const uint16_t *B0, const uint16_t *B1,
+// Weight rows a multiple of 4 KiB apart: workgroups that all start at column 0 ask the same few memory channels, and
+// being equally fast they go on doing so.  Such a launch starts every column tile (experts with one shallow row tile) or
+// block of eight (so that tiles that share operands in an XCD's L2 stay together) 2 KiB further on.  GEMM1 of 64 experts,
+// F 2560, 16 / 144 rows each, us: K 2048 276 / 349 -> 230 / 312, K 4096 481 / 645 -> 430 / 566, K 6144 716 / 949 -> 640 /
+// 831, K 8192 904 / 1192 -> 843 / 1088.  Other strides spread by themselves and lose up to 4 % (K 2560, 3072, 3584).  Above
+// 8192 the rows of A that the turned tiles share no longer fit the L2 (K 14336, 256 rows: 268 -> 281).  From 512 rows per
+// expert on the matrix cores bound the launch and it is up to 1 % slower.
+constexpr int kChannelStride = 4096, kTurnTiles = 16, kMaxTurnedK = 8192;
+constexpr int64_t kMaxTurnedRows = 512;
+
+static GemmArgs gemm_args(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0, const uint16_t *B1,
                           uint16_t *C, TileTableHeader *hdr, const TileEntry *table, int patch)
 {
     GemmArgs g = {};
     g.A = A, g.M = M, g.Kdim = Kdim, g.Ndim = Ndim, g.B0 = B0, g.B1 = B1, g.C = C, g.hdr = hdr, g.table = table;
     g.patch = patch, g.gather_div = 1;
+    g.k_turn = (int64_t)Kdim * 2 % kChannelStride == 0 && Kdim <= kMaxTurnedK && M < kMaxTurnedRows * E_local ? kTurnTiles : 0;
     return g;
 }
 
 template <class Main, class Light, bool kSwiglu, bool kGather = false, bool kScatter = false>
-static void launch_gemm(const uint16_t *A, int64_t M, int Kdim, int Ndim, const uint16_t *B0,
+static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0,
                         const uint16_t *B1, uint16_t *C, TileTableHeader *hdr,
                         const TileEntry *table, int patch, hipStream_t st,
                         const int32_t *gather_rows = nullptr, int gather_div = 1, uint32_t gather_bytes = 0,
@@ -396,7 +405,7 @@ static void launch_gemm(const uint16_t *A, int64_t M, int Kdim, int Ndim, const 
     const size_t lds_bytes = lds_bytes_of<Main, Light>();
     static std::atomic<uint64_t> raised{0};
     allow_lds(kern, lds_bytes, raised);
-    GemmArgs g = gemm_args(A, M, Kdim, Ndim, B0, B1, C, hdr, table, patch);
+    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, patch);
     g.gather_rows = gather_rows, g.gather_div = gather_div, g.gather_bytes = gather_bytes, g.scatter_w = scatter_w;
     // persistent grid: the workgroups draw their tiles from the table's counters
     const int grid = workgroup_slots(Main::kLdsBytes <= 80 * 1024 ? 2 : 1);
@@ -477,10 +486,10 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
     if (p.thin1)
         launch_thin_gate_up(xpb, M, H, F, wg, wu, k.a, k.hdr1, k.tab1, p.max_m_tiles1, p.out_cols1, gather_rows, K, (uint32_t)(N * H * 2), st);
     else if (gather_rows)
-        launch_gemm<BigTile<true>, ShallowTile<true>, true, true>(xpb, M, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1,
+        launch_gemm<BigTile<true>, ShallowTile<true>, true, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1,
                                                                   kPatch, st, gather_rows, K, (uint32_t)(N * H * 2));
     else
-        launch_gemm<BigTile<true>, ShallowTile<true>, true>(xpb, M, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, kPatch, st);
+        launch_gemm<BigTile<true>, ShallowTile<true>, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, kPatch, st);
     return check_launch("moe_ffn_gate_up");
 }
 
@@ -498,15 +507,15 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     if (p.thin2)
         launch_thin_down(k.a, M, H, F, wd, yb, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, nullptr, 1, nullptr, st);
     else if (p.narrow2)
-        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
+        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
     else
-        launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
+        launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
     return check_launch("moe_ffn_down");
 }
 
 // Both GEMMs in one launch, the second consuming the first's rows tile by tile (after launch_ffn_schedule).
 template <class Main2, class Light2>
-static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp, int64_t M, int64_t H, int64_t F,
+static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp, int64_t M, int64_t H, int64_t F, int E_local,
                         const void *W_gate, const void *W_up, const void *W_down, void *y, int64_t wait_limit,
                         hipStream_t st)
 {
@@ -517,9 +526,9 @@ static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp,
     lds_bytes = lds_bytes > lds_bytes_of<Main2, Light2>() ? lds_bytes : lds_bytes_of<Main2, Light2>();
     static std::atomic<uint64_t> raised{0};
     allow_lds(kern, lds_bytes, raised);
-    GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
+    GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
                             static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, kPatch);
-    GemmArgs g2 = gemm_args(k.a, M, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
+    GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
                             static_cast<uint16_t *>(y), k.hdr2, k.tab2, kPatch);
     g1.ready = g2.ready = k.ready;
     g1.hdr_dep = g2.hdr_dep = k.hdr1;
@@ -539,9 +548,9 @@ int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int
         return rc != MOE_OK ? rc : launch_ffn_down(MOE_BF16, M, H, F, E_local, nullptr, W_down, y, ws, st);
     }
     if (p.narrow2)
-        launch_both<NarrowBig<false>, NarrowShallow<false>>(p, k, xp, M, H, F, W_gate, W_up, W_down, y, wait_limit, st);
+        launch_both<NarrowBig<false>, NarrowShallow<false>>(p, k, xp, M, H, F, E_local, W_gate, W_up, W_down, y, wait_limit, st);
     else
-        launch_both<BigTile<false>, ShallowTile<false>>(p, k, xp, M, H, F, W_gate, W_up, W_down, y, wait_limit, st);
+        launch_both<BigTile<false>, ShallowTile<false>>(p, k, xp, M, H, F, E_local, W_gate, W_up, W_down, y, wait_limit, st);
     return check_launch("moe_ffn_gate_up_down");
 }
 
@@ -607,11 +616,11 @@ int launch_ffn_down_combine(int64_t N, int K, int64_t H, int64_t F, int E_local,
                          K, topk_w, st);
     else if (p.narrow2)
         launch_gemm<NarrowBig<false>, NarrowShallow<false>, false, false, true>(
-            k.a, M, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
+            k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
             reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, kPatch, st, row_of_slot, K, 0u, topk_w);
     else
         launch_gemm<BigTile<false>, ShallowTile<false>, false, false, true>(
-            k.a, M, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
+            k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
             reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, kPatch, st, row_of_slot, K, 0u, topk_w);
     hipLaunchKernelGGL(round_sums_bf16, dim3((unsigned)ceil_div(n8, 256)), dim3(256), 0, st,
                        reinterpret_cast<const f32x4 *>(sums), static_cast<u32x4 *>(out), n8);

@@ -54,6 +54,12 @@ struct TileEntry {
 };
 constexpr int kTileColBits = 24;
 
+#ifndef MOE_ORDER_ROWS
+#define MOE_ORDER_ROWS 4
+#define MOE_ORDER_COLS 8
+#endif
+constexpr int kOrderRows = MOE_ORDER_ROWS, kOrderCols = MOE_ORDER_COLS; // block of the tile order inside an expert
+
 constexpr int kXcds = 8;
 constexpr int kMaxGemmWorkgroups = 896; // workgroups of the persistent grid (ticket words of a table)
 
@@ -258,6 +264,7 @@ struct GemmArgs {
     TileTableHeader *hdr;
     const TileEntry *table;
     int patch;
+    int k_turn; // K tiles by which the start of the reduction moves on from column tile (light tiles) or block of them to the next
     const int32_t *gather_rows;
     int gather_div;
     uint32_t gather_bytes;
@@ -478,12 +485,15 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         uint32_t a_bytes, b_bytes;
         int32_t m0, m_end, n0;
         int32_t ext; // rows beyond BM (tall tiles)
+        int32_t k0;  // K tile the reduction starts with (it wraps around)
     };
     auto operands_of = [&](int tile) {
-        Operands o = {A, B0, 0u, 0u, 0, 0, 0, 0};
+        Operands o = {A, B0, 0u, 0u, 0, 0, 0, 0, 0};
         if (tile >= 0) {
             const TileEntry te = table[entry_of(tile)];
-            const int n0 = (te.n_tile & ((1 << kTileColBits) - 1)) * Cfg::kOutCols;
+            const int col = te.n_tile & ((1 << kTileColBits) - 1);
+            const int n0 = col * Cfg::kOutCols;
+            o.k0 = (int)((uint32_t)(Cfg::kKind == 1 ? col : col / kOrderCols) * (uint32_t)g.k_turn % (uint32_t)KT);
             o.ext = kTall ? te.n_tile >> kTileColBits : 0;
             const int64_t rows_left = (int64_t)te.m_end - te.m0; // >= 1
             const int cols_left = Ndim - n0;                      // >= 1
@@ -501,6 +511,11 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             o.n0 = n0;
         }
         return o;
+    };
+    // byte offset of K tile t of a tile inside its rows
+    auto k_offset = [&](int t, int k0) {
+        const int k = t + k0;
+        return (k >= KT ? k - KT : k) * (kBK * 2);
     };
     Operands cur, nxt; // the tile being computed; the one whose first K tiles are fetched behind it
     // kGather: the lane's rows of a tile -> their entries of gather_rows (rows past the segment: ~0) ...
@@ -558,7 +573,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     auto load_x = [&](auto ks_tag, int t, bool half) {
         constexpr int ks = decltype(ks_tag)::value;
         const u32x4 rs = x_resource(t < KT);
-        const int voff = x_voffset(half), soff = t * (kBK * 2) + ks * 32;
+        const int voff = x_voffset(half), soff = k_offset(t, cur.k0) + ks * 32;
         u32x4 &dst = xa[ks < kXRegs ? ks : 0]; // (a generic lambda does not capture through an asm operand)
         asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "+v"(dst) : "v"(voff), "s"(rs), "s"(soff));
     };
@@ -566,7 +581,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     auto load_x_first = [&](bool half) {
         static_assert(!kTall || kXRegs == 4, "four k-steps per K tile");
         const u32x4 rs = x_resource(true);
-        const int voff = x_voffset(half);
+        const int voff = x_voffset(half) + k_offset(0, cur.k0);
         u32x4 &d0 = xa[0], &d1 = xa[kXRegs > 1 ? 1 : 0], &d2 = xa[kXRegs > 2 ? 2 : 0], &d3 = xa[kXRegs > 3 ? 3 : 0];
         asm volatile("buffer_load_dwordx4 %0, %4, %5, 0 offen\n\t"
                      "buffer_load_dwordx4 %1, %4, %5, 0 offen offset:32\n\t"
@@ -585,7 +600,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs, (lds_ptr)(lds + Cfg::unit_base(unit) + (wave * Cfg::kAGroups + g) * 1024), 16,
             kGather ? (int)((here ? cur_row[g] : nxt_row[g]) + (uint32_t)a_off[g]) : a_off[g],
-            (here ? t : t - KT) * (kBK * 2), 0, 0);
+            k_offset(here ? t : t - KT, here ? cur.k0 : nxt.k0), 0, 0);
     };
     auto load_b_group = [&](int t, int unit, int g, auto tail_tag) {
         constexpr bool kTail = decltype(tail_tag)::value;
@@ -599,7 +614,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         // hint (aux bit 1) they do not push the other tiles' shared operands out of the caches.
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs, (lds_ptr)(lds + Cfg::unit_base(unit) + (wave * Cfg::kBGroups + g) * 1024), 16, b_off[g],
-            (here ? t : t - KT) * (kBK * 2), 0, Cfg::kKind == 1 ? MOE_LIGHT_AUX : 0);
+            k_offset(here ? t : t - KT, here ? cur.k0 : nxt.k0), 0, Cfg::kKind == 1 ? MOE_LIGHT_AUX : 0);
     };
 
     // ---- the ring.  K tile t keeps the rows of its "far" operand (the one whose loads run ahead in

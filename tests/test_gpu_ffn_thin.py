@@ -5,7 +5,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 # H and F in K lines of 64 columns: one, fewer than the wavefronts, a remainder over the turns, and enough columns for
-# the wide form (E * F / 32 >= 384 and E * H / 64 >= 384)
+# the wide form (more than 4 rows per expert, E * F / 32 and E * H / 64 at least 384)
 CASES = [
     # rows per expert, H, F
     ([1], 64, 64),
@@ -19,7 +19,9 @@ CASES = [
     ([64] + [0] * 30 + [1], 832, 448),          # wide tiles, row blocks of four
     ([32] * 8, 256, 256),                       # the rule's last rows ...
     ([33] * 8, 256, 256),                       # ... and the tiled kernel
-    ([16] * 16, 2048 + 64, 256),                # down projection tiled (more column tiles than the rule takes)
+    ([16] * 16, 4096 + 64, 256),                # down projection tiled (more column tiles than the rule takes)
+    ([4] * 8, 64, 128 * 28),                    # most column tiles with a few rows ...
+    ([5] * 8, 64, 128 * 28),                    # ... and short reductions
 ]
 
 

@@ -1,0 +1,47 @@
+"""Reductions that start past the first column and wrap around (rows of the weights a multiple of 4 KiB apart, up to 8192
+columns), in every form of tile: shallow, ragged, tall by a shared and by an own block row, several row tiles."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [300, 20, 64, 65, 276, 1, 0, 530]
+SIZES = [(2048, 128 * 17 + 64),  # gate/up turned: shallow tiles at 0 and 1 K tiles of 16, others from column tile 8 on
+         (256 * 17 + 64, 2048),  # down projection turned
+         (4096, 4096),           # both, four starting points
+         (6144, 1216)]           # a number of K tiles that 16 does not divide evenly into turns
+
+
+@pytest.mark.parametrize("H,F", SIZES)
+def test_turned_reduction(H, F):
+    import torch
+    import paper_2605_05888_amd as hub
+    print("turned", H, F, flush=True)
+    E, M = len(ROWS), sum(ROWS)
+    seg = np.concatenate([[0], np.cumsum(ROWS)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    dseg = torch.from_numpy(seg).cuda()
+    ws = torch.empty(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    y = torch.full((M, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hub.moe_grouped_ffn(xp, dseg, Wg, Wu, Wd, y, ws)
+    hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+    for e in range(E):
+        lo, hi = int(seg[e]), int(seg[e + 1])
+        if lo == hi:
+            continue
+        x = xp[lo:hi].double()
+        a = torch.nn.functional.silu(x @ Wg[e].double().T) * (x @ Wu[e].double().T)
+        want = a.to(torch.bfloat16).double() @ Wd[e].double().T
+        # one rounding of y (2^-9 at most); bf16 steps of `a` that fall on the other side are far rarer than that
+        assert float((y[lo:hi].double() - want).norm() / want.norm()) < 2.0 ** -9, e
+    # rows fetched through a map: bit for bit the same
+    perm = torch.randperm(M, generator=torch.Generator().manual_seed(3)).cuda()
+    x = torch.empty_like(xp)
+    x[perm] = xp
+    y2 = torch.full_like(y, float("nan"))
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+    hub.moe_ffn_gate_up_gather(x, 1, dseg, perm.to(torch.int32), Wg, Wu, ws)
+    hub.moe_ffn_down(dseg, Wd, y2, ws)
+    assert torch.equal(y, y2)
