@@ -10,6 +10,7 @@
 //           its cursors at offset[e] + unit_base[e][u] and walks its unit 64 rows
 //           at a time; inside a 64-row step the rank among equal experts comes
 //           from wavefront ballots, so the order is ascending r everywhere.
+// Up to kOneRows rows one workgroup does all three (layout_one_group).
 #include <atomic>
 
 #include "common.h"
@@ -196,6 +197,77 @@ __global__ __launch_bounds__(kWave *kWavesPerBlock) void layout_assign_slots(
     }
 }
 
+// ------------------------------------------------------------------------
+// Few rows: the three passes in one workgroup.  A wavefront owns kSteps * 64 consecutive rows and keeps their
+// experts and their ranks among its own rows in registers; the counts of all wavefronts meet in LDS.
+// Both forms wait for latency: here two memory round trips and one launch instead of six and three.  Captured calls, us,
+// E = 8 / 64 / 256: 256 rows 9.8 / 12.5 / 15.6 -> 3.1 / 3.3 / 4.0, 1024 rows 10.2 / 12.7 / 15.8 -> 3.5 / 3.8 / 4.6, 4096
+// rows 10.6 / 13.5 / 17.1 -> 5.5 / 6.8 / 8.1, 8192 rows - / 13.6 / 17.2 -> - / 10.4 / 13.1.  Every further 1024 rows take
+// 1.0 to 1.3 us more on the one compute unit and nothing there, so the line is drawn at 8192.
+// ------------------------------------------------------------------------
+constexpr int kOneWaves = 16, kOneRows = 8 * kOneWaves * kWave;
+
+template <int kSteps>
+__global__ __launch_bounds__(kWave *kOneWaves) void layout_one_group(
+    const int32_t *__restrict__ idx, int R, int E, int G, int nbits, int32_t *__restrict__ expert_counts,
+    int32_t *__restrict__ expert_offsets, int32_t *__restrict__ dest_counts, int32_t *__restrict__ dest_offsets,
+    int32_t *__restrict__ slot_of_row, int32_t *__restrict__ row_of_slot)
+{
+    extern __shared__ int32_t lds[]; // counts [wavefront][E], totals [E], offsets [E + 1]
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    int32_t *const cnt = lds + wave * E, *const total = lds + kOneWaves * E, *const off = total + E;
+    int ev[kSteps], rank[kSteps];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int r = (wave * kSteps + s) * kWave + lane;
+        const int e = r < R ? idx[r] : -1;
+        ev[s] = e < E ? e : -1;
+    }
+    for (int e = lane; e < E; e += kWave)
+        cnt[e] = 0;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        if ((wave * kSteps + s) * kWave >= R)
+            break;
+        const bool valid = ev[s] >= 0;
+        const uint64_t m = same_expert_lanes(ev[s], valid, nbits);
+        const uint64_t below = m & lanes_below(lane);
+        const int32_t before = valid ? cnt[ev[s]] : 0;
+        rank[s] = before + __popcll(below);
+        if (valid && below == 0)
+            cnt[ev[s]] = before + __popcll(m);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += kWave * kOneWaves) { // counts -> rows of earlier wavefronts
+        int32_t c[kOneWaves], run = 0;
+#pragma unroll
+        for (int w = 0; w < kOneWaves; ++w)
+            c[w] = lds[w * E + e];
+#pragma unroll
+        for (int w = 0; w < kOneWaves; ++w) {
+            lds[w * E + e] = run;
+            run += c[w];
+        }
+        total[e] = run;
+        expert_counts[e] = run;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        region_offsets(total, E, lane, off);
+        write_region_tables(off, E, G, lane, expert_offsets, dest_counts, dest_offsets);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int r = (wave * kSteps + s) * kWave + lane;
+        if (ev[s] >= 0) {
+            const int32_t slot = off[ev[s]] + cnt[ev[s]] + rank[s];
+            slot_of_row[r] = slot;
+            row_of_slot[slot] = r;
+        }
+    }
+}
+
 int launch_layout(const int32_t *topk_idx, int64_t R, int E, int G, int32_t *expert_counts,
                   int32_t *expert_offsets, int32_t *dest_counts, int32_t *dest_offsets,
                   int32_t *slot_of_row, int32_t *row_of_slot, void *ws, hipStream_t st)
@@ -204,6 +276,17 @@ int launch_layout(const int32_t *topk_idx, int64_t R, int E, int G, int32_t *exp
     int nbits = 1;
     while ((1 << nbits) < E)
         ++nbits;
+    // (the counts fit the LDS of any launch up to some 900 experts)
+    const size_t one_lds = (size_t)(kOneWaves + 2) * E * sizeof(int32_t) + sizeof(int32_t);
+    if (R <= kOneRows && one_lds <= 64 * 1024) {
+        auto kern = R <= kOneWaves * kWave       ? layout_one_group<1>
+                    : R <= 2 * kOneWaves * kWave ? layout_one_group<2>
+                    : R <= 4 * kOneWaves * kWave ? layout_one_group<4>
+                                                 : layout_one_group<8>;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kWave * kOneWaves), one_lds, st, topk_idx, (int)R, E, G, nbits, expert_counts,
+                           expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot);
+        return check_launch("moe_dispatch_layout");
+    }
     int32_t *unit_hist = static_cast<int32_t *>(ws);
     const int blocks = (int)ceil_div(U, kWavesPerBlock);
     if (U > 0) {
