@@ -98,8 +98,9 @@ def _ptr(t):
 
 
 def _stream():
+    # the handle itself; torch.cuda.current_stream() builds a Stream object around it at every call
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
