@@ -264,8 +264,8 @@ int moe_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t F,
  * incomplete.  The call itself still returns MOE_OK.  MOE_BF16 needs a 128-byte aligned
  * ws (with F % 64 == 0, as for every bf16 FFN, each row of the activation then is a whole
  * number of cache lines, so no line holds rows of two row tiles, one complete and one
- * still being written); otherwise MOE_ERR_UNSUPPORTED, and the two separate calls serve.  MOE_F32: runs the two
- * simple kernels one after the other.
+ * still being written); otherwise MOE_ERR_UNSUPPORTED, and the two separate calls serve.  MOE_F32, and
+ * launches with few rows: the two kernels one after the other.
  */
 int moe_ffn_gate_up_down(const void *xp, int dtype, int64_t M, int64_t H, int64_t F,
                          int E_local, const int32_t *seg_offsets,

@@ -459,7 +459,7 @@ extern "C" int moe_ffn_gate_up_down(const void *xp, int dtype, int64_t M, int64_
                         "cache lines); use moe_ffn_gate_up + moe_ffn_down");
         return launch_ffn_gate_up_down(xp, M, H, F, E_local, W_gate, W_up, W_down, y, ws, wait_limit, st);
     }
-    // fp32 (correctness path): the two simple kernels, one after the other
+    // fp32: the two kernels, one after the other
     MOE_TRY(launch_ffn_gate_up(xp, dtype, M, H, F, E_local, seg_offsets, W_gate, W_up, ws, st));
     return launch_ffn_down(dtype, M, H, F, E_local, seg_offsets, W_down, y, ws, st);
 }

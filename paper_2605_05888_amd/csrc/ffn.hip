@@ -11,6 +11,8 @@
 // XOR-swizzled units (grouped_gemm.h), one barrier per K tile.  GEMM1 keeps gate and up columns of the same f in one wavefront, so
 // the activation is applied to the accumulators and `g`, `u` never reach memory.
 //
+// Launches with few rows and few tiles go to ffn_thin.hip (use_thin below), fp32 to ffn_f32.hip.
+//
 // Scheduling is device side: a small kernel turns seg_offsets into a tile table
 // (expert, first row, end row, column tile), ordered so that tiles that run
 // together share weight tiles; workgroup ids are spread so that each XCD's L2
@@ -394,6 +396,18 @@ static GemmArgs gemm_args(const uint16_t *A, int64_t M, int E_local, int Kdim, i
     return g;
 }
 
+template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, bool kTurn>
+static void launch_gemm_form(const GemmArgs &g, hipStream_t st)
+{
+    auto kern = grouped_gemm_bf16<Main, Light, kSwiglu, kGather, kScatter, kTurn>;
+    const size_t lds_bytes = lds_bytes_of<Main, Light>();
+    static std::atomic<uint64_t> raised{0};
+    allow_lds(kern, lds_bytes, raised);
+    // persistent grid: the workgroups draw their tiles from the table's counters
+    const int grid = workgroup_slots(Main::kLdsBytes <= 80 * 1024 ? 2 : 1);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Main::kThreads), lds_bytes, st, g);
+}
+
 template <class Main, class Light, bool kSwiglu, bool kGather = false, bool kScatter = false>
 static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0,
                         const uint16_t *B1, uint16_t *C, TileTableHeader *hdr,
@@ -401,15 +415,12 @@ static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int
                         const int32_t *gather_rows = nullptr, int gather_div = 1, uint32_t gather_bytes = 0,
                         const float *scatter_w = nullptr)
 {
-    auto kern = grouped_gemm_bf16<Main, Light, kSwiglu, kGather, kScatter>;
-    const size_t lds_bytes = lds_bytes_of<Main, Light>();
-    static std::atomic<uint64_t> raised{0};
-    allow_lds(kern, lds_bytes, raised);
     GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, patch);
     g.gather_rows = gather_rows, g.gather_div = gather_div, g.gather_bytes = gather_bytes, g.scatter_w = scatter_w;
-    // persistent grid: the workgroups draw their tiles from the table's counters
-    const int grid = workgroup_slots(Main::kLdsBytes <= 80 * 1024 ? 2 : 1);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Main::kThreads), lds_bytes, st, g);
+    if (g.k_turn)
+        launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, true>(g, st);
+    else
+        launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, false>(g, st);
 }
 
 int check_ffn_shape(int dtype, int64_t H, int64_t F)

@@ -288,7 +288,9 @@ struct GemmArgs {
 // row tile's counter once its stores are acknowledged; 2 = consumer: a tile whose rows were not
 // complete when it was drawn is not prefetched, and its workgroup waits for the counter before loading.
 #if defined(__HIP_DEVICE_COMPILE__) // the body uses device-only types (buffer resources); the host pass only needs the kernels' stubs
-template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, int kDep>
+// kTurn: the reduction of a tile starts at a K tile that depends on its column tile (g.k_turn; without it 0).  A form of
+// its own because the wrap costs the matrix-bound launches 0.4 %.
+template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, int kDep, bool kTurn>
 __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
 {
     const uint16_t *__restrict__ const A = g.A;
@@ -493,7 +495,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             const TileEntry te = table[entry_of(tile)];
             const int col = te.n_tile & ((1 << kTileColBits) - 1);
             const int n0 = col * Cfg::kOutCols;
-            o.k0 = (int)((uint32_t)(Cfg::kKind == 1 ? col : col / kOrderCols) * (uint32_t)g.k_turn % (uint32_t)KT);
+            if constexpr (kTurn)
+                o.k0 = (int)((uint32_t)(Cfg::kKind == 1 ? col : col / kOrderCols) * (uint32_t)g.k_turn % (uint32_t)KT);
             o.ext = kTall ? te.n_tile >> kTileColBits : 0;
             const int64_t rows_left = (int64_t)te.m_end - te.m0; // >= 1
             const int cols_left = Ndim - n0;                      // >= 1
@@ -514,8 +517,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
     // byte offset of K tile t of a tile inside its rows
     auto k_offset = [&](int t, int k0) {
-        const int k = t + k0;
-        return (k >= KT ? k - KT : k) * (kBK * 2);
+        const int k = kTurn ? t + k0 : t;
+        return (kTurn && k >= KT ? k - KT : k) * (kBK * 2);
     };
     Operands cur, nxt; // the tile being computed; the one whose first K tiles are fetched behind it
     // kGather: the lane's rows of a tile -> their entries of gather_rows (rows past the segment: ~0) ...
@@ -1142,12 +1145,12 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
 #endif // __HIP_DEVICE_COMPILE__
 
 // One GEMM per launch.
-template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter = false>
+template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, bool kTurn>
 __global__ __launch_bounds__(Main::kThreads, (Main::kLdsBytes <= 80 * 1024 ? 2 : 1)) void grouped_gemm_bf16(GemmArgs g)
 {
     static_assert(!(kGather && kScatter) && !(kScatter && kSwiglu), "kScatter belongs to the down projection");
 #if defined(__HIP_DEVICE_COMPILE__) // the body uses device-only types (buffer resources); the host pass only needs the stub
-    gemm_phase<Main, Light, kSwiglu, kGather, kScatter, 0>(g);
+    gemm_phase<Main, Light, kSwiglu, kGather, kScatter, 0, kTurn>(g);
 #endif
 }
 
@@ -1159,9 +1162,9 @@ template <class Main1, class Light1, class Main2, class Light2>
 __global__ __launch_bounds__(Main1::kThreads, 1) void grouped_ffn_bf16(GemmArgs g1, GemmArgs g2)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    gemm_phase<Main1, Light1, true, false, false, 1>(g1);
+    gemm_phase<Main1, Light1, true, false, false, 1, true>(g1);
     __syncthreads(); // the ring is drained (every path out of a phase waits for its loads); LDS changes hands
-    gemm_phase<Main2, Light2, false, false, false, 2>(g2);
+    gemm_phase<Main2, Light2, false, false, false, 2, true>(g2);
 #endif
 }
 
