@@ -85,6 +85,8 @@ size_t moe_workspace_bytes(int op, int64_t N, int64_t H, int E, int K, int G, in
  * Selection is on the logits: the K largest per token, equal logits to the
  * lower expert index; topk_idx[n,0..K) in descending preference.
  * topk_w[n,k]: per score_mode, normalised over the K selected (sums to 1).
+ * The K picks of a token are distinct experts of [0,E) also where fp32 overflowed:
+ * a NaN logit counts as -infinity, and the weights of such a token may be NaN.
  *
  *   x        [N,H] dtype          W_r  [H,E] fp32        bias [E] fp32 or NULL
  *   topk_idx [N,K] int32 (out)    topk_w [N,K] fp32 (out)

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(512, 2) void router_logits_small(
     if (there && logits)
         logits[n * E + e] = val;
     if constexpr (kSelect) {
-        const float key = e < E ? val : -INFINITY;
+        const float key = e < E && val > -INFINITY ? val : -INFINITY; // (NaN counts as -infinity)
         const int rank = count_better<1>(key, e, 0);
         const float top = row_max16(key);
         const bool chosen = e < E && rank < K;
@@ -548,6 +548,9 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
 // Selection.  One wavefront per token, lane l holds experts l, l+64, ... (kPer of them).  A round takes the
 // largest value over the wavefront by data-parallel-primitive moves (no LDS), then the lowest index that has it
 // (experts in ascending order are ballots of ascending i, lanes from the lowest).
+// The K picks are distinct experts of [0, E) whatever the logits are: an overflowed token has infinities or NaN, a
+// masked expert a bias of -infinity.  NaN counts as -infinity; once no larger logit is left, the experts that are not
+// taken follow in ascending order.
 // kTakeRows: every routed row also takes its local row id from its expert's row pointer as it is
 // produced (Section IV-A3: the allocation unit hands out the next free row of a region on arrival);
 // rank[n*K + k] receives it, and the pointers end up as the experts' counts.
@@ -576,11 +579,13 @@ __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
     if (n >= N)
         return;
     const float *row = logits + n * E;
-    float val[kPer]; // -infinity: not there, or taken
+    float val[kPer];    // -infinity also: not there, or taken
+    uint32_t taken = 0; // bit i: expert i * 64 + lane is taken, or there is none
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         const int e = i * kWave + lane;
         val[i] = e < E ? row[e] : -INFINITY;
+        taken |= e < E ? 0u : 1u << i;
     }
     float my_logit = 0.0f, top = 0.0f; // lane k keeps the k-th pick
     int my_pick = 0;
@@ -590,15 +595,20 @@ __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
         for (int i = 1; i < kPer; ++i)
             best = fmaxf(best, val[i]);
         best = wave_max(best);
+        const bool larger = best > -INFINITY; // uniform; else only -infinity and NaN (or NaN alone) are left
         int pick = -1;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const uint64_t m = __ballot(val[i] == best);
+            const uint64_t m = __ballot(larger ? val[i] == best : (taken >> i & 1u) == 0u);
             if (pick < 0 && m != 0) {
                 const int at = __builtin_ctzll(m);
                 pick = i * kWave + at;
-                if (lane == at)
+                if (!larger)
+                    best = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(val[i]), at));
+                if (lane == at) {
                     val[i] = -INFINITY;
+                    taken |= 1u << i;
+                }
             }
         }
         if (k == 0)
