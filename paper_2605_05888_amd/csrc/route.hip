@@ -295,7 +295,9 @@ __global__ __launch_bounds__(512, 2) void router_logits_small(
         const float top = row_max16(key);
         const bool chosen = e < E && rank < K;
         const float s = chosen ? score(val, top, score_mode) : 0.0f;
-        const float sum = row_sum16(s);
+        // summed by rank like router_topk's scores, for the same bits: lane `rank` of the row receives the score
+        const float by_rank = __uint_as_float((uint32_t)__builtin_amdgcn_ds_permute(((lane & ~15) + rank) * 4, (int)__float_as_uint(s)));
+        const float sum = row_sum16(by_rank);
         if (chosen && n < N) {
             topk_idx[n * K + rank] = e;
             topk_w[n * K + rank] = s / sum;
@@ -619,9 +621,10 @@ __global__ __launch_bounds__(kWave *kRouteWaves) void router_topk(
         }
     }
     const float s = lane < K ? score(my_logit, top, score_mode) : 0.0f;
-    float sum = row_sum16(s); // K <= 32: the first two rows of sixteen lanes
-    sum = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum), 0)) +
-          __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum), 16));
+    // Sum in pairs of ranks that are 16, 8, 4, 2, 1 apart (K <= 32: the first two rows of sixteen lanes)
+    const float pairs = K > 16 ? s + __shfl_xor(s, 16) : s;
+    float sum = row_sum16(pairs);
+    sum = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sum), 0));
     if (lane < K) {
         topk_idx[n * K + lane] = my_pick;
         topk_w[n * K + lane] = s / sum;
