@@ -19,7 +19,7 @@
 // pair registers of one lane.
 //
 // Tokens past N and experts past E repeat the last one (their results are not stored).  Rows of W_r past H
-// count as zeros, and columns of x past H as any finite value: adding a zero product never changes a partial
+// count as zeros, and columns of x past H as zeros or any finite value: adding a zero product never changes a partial
 // sum (partials start at +0 and can never become -0), so a ragged last step gives the R64 sum bit for bit.
 #include <math.h>
 
@@ -31,6 +31,8 @@ namespace moe {
 
 constexpr int kRouteWaves = 4; // wavefronts per workgroup of the selection kernel
 constexpr int kRtExp = 16, kRtTok = 16;
+
+__device__ const u32x4 kZeroColumns = {0u, 0u, 0u, 0u}; // 16 bytes of x past H
 
 // Four columns of x (bf16: two per register) or fewer, as fetched; see x_value.
 template <bool kBf16, int kG>
@@ -173,15 +175,18 @@ __global__ __launch_bounds__(512, 2) void router_logits_small(
     struct Weights {
         float w[kBatch][kG];
     };
-    // batch i: x into LDS stage `set`, W_r into registers.  Chunks of x past H: the row's first one (any values).
+    // batch i: x into LDS stage `set`, W_r into registers.  Chunks of x past H: zeros (the row's own values would do as
+    // long as they are finite; an infinity among them would make every logit of the token NaN).
     auto fetch = [&](Weights &b, int64_t i, int set) {
         const int64_t h0 = i * kCols;
         const bool whole = h0 + kCols <= H;
 #pragma unroll
         for (int j = 0; j < kXLoads; ++j) {
-            const int64_t off = whole || h0 + x_col[j] < H ? h0 : -(int64_t)x_col[j];
+            const unsigned char *const from = whole || h0 + x_col[j] < H
+                                                  ? px[j] + h0 * kXb
+                                                  : reinterpret_cast<const unsigned char *>(&kZeroColumns);
             __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(px[j] + off * kXb),
+                (const __attribute__((address_space(1))) void *)from,
                 (__attribute__((address_space(3))) void *)(lds + set * kXStage + (ps * kXLoads + j) * 1024), 16, 0, 0);
         }
         if (whole) {

@@ -59,3 +59,21 @@ def test_picks_are_distinct_experts_whatever_the_logits(N, H, E, K):
         assert np.array_equal(G.host(idx2), want)
         assert (G.host(guarded[:32]) == -7).all() and (G.host(guarded[32 + E:]) == -7).all()
         check_layout_is_valid(want, E, 1, {k: G.host(v) for k, v in out.items()})
+
+
+@pytest.mark.parametrize("N,H,E,bf16", [(19, 520, 30, False), (19, 584, 30, True), (40, 4, 6, False), (33, 1000, 15, True)])
+def test_an_infinity_in_x_meets_the_columns_of_its_row_only(N, H, E, bf16):
+    """H is no multiple of the 512 columns of a batch: what stands for the columns past H must not be the infinity."""
+    import gpu_layer as G
+    import moe_inputs as mi
+    import moe_inputs.device as mid
+    print("route, infinite x", N, H, E, bf16, flush=True)
+    rng = np.random.default_rng(H + E)
+    x = mi.f32_to_bf16_bits(rng.standard_normal((N, H)).astype(np.float32)) if bf16 else rng.standard_normal((N, H)).astype(np.float32)
+    x[3, 1], x[8, 0], x[N - 1, 2] = (0x7F80, 0xFF80, 0x7F80) if bf16 else (np.inf, -np.inf, np.inf)
+    W = rng.standard_normal((H, E)).astype(np.float32)
+    want, _, logits = oracle.route(x, W, None, 2, oracle.SOFTMAX_TOPK)
+    assert np.isinf(logits[[3, 8, N - 1]]).all() and np.isfinite(np.delete(logits, [3, 8, N - 1], 0)).all()
+    idx, _, lg = G.gpu_route(mid.to_device(x), mid.to_device(W), None, 2, oracle.SOFTMAX_TOPK)
+    assert np.array_equal(G.host(lg), logits)
+    assert np.array_equal(G.host(idx), want)
