@@ -157,7 +157,9 @@ __global__ __launch_bounds__(512, 2) void router_logits_small(
     const int blk = lane / 16, c = lane % 16;
     const int e_tiles = (E + kRtExp - 1) / kRtExp;
     const int e0 = (int)(blockIdx.x % e_tiles) * kRtExp;
-    const int64_t n0 = (int64_t)(blockIdx.x / e_tiles) * kRtTok;
+    const int64_t n0 = ((int64_t)blockIdx.y * (gridDim.x / e_tiles) + blockIdx.x / e_tiles) * kRtTok;
+    if (n0 >= N) // (the last row of the grid)
+        return;
     const int l0 = 4 * kG * ps + kG * blk; // first of the lane's kG partials
     const float *pw = W_r + (int64_t)l0 * E + (e0 + c < E ? e0 + c : E - 1);
 
@@ -664,7 +666,9 @@ static void launch_logits(const void *x, int64_t N, int64_t H, const float *W_r,
                            st, x, N, (int)H, W_r, bias, E, logits);
         return;
     }
-    const dim3 grid((unsigned)(ceil_div(N, kRtTok) * e_tiles));
+    // One dimension of a grid holds fewer than 2^32 threads (2^23 of these workgroups): the token tiles go in rows.
+    const int64_t tok_tiles = ceil_div(N, kRtTok), fit = ((int64_t)1 << 22) / e_tiles, per_row = tok_tiles < fit ? tok_tiles : fit;
+    const dim3 grid((unsigned)(per_row * e_tiles), (unsigned)ceil_div(tok_tiles, per_row));
     if (select)
         hipLaunchKernelGGL((router_logits_small<kBf16, true>), grid, dim3(512), 0, st, x, N, H, W_r, bias, E, logits, K,
                            score_mode, topk_idx, topk_w);
