@@ -31,7 +31,7 @@ FLAGS = [
 # hand-written buffer loads fill while hand-written matrix instructions are still to read them; the
 # compiler is not told, and the kernel is correct only as long as it never copies or reuses those
 # registers inside the K loop.  That was checked in the generated code of the compilers listed here
-# (and is checked on the GPU by the test that reverses every expert segment and expects the same bits).
+# (and is checked on the GPU by the tests that reverse every expert segment and expect the same bits).
 # Another compiler may schedule differently: read the listing again before adding it.
 TESTED_COMPILERS = ("7.2.26015",)
 
@@ -46,7 +46,8 @@ def check_compiler() -> str:
                 "The tall-tile code of csrc/grouped_gemm.h relies on the compiler leaving the registers of "
                 "`xa` alone inside the K loop: inspect the listing of grouped_gemm_bf16 (no instruction but "
                 "the hand-written buffer loads and v_mfma may touch them), run "
-                "tests/test_gpu_parity.py::test_ffn_remainder_rows_riding_with_the_last_full_tile, then add "
+                "tests/test_gpu_parity.py::test_ffn_remainder_rows_riding_with_the_last_full_tile and "
+                "tests/test_gpu_ffn_turned.py, then add "
                 "the version to TESTED_COMPILERS or set MOE_HUB_UNTESTED_COMPILER=1.")
         sys.stderr.write(f"warning: untested hipcc (HIP version {version})\n")
     return version

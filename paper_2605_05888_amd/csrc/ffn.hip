@@ -525,27 +525,40 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
 }
 
 // Both GEMMs in one launch, the second consuming the first's rows tile by tile (after launch_ffn_schedule).
+template <class Main2, class Light2, bool kTurn1, bool kTurn2>
+static void launch_both_form(const GemmArgs &g1, const GemmArgs &g2, hipStream_t st)
+{
+    using Main1 = BigTile<true>;
+    using Light1 = ShallowTile<true>;
+    auto kern = grouped_ffn_bf16<Main1, Light1, Main2, Light2, kTurn1, kTurn2>;
+    size_t lds_bytes = lds_bytes_of<Main1, Light1>();
+    lds_bytes = lds_bytes > lds_bytes_of<Main2, Light2>() ? lds_bytes : lds_bytes_of<Main2, Light2>();
+    static std::atomic<uint64_t> raised{0};
+    allow_lds(kern, lds_bytes, raised);
+    hipLaunchKernelGGL(kern, dim3(workgroup_slots(1)), dim3(Main1::kThreads), lds_bytes, st, g1, g2);
+}
+
 template <class Main2, class Light2>
 static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp, int64_t M, int64_t H, int64_t F, int E_local,
                         const void *W_gate, const void *W_up, const void *W_down, void *y, int64_t wait_limit,
                         hipStream_t st)
 {
-    using Main1 = BigTile<true>;
-    using Light1 = ShallowTile<true>;
-    auto kern = grouped_ffn_bf16<Main1, Light1, Main2, Light2>;
-    size_t lds_bytes = lds_bytes_of<Main1, Light1>();
-    lds_bytes = lds_bytes > lds_bytes_of<Main2, Light2>() ? lds_bytes : lds_bytes_of<Main2, Light2>();
-    static std::atomic<uint64_t> raised{0};
-    allow_lds(kern, lds_bytes, raised);
     GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
                             static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, kPatch);
     GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
                             static_cast<uint16_t *>(y), k.hdr2, k.tab2, kPatch);
     g1.ready = g2.ready = k.ready;
     g1.hdr_dep = g2.hdr_dep = k.hdr1;
-    g1.ready_per_launch = g2.ready_per_launch = Main1::kWaves * p.n_tiles1;
+    g1.ready_per_launch = g2.ready_per_launch = BigTile<true>::kWaves * p.n_tiles1;
     g1.wait_limit = g2.wait_limit = wait_limit > 0 ? wait_limit : kDefaultWaitLimit;
-    hipLaunchKernelGGL(kern, dim3(workgroup_slots(1)), dim3(Main1::kThreads), lds_bytes, st, g1, g2);
+    if (g1.k_turn && g2.k_turn)
+        launch_both_form<Main2, Light2, true, true>(g1, g2, st);
+    else if (g1.k_turn)
+        launch_both_form<Main2, Light2, true, false>(g1, g2, st);
+    else if (g2.k_turn)
+        launch_both_form<Main2, Light2, false, true>(g1, g2, st);
+    else
+        launch_both_form<Main2, Light2, false, false>(g1, g2, st);
 }
 
 int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int E_local, const void *W_gate,

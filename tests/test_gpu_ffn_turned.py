@@ -45,3 +45,50 @@ def test_turned_reduction(H, F):
     hub.moe_ffn_gate_up_gather(x, 1, dseg, perm.to(torch.int32), Wg, Wu, ws)
     hub.moe_ffn_down(dseg, Wd, y2, ws)
     assert torch.equal(y, y2)
+
+
+# narrow column tiles in the down projection (up to 256 tiles of 256 columns) and wide ones; gate/up, down or both turned
+@pytest.mark.parametrize("H,F", [(2048, 320), (320, 2048), (2048, 4096), (6144, 1216), (5696, 2048), (6144, 4096)])
+def test_turned_reduction_in_the_other_forms(H, F):
+    """Both GEMMs in one launch, the combine in the down projection's epilogue, and every segment reversed (so that a
+    remainder of rows that rode with a full tile is an ordinary part of it): the bits of the separate launches."""
+    import torch
+    import paper_2605_05888_amd as hub
+    print("turned, other forms", H, F, flush=True)
+    E, M = len(ROWS), sum(ROWS)
+    seg = np.concatenate([[0], np.cumsum(ROWS)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    dseg = torch.from_numpy(seg).cuda()
+    ws = torch.empty(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    y = torch.full((M, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hub.moe_grouped_ffn(xp, dseg, Wg, Wu, Wd, y, ws)
+    want = torch.cat([(torch.nn.functional.silu(x @ Wg[e].double().T) * (x @ Wu[e].double().T)).to(torch.bfloat16).double() @
+                      Wd[e].double().T for e, x in enumerate(xp[lo:hi].double() for lo, hi in zip(seg[:-1], seg[1:]))])
+    assert float((y.double() - want).norm() / want.norm()) < 2.0 ** -9   # (one rounding of y)
+
+    def one_launch(rows, times):
+        out = torch.full_like(y, float("nan"))
+        hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+        for _ in range(times):
+            hub.moe_ffn_gate_up_down(rows, dseg, Wg, Wu, Wd, out, ws)
+        hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+        return out
+
+    assert torch.equal(one_launch(xp, 1), y)
+    assert torch.equal(one_launch(xp, 3), y)                             # three times over one schedule
+    rev = torch.cat([torch.arange(lo, hi).flip(0) for lo, hi in zip(seg[:-1], seg[1:])]).cuda()
+    y_rev = torch.full_like(y, float("nan"))
+    hub.moe_grouped_ffn(xp[rev].contiguous(), dseg, Wg, Wu, Wd, y_rev, ws)
+    assert torch.equal(y_rev, y[rev])
+    assert torch.equal(one_launch(xp[rev].contiguous(), 1), y[rev])
+    # rows fetched through the map, and added to their tokens' sums (top-1, weight 2: exact doubles); x[rev[m]] is row m
+    x = torch.empty_like(xp)
+    x[rev] = xp
+    rows = rev.to(torch.int32)
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+    hub.moe_ffn_gate_up_gather(x, 1, dseg, rows, Wg, Wu, ws)
+    sums, out = torch.empty(M, H, device="cuda"), torch.empty(M, H, dtype=torch.bfloat16, device="cuda")
+    hub.moe_ffn_down_combine(1, dseg, Wd, rows, torch.full((M, 1), 2.0, device="cuda"), sums, out, ws)
+    assert torch.equal(out[rev], (2.0 * y.float()).to(torch.bfloat16))
