@@ -98,9 +98,13 @@ def _ptr(t):
 
 
 def _stream():
-    # the handle itself; torch.cuda.current_stream() builds a Stream object around it at every call
+    # the handle itself where this torch hands it out (the name is private to it); torch.cuda.current_stream() builds a
+    # Stream object around it at every call
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
