@@ -112,7 +112,8 @@ __global__ __launch_bounds__(kF32Threads, (kStages > 3 ? 2 : 4)) void ffn_f32_ti
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // Tiles in bands of kBand row tiles, column by column; workgroup ids are dealt round-robin to the XCDs, and the
     // kBand tiles of a band that share a weight tile go to one XCD, one after the other.
-    const int64_t slot = blockIdx.x / (kXcdCount * kBand) * (int64_t)(kXcdCount * kBand) +
+    // (A row of the grid is a multiple of kXcdCount * kBand workgroups long.)
+    const int64_t slot = (int64_t)blockIdx.y * gridDim.x + blockIdx.x / (kXcdCount * kBand) * (kXcdCount * kBand) +
                          blockIdx.x % kXcdCount * kBand + blockIdx.x / kXcdCount % kBand;
     const int64_t band = slot / ((int64_t)kBand * col_tiles);
     const int in_band = (int)(slot - band * kBand * col_tiles);
@@ -248,14 +249,14 @@ static int launch_tiles(const float *A, int64_t M, int64_t Kdim, int64_t Ndim, i
     // an upper bound of the row tiles: workgroups that find none leave at once
     const int64_t row_tiles = M / kF32Rows + E_local < M ? M / kF32Rows + E_local : M;
     const int64_t blocks = ceil_div(ceil_div(row_tiles, kBand) * kBand * col_tiles, kXcdCount * kBand) * (kXcdCount * kBand);
-    if (blocks >= ((int64_t)1 << 32) / kF32Threads)
-        return fail(MOE_ERR_UNSUPPORTED, "%s: M=%lld rows by %lld columns are more tiles than one launch takes", what,
-                    (long long)M, (long long)Ndim);
+    // one dimension of a grid holds fewer than 2^32 threads: rows of 2^23 workgroups beyond that
+    constexpr int64_t kGridRow = (int64_t)1 << 23;
+    const dim3 grid((unsigned)(blocks < kGridRow ? blocks : kGridRow), (unsigned)ceil_div(blocks, kGridRow));
     // A launch that is resident at once with two workgroups per compute unit waits for latency, not for the matrix
     // pipe: as many K tiles in flight as two workgroups have LDS for.  Larger ones: four workgroups per unit.
     constexpr int kDeep = kSwiglu ? 4 : 6, kShallow = kSwiglu ? 2 : 3;
     auto kern = blocks <= 512 ? ffn_f32_tiles<kSwiglu, kDeep> : ffn_f32_tiles<kSwiglu, kShallow>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kF32Threads), 0, st, A, M, (int)Kdim,
+    hipLaunchKernelGGL(kern, grid, dim3(kF32Threads), 0, st, A, M, (int)Kdim,
                        (int)Ndim, E_local, seg, B0, B1, C, gather_rows, gather_div, col_tiles);
     return check_launch(what);
 }

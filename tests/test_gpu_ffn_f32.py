@@ -49,3 +49,24 @@ def test_fp32_ffn_at_tile_edges(rows, H, F, gather):
         hub.moe_ffn_down(dseg, dW[2], y, ws)
     torch.cuda.synchronize()
     G.check_close(G.host(y), want, 1e-4, 1e-5, what="fp32 ffn")
+
+
+def test_more_tiles_than_one_grid_dimension_takes():
+    """One row tile by 2^21 column tiles, eight row tiles to a band: 2^24 workgroups of 256 threads."""
+    import torch
+    import gpu_layer as G
+    import paper_2605_05888_amd as hub
+    M, H, F = 8, 4, 1 << 27
+    print("fp32 ffn, many column tiles", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty(M, H, device="cuda").normal_(generator=g)
+    Wg, Wu = (torch.empty(1, F, H, device="cuda").normal_(generator=g) for _ in range(2))
+    seg = torch.tensor([0, M], dtype=torch.int32, device="cuda")
+    ws = torch.full((hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=1, F=F, dtype=hub.F32) // 4,), float("nan"), device="cuda")
+    hub.moe_ffn_gate_up(x, seg, Wg, Wu, ws)
+    a = ws[:M * F].view(M, F)
+    for lo in range(0, F, 1 << 23):
+        part = slice(lo, lo + (1 << 23))
+        want = torch.nn.functional.silu(x.double() @ Wg[0, part].double().T) * (x.double() @ Wu[0, part].double().T)
+        # four products per sum: off by 2^-22 of their magnitudes at most, times the other factor
+        assert float((a[:, part].double() - want).norm() / want.norm()) < 1e-6, lo
