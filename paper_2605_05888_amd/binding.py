@@ -101,8 +101,9 @@ def _stream():
     # the handle itself where this torch hands it out (the name is private to it); torch.cuda.current_stream() builds a
     # Stream object around it at every call
     import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    try:
+        raw = torch._C._cuda_getCurrentRawStream
+    except AttributeError:
         return torch.cuda.current_stream().cuda_stream
     return raw(torch.cuda.current_device())
 
