@@ -1,5 +1,5 @@
-"""fp32 expert FFN on the matrix cores (64 x 64 tiles, K tiles of 32): sizes on both sides of every edge, against
-the fp64 oracle.  Bound: sums of n products in fp32 are off by at most n * 2^-24 relative to the sum of the
+"""fp32 expert FFN on the matrix cores (tiles of 32 rows x 64 columns, K tiles of 32): sizes on both sides of every edge,
+against the fp64 oracle.  Bound: sums of n products in fp32 are off by at most n * 2^-24 relative to the sum of the
 products' magnitudes; with two GEMMs of up to 100 terms of unit-variance results that is below 1e-5 in relative
 L2 and below 1e-4 per element (the observed error is 3e-7)."""
 import dataclasses
@@ -70,3 +70,43 @@ def test_more_tiles_than_one_grid_dimension_takes():
         want = torch.nn.functional.silu(x.double() @ Wg[0, part].double().T) * (x.double() @ Wu[0, part].double().T)
         # four products per sum: off by 2^-22 of their magnitudes at most, times the other factor
         assert float((a[:, part].double() - want).norm() / want.norm()) < 1e-6, lo
+
+
+# Launches beyond 512 workgroups take fewer K tiles in flight (two in gate/up, three in down) and more workgroups per
+# compute unit.  Workgroups, gate/up and down (row tiles rounded up to 8, times columns / 64, rounded up to 64):
+MANY = [([313, 0, 97, 31, 300, 256, 33, 1, 480, 500, 499, 493], 516, 1028),   # 1920, 1024: ragged rows, columns and K
+        ([300, 148], 2052, 2048),                                             # 512 (the last with more in flight), 576
+        ([300, 148], 2048, 2052),                                             # 576, 512
+        ([40] * 40, 100, 2500),                                               # 3840, 192: many experts, K shorter than the ring
+        ([1500, 0, 0, 1], 4, 4096)]                                           # 3584 (one K tile of one chunk), 64
+
+
+@pytest.mark.parametrize("gather", [False, True])
+@pytest.mark.parametrize("rows,H,F", MANY, ids=[f"{sum(r)}-{h}-{f}" for r, h, f in MANY])
+def test_fp32_ffn_of_many_workgroups(rows, H, F, gather):
+    import torch
+    import paper_2605_05888_amd as hub
+    print("fp32 ffn, many workgroups", rows[:12], H, F, gather, flush=True)
+    E, M = len(rows), sum(rows)
+    seg = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    normal = lambda shape, std: torch.empty(shape, device="cuda").normal_(0.0, std, generator=g)
+    xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    dseg = torch.from_numpy(seg).cuda()
+    ws = torch.full((hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F, dtype=hub.F32) // 4,), float("nan"), device="cuda")
+    y = torch.full((M, H), float("nan"), device="cuda")
+    if gather:
+        perm = torch.randperm(M, generator=torch.Generator().manual_seed(5)).cuda()   # slot m holds row perm[m] of x
+        x = torch.empty_like(xp)
+        x[perm] = xp
+        hub.moe_ffn_gate_up_gather(x, 1, dseg, perm.to(torch.int32), Wg, Wu, ws)
+        hub.moe_ffn_down(dseg, Wd, y, ws)
+    else:
+        hub.moe_grouped_ffn(xp, dseg, Wg, Wu, Wd, y, ws)
+    # n products of an fp32 sum are off by n * 2^-24 of their magnitudes at most, and as rounding errors mostly cancel by
+    # some sqrt(n) * 2^-25 of the result: at n = 2500, twice, 3e-6
+    for e, (lo, hi) in enumerate(zip(seg[:-1], seg[1:])):
+        xe = xp[lo:hi].double()
+        a = torch.nn.functional.silu(xe @ Wg[e].double().T) * (xe @ Wu[e].double().T)
+        for got, want in ((ws[:M * F].view(M, F)[lo:hi], a), (y[lo:hi], a @ Wd[e].double().T)):
+            assert lo == hi or float((got.double() - want).norm() / want.norm()) < 3e-6, e

@@ -81,3 +81,46 @@ def test_few_rows_need_their_schedule():
     hub.moe_ffn_gate_up(torch.zeros(M, H, dtype=torch.bfloat16, device="cuda"), seg, w, w, ws)
     with pytest.raises(hub.MoEHubError, match="MOE_ERR_STATE"):
         hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+
+
+# tokens, experts, top-K, H, F: the down projection thin or tiled, one row per expert up to whole row blocks
+@pytest.mark.parametrize("N,E,K,H,F", [(1, 64, 4, 2048, 1408), (1, 4, 4, 512, 256), (3, 8, 2, 320, 576), (40, 16, 3, 256, 192),
+                                       (64, 8, 4, 448, 320)])
+def test_few_tokens_with_several_experts_each(N, E, K, H, F):
+    """Rows fetched from x through a map with K slots per token: the bits of permute and the plain form; the down
+    projection that adds K weighted rows per token against float64."""
+    import torch
+    import paper_2605_05888_amd as hub
+    print("few tokens", N, E, K, H, F, flush=True)
+    g = torch.Generator().manual_seed(N + E)
+    normal = lambda shape, std: (torch.randn(shape, generator=g) * std).to(torch.bfloat16).cuda()
+    x, Wg, Wu, Wd = normal((N, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    idx = torch.stack([torch.randperm(E, generator=g)[:K] for _ in range(N)]).to(torch.int32).cuda()
+    w = torch.rand((N, K), generator=g).cuda() + 0.5
+    M = N * K
+    i32 = lambda n: torch.empty(n, dtype=torch.int32, device="cuda")
+    raw = lambda n: torch.empty(max(n, 16), dtype=torch.uint8, device="cuda")
+    counts, offsets, dest, dest_off, slot, row = i32(E), i32(E + 1), i32(1), i32(2), i32(M), i32(M)
+    hub.moe_dispatch_layout(idx, E, 1, counts, offsets, dest, dest_off, slot, row,
+                            raw(hub.workspace_bytes(hub.OP_DISPATCH_LAYOUT, N=N, E=E, K=K)))
+    xp, y, y2 = x.new_empty(M, H), x.new_full((M, H), float("nan")), x.new_full((M, H), float("nan"))
+    ws = raw(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F))
+    hub.moe_permute(x, K, slot, row, xp)
+    hub.moe_grouped_ffn(xp, offsets, Wg, Wu, Wd, y, ws)
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, offsets, ws)
+    hub.moe_ffn_gate_up_gather(x, K, offsets, row, Wg, Wu, ws)
+    hub.moe_ffn_down(offsets, Wd, y2, ws)
+    assert torch.equal(y, y2)
+    sums, out = torch.empty(N, H, device="cuda"), x.new_empty(N, H)
+    hub.moe_ffn_down_combine(K, offsets, Wd, row, w, sums, out, ws)
+    hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+    want_y, want = torch.zeros(M, H, dtype=torch.float64, device="cuda"), torch.zeros(N, H, dtype=torch.float64, device="cuda")
+    for n in range(N):
+        for k in range(K):
+            e, xr = int(idx[n, k]), x[n].double()
+            a = torch.nn.functional.silu(Wg[e].double() @ xr) * (Wu[e].double() @ xr)
+            want_y[slot[n * K + k]] = Wd[e].double() @ a.to(torch.bfloat16).double()
+            want[n] += float(w[n, k]) * want_y[slot[n * K + k]]
+    # one rounding to bf16 each (2^-9 at most); fp32 sums are far below that
+    assert float((y.double() - want_y).norm() / want_y.norm()) < 2.0 ** -9
+    assert float((out.double() - want).norm() / want.norm()) < 2.0 ** -9
