@@ -258,12 +258,28 @@ struct FfnPlan {
 // A tile of a short reduction is mostly start and end, hence the higher limit there.  With many experts (128 of H = F =
 // 2880: 642 / 334 -> 830 / 405) thin workgroups are too short-lived themselves.  The bound on M keeps the worst case, all
 // rows with one expert, at a few passes over its weights, all but the first from the caches.
+// Where the lines lie: both forms on 4000 random launches that the lines take, 1 - 128 experts, K 512 - 16384, rows spread
+// evenly, by Zipf's law or all with one expert: twice as fast in the median, 0.2 % of them more than 1 % slower.  Up to
+// 64 tiles thin never lost.  Beyond that every block of columns reads the rows of A again, which counts with rows * K: 4
+// experts, K 7168, N 4096, 31 rows each 82 -> 96, 16 experts, K 15488, N 896, 16 rows 120 -> 125, but 16 rows of K 6464 62
+// -> 53.  Above 176 tiles long reductions lose, spread rows at least: 8 experts, K 5120, N 3264, 2 rows 62 -> 72, K 6976, N
+// 8640, 1 row 137 -> 151, but 12 experts, K 3584, N 1728, 2 rows 76 -> 70.  Above 384 tiles of 256 weight rows the thin
+// form's last round decides: 8 experts, N 6400, K 1280, 13 rows 64 -> 77, K 1984, 8 rows 86 -> 95, but 16 experts, N 3136, K
+// 1024, 16 rows 36 -> 23.
 constexpr int kThinMaxRows = 256;
-static bool use_thin(int64_t M, int64_t experts, int64_t tiles, int64_t Kdim)
+// tiles: of the tiled form, tile_rows weight rows each
+static bool use_thin(int64_t M, int64_t experts, int64_t tiles, int tile_rows, int64_t Kdim)
 {
     if (M > kThinMaxRows || M > 32 * experts)
         return false;
-    return tiles <= 128 || (tiles <= 224 && M <= 4 * experts) || (tiles <= 448 && M <= 16 * experts && Kdim <= 2048);
+    const int64_t reread = M * Kdim / (8192 * experts); // columns of A per expert, in units of 8192
+    if (tiles <= 128)
+        return tiles <= 64 || reread < 24;
+    if (tiles <= 224 && M <= 4 * experts && (Kdim <= 4096 || (tiles <= 176 && reread < 3)))
+        return true;
+    if (M > 16 * experts || Kdim > 2048)
+        return false;
+    return tiles <= 384 || (tiles <= 448 && (tile_rows == 128 || Kdim <= 1024 || M <= 2 * experts));
 }
 // Workgroups of four blocks of weight rows instead of two read the rows of A half as often: better once there are some
 // rows and enough workgroups (8 experts, H 7168, F 2048, 16 rows each, 512 of them: 114 -> 102 us; one row: 91 -> 91; 2
@@ -299,8 +315,8 @@ static FfnPlan make_plan(int64_t M, int64_t H, int64_t F, int E_local)
     // (the workspace's layout is the tiled form's, so that its size keeps growing with M)
     const int thin_tiles = (int)(M / kThinRows + E_local < M ? M / kThinRows + E_local : M);
     const int64_t experts = E_local < M ? E_local : M;
-    p.thin1 = use_thin(M, experts, experts * p.n_tiles1, H) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
-    p.thin2 = use_thin(M, experts, experts * p.n_tiles2, F) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
+    p.thin1 = use_thin(M, experts, experts * p.n_tiles1, 256, H) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
+    p.thin2 = use_thin(M, experts, experts * p.n_tiles2, p.out_cols2, F) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
     if (p.thin1) {
         p.max_m_tiles1 = thin_tiles, p.n_tiles1 = 1;
         p.out_cols1 = wide_thin(M, experts, experts * ceil_div(F, 32)) ? 32 : 16;

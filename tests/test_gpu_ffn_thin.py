@@ -124,3 +124,50 @@ def test_few_tokens_with_several_experts_each(N, E, K, H, F):
     # one rounding to bf16 each (2^-9 at most); fp32 sums are far below that
     assert float((y.double() - want_y).norm() / want_y.norm()) < 2.0 ** -9
     assert float((out.double() - want).norm() / want.norm()) < 2.0 ** -9
+
+
+# On both sides of the rule's lines: tiles (gate/up: of 128 columns; down: of 128, or of 256 beyond 256 of those), rows per
+# expert, reduction length.
+EDGES = [
+    ([30, 31, 34, 33], 6144, 2176),      # gate/up 68 tiles, 128 rows * 6144 (24 * 8192 per expert): tiled
+    ([30, 31, 34, 32], 6144, 2176),      # ... and the last few-row launch
+    ([1, 4, 7, 4], 6080, 4224),          # 132 tiles, 16 rows * 6080 ...
+    ([1, 4, 7, 4], 6144, 4224),          # ... and one K tile more
+    ([4, 0, 8, 4], 4096, 5760),          # 180 tiles, K 4096 ...
+    ([4, 0, 8, 4], 4160, 5760),          # ... and one K tile more
+    ([4, 0, 8, 4], 5760, 4096),          # down projection of 180 narrow tiles, K 4096 ...
+    ([4, 0, 8, 4], 5760, 4160),          # ... and one K tile more
+    ([16, 9, 23, 16], 1024, 12416),      # gate/up 388 tiles: K 1024 with 16 rows ...
+    ([16, 9, 23, 16], 1088, 12416),      # ... 1088 with 16 (tiled) ...
+    ([2, 1, 3, 2], 1088, 12416),         # ... and with 2
+    ([16, 9, 23, 16], 1088, 12288),      # 384 tiles
+]
+
+
+@pytest.mark.parametrize("rows,H,F", EDGES, ids=[f"{len(r)}x{max(r)}-{h}-{f}" for r, h, f in EDGES])
+def test_lines_of_the_rule(rows, H, F):
+    import torch
+    import paper_2605_05888_amd as hub
+    print("few rows, lines of the rule", rows, H, F, flush=True)
+    E, M = len(rows), sum(rows)
+    seg = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(17)
+    normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    dseg = torch.from_numpy(seg).cuda()
+    ws = torch.empty(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    y = torch.full((M, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hub.moe_grouped_ffn(xp, dseg, Wg, Wu, Wd, y, ws)
+    hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+    y2 = torch.full_like(y, float("nan"))
+    hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
+    hub.moe_ffn_gate_up_down(xp, dseg, Wg, Wu, Wd, y2, ws)
+    assert torch.equal(y, y2)
+    for e in range(E):
+        lo, hi = int(seg[e]), int(seg[e + 1])
+        if lo == hi:
+            continue
+        x = xp[lo:hi].double()
+        a = torch.nn.functional.silu(x @ Wg[e].double().T) * (x @ Wu[e].double().T)
+        want = a.to(torch.bfloat16).double() @ Wd[e].double().T
+        assert float((y[lo:hi].double() - want).norm() / want.norm()) < 2.0 ** -9, e   # (one rounding of y)
