@@ -231,8 +231,9 @@ template <bool kSwiglu> using ShallowTile = GemmCfg<64, 256, 1, 4, kSwiglu, 64, 
 
 // The down projection with 128-column tiles, for launches with fewer tiles than compute units (few
 // tokens): every tile of such a launch streams its whole weight panel alone and the launch lasts as
-// long as one tile, so half as wide a panel on twice as many compute units halves it.  Every output
-// element is the same sum in the same order, so y has the same bits as with the 256-column tiles.
+// long as one tile, so half as wide a panel on twice as many compute units halves it.  Where reductions
+// are not turned (turn_of below) every output element is the same sum in the same order as with the
+// 256-column tiles, so y has the same bits; a turned one starts at a K tile that depends on the tile's width.
 template <bool kSwiglu> using NarrowBig = GemmCfg<256, 128, 2, 2, kSwiglu, 64, 6, 0x2222, 0x1111, 0, 64>;
 template <bool kSwiglu> using NarrowShallow = GemmCfg<64, 128, 1, 4, kSwiglu, 64, 8, 0x1010, 0x1111, 1>;
 // upper bound of the down projection's 256-column tiles up to which the narrow form is used
@@ -397,18 +398,31 @@ static size_t lds_bytes_of()
 // block of eight (so that tiles that share operands in an XCD's L2 stay together) 2 KiB further on.  GEMM1 of 64 experts,
 // F 2560, 16 / 144 rows each, us: K 2048 276 / 349 -> 230 / 312, K 4096 481 / 645 -> 430 / 566, K 6144 716 / 949 -> 640 /
 // 831, K 8192 904 / 1192 -> 843 / 1088.  Other strides spread by themselves and lose up to 4 % (K 2560, 3072, 3584).  Above
-// 8192 the rows of A that the turned tiles share no longer fit the L2 (K 14336, 256 rows: 268 -> 281).  From 512 rows per
-// expert on the matrix cores bound the launch and it is up to 1 % slower.
-constexpr int kChannelStride = 4096, kTurnTiles = 16, kMaxTurnedK = 8192;
-constexpr int64_t kMaxTurnedRows = 512;
+// 8192 the rows of A that the turned tiles share no longer fit the L2 (K 14336, 256 rows: 268 -> 281).  From 256 rows per
+// expert on the matrix cores bound the launch, and it takes channels that streaming would not fill where there are fewer
+// tiles than compute units, or one or two starting points only: of 900 random launches (K 2048 - 8192, unturned -> turned)
+// those within all the lines take 0.95 of the time in the median, below 64 rows 0.93; with 256 to 600 rows it is 1.00, with
+// fewer than 192 tiles 1.01 (64 experts, K 4096, N 256, 40 rows 53 -> 65), with two column tiles 1.01 (256 experts, K 2048,
+// N 256, 12 rows 98 -> 104).
+constexpr int kChannelStride = 4096, kTurnTiles = 16, kMaxTurnedK = 8192, kMinTurnedTiles = 192;
+constexpr int64_t kMaxTurnedRows = 256;
+
+// tiles: column tiles of the launch's tile width
+static int turn_of(int64_t M, int E_local, int Kdim, int64_t tiles)
+{
+    const int64_t experts = E_local < M ? E_local : M; // at most so many have rows
+    const bool turned = (int64_t)Kdim * 2 % kChannelStride == 0 && Kdim <= kMaxTurnedK && M < kMaxTurnedRows * E_local &&
+                        tiles > 2 && tiles * experts >= kMinTurnedTiles;
+    return turned ? kTurnTiles : 0;
+}
 
 static GemmArgs gemm_args(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0, const uint16_t *B1,
-                          uint16_t *C, TileTableHeader *hdr, const TileEntry *table, int patch)
+                          uint16_t *C, TileTableHeader *hdr, const TileEntry *table, int patch, int out_cols)
 {
     GemmArgs g = {};
     g.A = A, g.M = M, g.Kdim = Kdim, g.Ndim = Ndim, g.B0 = B0, g.B1 = B1, g.C = C, g.hdr = hdr, g.table = table;
     g.patch = patch, g.gather_div = 1;
-    g.k_turn = (int64_t)Kdim * 2 % kChannelStride == 0 && Kdim <= kMaxTurnedK && M < kMaxTurnedRows * E_local ? kTurnTiles : 0;
+    g.k_turn = turn_of(M, E_local, Kdim, ceil_div(Ndim, out_cols));
     return g;
 }
 
@@ -431,7 +445,7 @@ static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int
                         const int32_t *gather_rows = nullptr, int gather_div = 1, uint32_t gather_bytes = 0,
                         const float *scatter_w = nullptr)
 {
-    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, patch);
+    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, patch, Main::kOutCols);
     g.gather_rows = gather_rows, g.gather_div = gather_div, g.gather_bytes = gather_bytes, g.scatter_w = scatter_w;
     if (g.k_turn)
         launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, true>(g, st);
@@ -560,9 +574,9 @@ static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp,
                         hipStream_t st)
 {
     GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
-                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, kPatch);
+                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, kPatch, p.out_cols1);
     GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, kPatch);
+                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, kPatch, p.out_cols2);
     g1.ready = g2.ready = k.ready;
     g1.hdr_dep = g2.hdr_dep = k.hdr1;
     g1.ready_per_launch = g2.ready_per_launch = BigTile<true>::kWaves * p.n_tiles1;

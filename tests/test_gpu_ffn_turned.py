@@ -6,19 +6,23 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 ROWS = [300, 20, 64, 65, 276, 1, 0, 530]
-SIZES = [(2048, 128 * 17 + 64),  # gate/up turned: shallow tiles at 0 and 1 K tiles of 16, others from column tile 8 on
-         (256 * 17 + 64, 2048),  # down projection turned
-         (4096, 4096),           # both, four starting points
-         (6144, 1216)]           # a number of K tiles that 16 does not divide evenly into turns
+# H, F, how often ROWS (reductions are turned from 192 column tiles on, of all experts together)
+SIZES = [(2048, 128 * 17 + 64, 1),  # too few tiles: not turned
+         (2048, 128 * 17 + 64, 2),  # gate/up turned: shallow tiles at 0 and 1 K tiles of 16, others from column tile 8 on
+         (256 * 17 + 64, 2048, 1),  # down projection turned
+         (4096, 4096, 1),           # both, four starting points
+         (6144, 1216, 1),
+         (6144, 1216, 4)]           # a number of K tiles that 16 does not divide evenly into turns
 
 
-@pytest.mark.parametrize("H,F", SIZES)
-def test_turned_reduction(H, F):
+@pytest.mark.parametrize("H,F,times", SIZES)
+def test_turned_reduction(H, F, times):
     import torch
     import paper_2605_05888_amd as hub
-    print("turned", H, F, flush=True)
-    E, M = len(ROWS), sum(ROWS)
-    seg = np.concatenate([[0], np.cumsum(ROWS)]).astype(np.int32)
+    print("turned", H, F, times, flush=True)
+    rows_of = ROWS * times
+    E, M = len(rows_of), sum(rows_of)
+    seg = np.concatenate([[0], np.cumsum(rows_of)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(11)
     normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
     xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
@@ -48,15 +52,17 @@ def test_turned_reduction(H, F):
 
 
 # narrow column tiles in the down projection (up to 256 tiles of 256 columns) and wide ones; gate/up, down or both turned
-@pytest.mark.parametrize("H,F", [(2048, 320), (320, 2048), (2048, 4096), (6144, 1216), (5696, 2048), (6144, 4096)])
-def test_turned_reduction_in_the_other_forms(H, F):
+@pytest.mark.parametrize("H,F,times", [(2048, 320, 1), (320, 2048, 1), (2048, 4096, 1), (6144, 1216, 1), (5696, 2048, 1), (6144, 4096, 1),
+                                       (2048, 320, 8), (320, 2048, 8), (2048, 4096, 2), (6144, 1216, 4), (5696, 2048, 2)])
+def test_turned_reduction_in_the_other_forms(H, F, times):
     """Both GEMMs in one launch, the combine in the down projection's epilogue, and every segment reversed (so that a
     remainder of rows that rode with a full tile is an ordinary part of it): the bits of the separate launches."""
     import torch
     import paper_2605_05888_amd as hub
-    print("turned, other forms", H, F, flush=True)
-    E, M = len(ROWS), sum(ROWS)
-    seg = np.concatenate([[0], np.cumsum(ROWS)]).astype(np.int32)
+    print("turned, other forms", H, F, times, flush=True)
+    rows_of = ROWS * times
+    E, M = len(rows_of), sum(rows_of)
+    seg = np.concatenate([[0], np.cumsum(rows_of)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(12)
     normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
     xp, Wg, Wu, Wd = normal((M, H), 1.0), normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)

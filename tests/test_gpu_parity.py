@@ -341,7 +341,8 @@ def test_grouped_ffn_random_segmentations(G, seed):
     assert np.array_equal(G.host(G.gpu_ffn(*args)), y)
     # The down projection picks 128-column tiles when the launch can have only few tiles (judged by an upper
     # bound from M and the number of experts) and 256-column tiles otherwise; 300 empty experts in front push
-    # this launch over the bound.  Every output element is the same sum in the same order: same bits.
+    # this launch over the bound.  Every output element is the same sum in the same order (F is not a multiple of
+    # 2048, so no reduction is turned): same bits.
     pad = 300
     seg_p = np.concatenate([np.zeros(pad, np.int32), seg]).astype(np.int32)
     cfg_p = dataclasses.replace(cfg, E=E + pad)
