@@ -335,7 +335,7 @@ constexpr int kRbTok = 32, kRbExp = 32, kRbWaves = 8;
 template <bool kBf16>
 __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
     const void *__restrict__ x, int64_t N, int H, const float *__restrict__ W_r, const float *__restrict__ bias,
-    int E, float *__restrict__ logits)
+    int E, float *__restrict__ logits, bool by_expert)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int kG = 8, kXb = kBf16 ? 2 : 4;
@@ -350,24 +350,30 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
     const int ps = wave % 2, tg = wave / 2 % 2, eg = wave / 4;
     const int blk = lane / 16, c = lane % 16;
 
-    // ---- tiles.  Workgroup ids are dealt round-robin to the XCDs: an XCD takes all expert tiles of a token tile,
-    //      next to each other, so the tokens' rows are fetched once into its L2.
-    const int e_tiles = (E + kRbExp - 1) / kRbExp, xcd = blockIdx.x % 8, per_xcd = gridDim.x / 8;
-    const int64_t tok_tiles = (N + kRbTok - 1) / kRbTok;
-    struct Place { // tile i of this XCD is expert tile i % e_tiles of its token tile i / e_tiles
-        int64_t t;
-        int e;
+    // ---- tiles.  Workgroup ids are dealt round-robin to the XCDs; each XCD takes an eighth of the tiles, one run of the
+    //      list.  The list goes token tile by token tile, so the tokens' rows are fetched into one L2 and W_r into all of
+    //      them, or, with `by_expert` (W_r is the larger one), the other way round.  (All expert tiles of a token tile to
+    //      the XCD of its number: 582 tokens, 384 experts are 19 x 12 tiles, three XCDs had 36 of them on 32 workgroups.)
+    const unsigned e_tiles = (E + kRbExp - 1) / kRbExp, tok_tiles = (unsigned)((N + kRbTok - 1) / kRbTok);
+    const unsigned tiles = tok_tiles * e_tiles; // (below 2^31: N < 2^31 and at most 32 expert tiles)
+    const unsigned inner = by_expert ? tok_tiles : e_tiles; // tiles that follow each other over one row of the list
+    const unsigned xcd = blockIdx.x % 8, per_xcd = gridDim.x / 8, share = tiles / 8, rest = tiles % 8;
+    struct Place {
+        unsigned outer, inner; // position in the list
+        int left;              // tiles of this XCD from here on; <= 0: none
     };
-    const Place step = {per_xcd / e_tiles, per_xcd % e_tiles};
-    const Place first = {blockIdx.x / 8 / e_tiles, (int)(blockIdx.x / 8) % e_tiles};
+    const unsigned from = xcd * share + (xcd < rest ? xcd : rest) + blockIdx.x / 8;
+    const Place step = {per_xcd / inner, per_xcd % inner, (int)per_xcd};
+    const Place first = {from / inner, from % inner, (int)(share + (xcd < rest)) - (int)(blockIdx.x / 8)};
     auto advance = [&](Place &p) { // by per_xcd tiles
-        p.t += step.t;
-        p.e += step.e;
-        if (p.e >= e_tiles)
-            p.e -= e_tiles, ++p.t;
+        p.outer += step.outer;
+        p.inner += step.inner;
+        if (p.inner >= inner)
+            p.inner -= inner, ++p.outer;
+        p.left -= step.left;
     };
-    const int64_t my_tokens = tok_tiles > xcd ? (tok_tiles - 1 - xcd) / 8 + 1 : 0; // token tiles of this XCD
-    auto token_of = [&](const Place &p) { return (p.t * 8 + xcd) * kRbTok; };
+    auto token_of = [&](const Place &p) { return (int64_t)(by_expert ? p.inner : p.outer) * kRbTok; };
+    auto expert_of = [&](const Place &p) { return (int)(by_expert ? p.outer : p.inner) * kRbExp; };
 
     // ---- loads of a K tile
     int x_off[kXLoads], w_off[kWLoads];
@@ -395,12 +401,13 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
     const unsigned char *x_at, *w_at;
     int x_bytes, w_bytes;
     auto load_from = [&]() { // (past the last tile: no bytes, so that the number of loads in flight stays)
-        const bool there = load.t < my_tokens;
+        const bool there = load.left > 0;
         const int64_t n = there ? token_of(load) : 0;
+        const int e = there ? expert_of(load) : 0;
         x_at = static_cast<const unsigned char *>(x) + n * H * kXb;
-        w_at = reinterpret_cast<const unsigned char *>(W_r + load.e * kRbExp);
+        w_at = reinterpret_cast<const unsigned char *>(W_r + e);
         x_bytes = there ? (int)(N - n < kRbTok ? N - n : kRbTok) * H * kXb : 0;
-        w_bytes = there ? (H * E - load.e * kRbExp) * 4 : 0;
+        w_bytes = there ? (H * E - e) * 4 : 0;
     };
     load_from();
     auto issue = [&](int stage) {
@@ -491,7 +498,7 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
     read(o0, 0, 0);
     int stage = 0;
     float *const box = reinterpret_cast<float *>(lds + kStages * kStage); // [wavefront][2 * kG][lane]
-    for (Place at = first; at.t < my_tokens; advance(at)) {
+    for (Place at = first; at.left > 0; advance(at)) {
 #pragma unroll
         for (int g = 0; g < kG; ++g)
 #pragma unroll
@@ -541,7 +548,7 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
         for (int u = 0; u < 2; ++u) {
             float val = fold_in_lane<kG>(v[u]);
             const int64_t n = n_tile + tg * kRtTok + 4 * blk + 2 * ps + u;
-            const int e = at.e * kRbExp + eg * kRtExp + c;
+            const int e = expert_of(at) + eg * kRtExp + c;
             if (n < N && e < E) {
                 if (bias)
                     val = val + bias[e];
@@ -661,9 +668,9 @@ static void launch_logits(const void *x, int64_t N, int64_t H, const float *W_r,
     // against 49) and its 16-byte loads of W_r are aligned; below that the small form spreads over more of them.
     const int64_t tiles = ceil_div(N, kRbTok) * ceil_div(E, kRbExp);
     if (!select && E % 4 == 0 && tiles >= 128 && H * kRbTok * 4 < ((int64_t)1 << 31) && H * (int64_t)E * 4 < ((int64_t)1 << 31)) {
-        const int64_t groups = ceil_div(ceil_div(N, kRbTok), 8) * 8 * ceil_div(E, kRbExp);
+        const int64_t groups = ceil_div(tiles, 8) * 8;
         hipLaunchKernelGGL(router_logits_large<kBf16>, dim3((unsigned)(groups < 256 ? groups : 256)), dim3(kWave * kRbWaves), 0,
-                           st, x, N, (int)H, W_r, bias, E, logits);
+                           st, x, N, (int)H, W_r, bias, E, logits, N * (kBf16 ? 2 : 4) < (int64_t)E * 4);
         return;
     }
     // One dimension of a grid holds fewer than 2^32 threads (2^23 of these workgroups): the token tiles go in rows.

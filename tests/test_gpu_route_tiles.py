@@ -15,7 +15,10 @@ CASES = [(1, 8, 16, 3, mi.BF16), (17, 520, 17, 5, mi.BF16), (16, 2048, 15, 15, m
          (8192, 128, 16, 2, mi.BF16),                                    # selection in the logits kernel, many tiles
          (8160, 136, 20, 2, mi.BF16), (8193, 264, 20, 2, mi.F32),        # large form, ragged last tokens and columns
          (515, 8, 256, 8, mi.BF16), (2000, 648, 68, 4, mi.F32), (4100, 384, 32, 4, mi.BF16),
-         (9001, 72, 100, 6, mi.BF16)]                                    # several tiles per workgroup, one K tile each
+         (9001, 72, 100, 6, mi.BF16),                                    # several tiles per workgroup, one K tile each
+         # large form, the tiles' list by experts (x smaller than W_r) and by tokens, in runs of different lengths per XCD
+         (582, 136, 384, 2, mi.F32), (300, 264, 512, 8, mi.BF16), (129, 520, 1024, 4, mi.BF16), (1637, 72, 160, 1, mi.BF16),
+         (2961, 264, 96, 3, mi.F32)]
 
 
 @pytest.mark.parametrize("N,H,E,K,dtype", CASES)
