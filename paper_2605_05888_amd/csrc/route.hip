@@ -664,17 +664,20 @@ static void launch_logits(const void *x, int64_t N, int64_t H, const float *W_r,
                           int score_mode, int32_t *topk_idx, float *topk_w, float *logits, bool select, hipStream_t st)
 {
     const int64_t e_tiles = ceil_div(E, kRtExp);
-    // The large form once it has a tile for half of the compute units (512 tokens, H = 7168, 256 experts: 45 us
-    // against 49) and its 16-byte loads of W_r are aligned; below that the small form spreads over more of them.
-    const int64_t tiles = ceil_div(N, kRbTok) * ceil_div(E, kRbExp);
-    if (!select && E % 4 == 0 && tiles >= 128 && H * kRbTok * 4 < ((int64_t)1 << 31) && H * (int64_t)E * 4 < ((int64_t)1 << 31)) {
+    // The large form (its 16-byte loads of W_r aligned) once the small one has more workgroups than there are compute
+    // units; a workgroup of the small form then waits for, or shares a unit with, another.  Small / large, us: 256
+    // workgroups: 250 tokens, H 3584, 256 experts, fp32 21 / 30; 260: 1033 tokens, H 2944, 64 experts 25 / 24; 272: 532
+    // tokens, H 1152, 128 experts, fp32 18 / 15; 426: 1136 tokens, H 5696, 96 experts, fp32 51 / 38; 490: 3920 tokens, H
+    // 2304, 32 experts 28 / 22.  (Between 300 and 400 two of fourteen were better off small, 4 - 6 %.)
+    const int64_t tok_tiles = ceil_div(N, kRtTok), tiles = ceil_div(N, kRbTok) * ceil_div(E, kRbExp);
+    if (!select && E % 4 == 0 && tok_tiles * e_tiles > 256 && H * kRbTok * 4 < ((int64_t)1 << 31) && H * (int64_t)E * 4 < ((int64_t)1 << 31)) {
         const int64_t groups = ceil_div(tiles, 8) * 8;
         hipLaunchKernelGGL(router_logits_large<kBf16>, dim3((unsigned)(groups < 256 ? groups : 256)), dim3(kWave * kRbWaves), 0,
                            st, x, N, (int)H, W_r, bias, E, logits, N * (kBf16 ? 2 : 4) < (int64_t)E * 4);
         return;
     }
     // One dimension of a grid holds fewer than 2^32 threads (2^23 of these workgroups): the token tiles go in rows.
-    const int64_t tok_tiles = ceil_div(N, kRtTok), fit = ((int64_t)1 << 22) / e_tiles, per_row = tok_tiles < fit ? tok_tiles : fit;
+    const int64_t fit = ((int64_t)1 << 22) / e_tiles, per_row = tok_tiles < fit ? tok_tiles : fit;
     const dim3 grid((unsigned)(per_row * e_tiles), (unsigned)ceil_div(tok_tiles, per_row));
     if (select)
         hipLaunchKernelGGL((router_logits_small<kBf16, true>), grid, dim3(512), 0, st, x, N, H, W_r, bias, E, logits, K,

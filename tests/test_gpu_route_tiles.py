@@ -1,5 +1,5 @@
 """Router logits at the edges of its tiles: 16 tokens x 16 experts and batches of 512 columns in the small form,
-32 tokens x 32 experts and K tiles of 128 columns in the large one (from 128 tiles on, E % 4 == 0).
+32 tokens x 32 experts and K tiles of 128 columns in the large one (from 257 small tiles on, E % 4 == 0).
 Bit for bit against the oracle's fp32 order; selection included."""
 import dataclasses
 
@@ -18,7 +18,9 @@ CASES = [(1, 8, 16, 3, mi.BF16), (17, 520, 17, 5, mi.BF16), (16, 2048, 15, 15, m
          (9001, 72, 100, 6, mi.BF16),                                    # several tiles per workgroup, one K tile each
          # large form, the tiles' list by experts (x smaller than W_r) and by tokens, in runs of different lengths per XCD
          (582, 136, 384, 2, mi.F32), (300, 264, 512, 8, mi.BF16), (129, 520, 1024, 4, mi.BF16), (1637, 72, 160, 1, mi.BF16),
-         (2961, 264, 96, 3, mi.F32)]
+         (2961, 264, 96, 3, mi.F32),
+         # 256 tiles of the small form, 258 and 272
+         (2048, 72, 32, 2, mi.BF16), (2049, 72, 32, 2, mi.BF16), (256, 136, 260, 3, mi.F32)]
 
 
 @pytest.mark.parametrize("N,H,E,K,dtype", CASES)
