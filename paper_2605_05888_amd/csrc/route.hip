@@ -19,7 +19,7 @@
 // pair registers of one lane.
 //
 // Tokens past N and experts past E repeat the last one (their results are not stored).  Rows of W_r past H
-// count as zeros, and columns of x past H as zeros or any finite value: adding a zero product never changes a partial
+// count as zeros, and so do columns of x past H: adding a zero product never changes a partial
 // sum (partials start at +0 and can never become -0), so a ragged last step gives the R64 sum bit for bit.
 #include <math.h>
 
@@ -376,12 +376,15 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
     auto expert_of = [&](const Place &p) { return (int)(by_expert ? p.outer : p.inner) * kRbExp; };
 
     // ---- loads of a K tile
-    int x_off[kXLoads], w_off[kWLoads];
+    const int KT = (H + kTile - 1) / kTile;
+    int x_off[kXLoads], x_off_last[kXLoads], w_off[kWLoads]; // (of the last K tile: past the end where columns are past H)
 #pragma unroll
     for (int i = 0; i < kXLoads; ++i) {
         constexpr int kChunks = kXRow / 16;
         const int r = (wave * kXLoads + i) * (kWave / kChunks) + lane / kChunks;
-        x_off[i] = r * H * kXb + (((lane % kChunks) ^ (r & 15)) << 4);
+        const int in_row = ((lane % kChunks) ^ (r & 15)) << 4;
+        x_off[i] = r * H * kXb + in_row;
+        x_off_last[i] = in_row < (H - (KT - 1) * kTile) * kXb ? x_off[i] : 0x7FFFFFF0;
     }
 #pragma unroll
     for (int i = 0; i < kWLoads; ++i) {
@@ -392,10 +395,9 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
         w_off[i] = (row * E + (lane / 32) * kRtExp + (lane % 4) * 4) * 4;
     }
     // The position of a K tile goes into the base addresses and the byte counts of the resources: the range check
-    // covers the per-lane offset, and rows of W_r past H and tokens past N have to come back as zeros.  Columns past
-    // H of any token but the tile's last are the start of the next token's row: finite values that meet zeros.
+    // covers the per-lane offset, and rows of W_r past H and tokens past N have to come back as zeros.  Columns past H
+    // would be the start of the next token's row; they come back as zeros too, so that an infinity there stays there.
     // Kept as running values: little scalar work per K tile.
-    const int KT = (H + kTile - 1) / kTile;
     Place load = first; // of the stream's next K tile: its tile ...
     int load_kt = 0;    // ... and its position there
     const unsigned char *x_at, *w_at;
@@ -410,6 +412,10 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
         w_bytes = there ? (H * E - e) * 4 : 0;
     };
     load_from();
+    int x_now[kXLoads];
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i)
+        x_now[i] = KT == 1 ? x_off_last[i] : x_off[i];
     auto issue = [&](int stage) {
         const __amdgpu_buffer_rsrc_t rs_x =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(x_at), 0, x_bytes, 0x00020000);
@@ -420,7 +426,7 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
 #pragma unroll
         for (int i = 0; i < kXLoads; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rs_x, (__attribute__((address_space(3))) void *)(st + (wave * kXLoads + i) * 1024), 16, x_off[i], 0, 0, 0);
+                rs_x, (__attribute__((address_space(3))) void *)(st + (wave * kXLoads + i) * 1024), 16, x_now[i], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < kWLoads; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -430,10 +436,15 @@ __global__ __launch_bounds__(kWave *kRbWaves, 2) void router_logits_large(
         x_bytes = x_bytes > kTile * kXb ? x_bytes - kTile * kXb : 0;
         w_at += kTile * E * 4;
         w_bytes = w_bytes > kTile * E * 4 ? w_bytes - kTile * E * 4 : 0;
-        if (++load_kt == KT) {
-            load_kt = 0;
-            advance(load);
-            load_from();
+        if (++load_kt >= KT - 1) {
+            if (load_kt == KT) {
+                load_kt = 0;
+                advance(load);
+                load_from();
+            }
+#pragma unroll
+            for (int i = 0; i < kXLoads; ++i)
+                x_now[i] = load_kt == KT - 1 ? x_off_last[i] : x_off[i];
         }
     };
 

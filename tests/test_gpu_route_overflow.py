@@ -61,9 +61,11 @@ def test_picks_are_distinct_experts_whatever_the_logits(N, H, E, K):
         check_layout_is_valid(want, E, 1, {k: G.host(v) for k, v in out.items()})
 
 
-@pytest.mark.parametrize("N,H,E,bf16", [(19, 520, 30, False), (19, 584, 30, True), (40, 4, 6, False), (33, 1000, 15, True)])
+@pytest.mark.parametrize("N,H,E,bf16", [(19, 520, 30, False), (19, 584, 30, True), (40, 4, 6, False), (33, 1000, 15, True),
+                                          (2100, 520, 32, False), (2100, 584, 32, True), (2100, 128, 32, True)])
 def test_an_infinity_in_x_meets_the_columns_of_its_row_only(N, H, E, bf16):
-    """H is no multiple of the 512 columns of a batch: what stands for the columns past H must not be the infinity."""
+    """H is no multiple of the 512 columns of a batch, or of the 128 of the large form's K tile: what stands for the columns
+    past H must be neither an infinity of the row nor one of the next row."""
     import gpu_layer as G
     import moe_inputs as mi
     import moe_inputs.device as mid
