@@ -212,6 +212,12 @@ int moe_permute(const void *x, int dtype, int64_t N, int64_t H, int K,
  * ws: moe_workspace_bytes(MOE_OP_GROUPED_FFN, M, H, E_local, 0, 0, F, dtype).
  * For an expert-parallel rank pass seg_offsets = expert_offsets + g*E/G and the
  * weights of that destination's experts.
+ * The order in which the products of an output element are added (fp32) depends on
+ * M, H, F and E_local, which pick the kernel and where its reductions start, and on
+ * whether the expert has more than 64 rows; not on the other rows, nor on where in
+ * its segment a row lies.  So equal calls give equal bits, whatever the order of an
+ * expert's rows, but the same row in a launch of another size (another batch) may
+ * come out with other last bits of those sums.
  */
 int moe_grouped_ffn(const void *xp, int dtype, int64_t M, int64_t H, int64_t F,
                     int E_local, const int32_t *seg_offsets,

@@ -171,3 +171,30 @@ def test_lines_of_the_rule(rows, H, F):
         a = torch.nn.functional.silu(x @ Wg[e].double().T) * (x @ Wu[e].double().T)
         want = a.to(torch.bfloat16).double() @ Wd[e].double().T
         assert float((y[lo:hi].double() - want).norm() / want.norm()) < 2.0 ** -9, e   # (one rounding of y)
+
+
+@pytest.mark.parametrize("H,F,E,M", [(2048, 1408, 8, 100), (2048, 2048, 24, 800), (576, 320, 6, 500)], ids=["few-rows", "turned", "tiled"])
+def test_a_row_does_not_depend_on_the_others(H, F, E, M):
+    """Same launch size, other rows and other segments (on the same side of 64 rows): a row keeps its bits."""
+    import torch
+    import paper_2605_05888_amd as hub
+    print("row by itself", H, F, E, M, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(29)
+    normal = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    Wg, Wu, Wd = normal((E, F, H), H ** -0.5), normal((E, F, H), H ** -0.5), normal((E, H, F), F ** -0.5)
+    ws = torch.empty(hub.workspace_bytes(hub.OP_GROUPED_FFN, N=M, H=H, E=E, F=F), dtype=torch.uint8, device="cuda")
+    small, large = normal((5, H), 1.0), normal((70, H), 1.0)
+
+    def rows_of(n_small, n_large, at):
+        seg = [0, n_small, n_small + n_large] + [M] * (E - 2)   # expert 2 takes the rest
+        x = normal((M, H), 1.0)
+        x[at:at + 5] = small
+        x[n_small:n_small + 70] = large
+        y = torch.full((M, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+        hub.moe_grouped_ffn(x, torch.tensor(seg, dtype=torch.int32, device="cuda"), Wg, Wu, Wd, y, ws)
+        hub.moe_ffn_status(hub.BF16, M, H, F, E, ws)
+        return y[at:at + 5], y[n_small:n_small + 70]
+
+    a, b = rows_of(5, 70, 0), rows_of(23, 72, 17)
+    assert torch.isfinite(a[0]).all() and torch.isfinite(a[1]).all()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
