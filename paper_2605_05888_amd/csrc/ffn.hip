@@ -251,7 +251,7 @@ struct FfnPlan {
 };
 
 // Few rows per expert, and so few of the tiled kernel's tiles that compute units stay idle: ffn_thin.hip.  GEMM1 / GEMM2,
-// rows per expert given, tiled -> thin, us:
+// every expert with the rows given, tiled -> thin, us:
 //   4 experts, H 2048, F 1408 (44 / 64 tiles):   1: 40 / 23 -> 16 / 12    16: 42 / 25 -> 17 / 12    32: 46 / 28 -> 20 / 12
 //   8 experts, H 7168, F 2048 (128 / 448 tiles): 1: 136 / 63 -> 91 / 49   16: 135 / 63 -> 102 / 56  32: 140 / 64 -> 114 / 64
 //   2 experts, H 4096, F 14336 (224 / 64 tiles): 1: 91 / 104 -> 85 / 49   16: 96 / 110 -> 101 / 59  32: 98 / 112 -> 116 / 67
