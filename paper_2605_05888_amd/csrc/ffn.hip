@@ -417,11 +417,11 @@ static int turn_of(int64_t M, int E_local, int Kdim, int64_t tiles)
 }
 
 static GemmArgs gemm_args(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0, const uint16_t *B1,
-                          uint16_t *C, TileTableHeader *hdr, const TileEntry *table, int patch, int out_cols)
+                          uint16_t *C, TileTableHeader *hdr, const TileEntry *table, int out_cols)
 {
     GemmArgs g = {};
     g.A = A, g.M = M, g.Kdim = Kdim, g.Ndim = Ndim, g.B0 = B0, g.B1 = B1, g.C = C, g.hdr = hdr, g.table = table;
-    g.patch = patch, g.gather_div = 1;
+    g.gather_div = 1;
     g.k_turn = turn_of(M, E_local, Kdim, ceil_div(Ndim, out_cols));
     return g;
 }
@@ -441,11 +441,11 @@ static void launch_gemm_form(const GemmArgs &g, hipStream_t st)
 template <class Main, class Light, bool kSwiglu, bool kGather = false, bool kScatter = false>
 static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0,
                         const uint16_t *B1, uint16_t *C, TileTableHeader *hdr,
-                        const TileEntry *table, int patch, hipStream_t st,
+                        const TileEntry *table, hipStream_t st,
                         const int32_t *gather_rows = nullptr, int gather_div = 1, uint32_t gather_bytes = 0,
                         const float *scatter_w = nullptr)
 {
-    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, patch, Main::kOutCols);
+    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, Main::kOutCols);
     g.gather_rows = gather_rows, g.gather_div = gather_div, g.gather_bytes = gather_bytes, g.scatter_w = scatter_w;
     if (g.k_turn)
         launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, true>(g, st);
@@ -462,11 +462,6 @@ int check_ffn_shape(int dtype, int64_t H, int64_t F)
     return MOE_OK;
 }
 
-// consecutive tiles each XCD takes at a time (see stream_position)
-#ifndef MOE_PATCH
-#define MOE_PATCH 32
-#endif
-constexpr int kPatch = MOE_PATCH;
 // polls (about a microsecond each) a dependent tile spends on its rows before it gives up: seconds
 constexpr int64_t kDefaultWaitLimit = (int64_t)1 << 22;
 
@@ -528,9 +523,9 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
         launch_thin_gate_up(xpb, M, H, F, wg, wu, k.a, k.hdr1, k.tab1, p.max_m_tiles1, p.out_cols1, gather_rows, K, (uint32_t)(N * H * 2), st);
     else if (gather_rows)
         launch_gemm<BigTile<true>, ShallowTile<true>, true, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1,
-                                                                  kPatch, st, gather_rows, K, (uint32_t)(N * H * 2));
+                                                                  st, gather_rows, K, (uint32_t)(N * H * 2));
     else
-        launch_gemm<BigTile<true>, ShallowTile<true>, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, kPatch, st);
+        launch_gemm<BigTile<true>, ShallowTile<true>, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, st);
     return check_launch("moe_ffn_gate_up");
 }
 
@@ -548,9 +543,9 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     if (p.thin2)
         launch_thin_down(k.a, M, H, F, wd, yb, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, nullptr, 1, nullptr, st);
     else if (p.narrow2)
-        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
+        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, st);
     else
-        launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, kPatch, st);
+        launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, st);
     return check_launch("moe_ffn_down");
 }
 
@@ -574,9 +569,9 @@ static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp,
                         hipStream_t st)
 {
     GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
-                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, kPatch, p.out_cols1);
+                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, p.out_cols1);
     GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, kPatch, p.out_cols2);
+                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, p.out_cols2);
     g1.ready = g2.ready = k.ready;
     g1.hdr_dep = g2.hdr_dep = k.hdr1;
     g1.ready_per_launch = g2.ready_per_launch = BigTile<true>::kWaves * p.n_tiles1;
@@ -671,11 +666,11 @@ int launch_ffn_down_combine(int64_t N, int K, int64_t H, int64_t F, int E_local,
     else if (p.narrow2)
         launch_gemm<NarrowBig<false>, NarrowShallow<false>, false, false, true>(
             k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, kPatch, st, row_of_slot, K, 0u, topk_w);
+            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, st, row_of_slot, K, 0u, topk_w);
     else
         launch_gemm<BigTile<false>, ShallowTile<false>, false, false, true>(
             k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, kPatch, st, row_of_slot, K, 0u, topk_w);
+            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, st, row_of_slot, K, 0u, topk_w);
     hipLaunchKernelGGL(round_sums_bf16, dim3((unsigned)ceil_div(n8, 256)), dim3(256), 0, st,
                        reinterpret_cast<const f32x4 *>(sums), static_cast<u32x4 *>(out), n8);
     return check_launch("moe_ffn_down_combine");

@@ -24,7 +24,7 @@
 //     that waits for it, which is what a load from HBM needs here.
 //   * The matrix-core operands are swapped (weights as the "A" operand), so a lane
 //     ends up with 4 consecutive output columns of one row per accumulator
-//     quadruple and stores them as one 8-byte vector.
+//     quadruple, and lanes trade them for 16-byte stores.
 //   * kSwiglu: the B tile holds BN/2 gate rows and the same BN/2 up rows, arranged
 //     so that each wavefront has matching gate/up blocks; the epilogue writes
 //     silu(g)*u, so g and u never reach memory.
@@ -32,7 +32,13 @@
 // Scheduling: the grid is persistent, one workgroup per compute unit.  Workgroups draw tiles
 // from per-XCD counters of the tile table (own XCD first), so the tiles an XCD holds at a
 // time are neighbours in the table's order; while a workgroup multiplies the last K tiles of
-// one output tile, its loads already fetch the first K tiles of its next one.  The table has
+// one output tile, its loads already fetch the first K tiles of its next one.  Between two tiles
+// nothing waits for everything in flight: the ticket of the tile after next is drawn before the
+// epilogue and looked at behind it, the table is read through the scalar cache, and the epilogue's
+// stores go out without branches, so that the compiler keeps count of them.  (With the draw
+// waited for on the spot, vector loads of the table and 8-byte stores: 65536 rows over 8 experts,
+// H 7168, F 2048, down projection 1645 -> 1522 us; 32768 rows over 64, H 2048, F 1408: 244 -> 225.)
+// The table has
 // two streams of tiles, served by two tile geometries inside the one kernel: 256x256 tiles, and
 // 64x256 tiles four K tiles deep for experts with at most 64 rows, which do little arithmetic
 // and live on how many bytes they keep in flight.  A 256-row tile can be "tall": the last full
@@ -99,11 +105,15 @@ constexpr int kReadyBit = 1 << 30;                 // in a drawn tile word: the 
 #define MOE_DEP_STORE_THROUGH 1
 #endif
 
-// Ticket j of an XCD -> position in a stream: each XCD takes runs of `patch` consecutive tiles, so
+// Ticket j of an XCD -> position in a stream: each XCD takes runs of kPatch consecutive tiles, so
 // its L2 sees tiles that share weight and activation rows.
-__device__ __forceinline__ int stream_position(int xcd, int j, int patch)
+#ifndef MOE_PATCH
+#define MOE_PATCH 32
+#endif
+constexpr int kPatch = MOE_PATCH;
+__device__ __forceinline__ int stream_position(int xcd, int j)
 {
-    return (j / patch) * (patch * kXcds) + xcd * patch + (j % patch);
+    return (int)((uint32_t)j / kPatch) * (kPatch * kXcds) + xcd * kPatch + (int)((uint32_t)j % kPatch);
 }
 
 // silu(g) * u with the hardware reciprocal (1 ulp): the result is rounded to bf16 right after
@@ -263,7 +273,6 @@ struct GemmArgs {
     uint16_t *C;
     TileTableHeader *hdr;
     const TileEntry *table;
-    int patch;
     int k_turn; // K tiles by which the start of the reduction moves on from column tile (light tiles) or block of them to the next
     const int32_t *gather_rows;
     int gather_div;
@@ -300,7 +309,6 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     uint16_t *__restrict__ const C = g.C;
     TileTableHeader *__restrict__ const hdr = g.hdr;
     const TileEntry *__restrict__ const table = g.table;
-    const int patch = g.patch;
     const int32_t *__restrict__ const gather_rows = g.gather_rows;
     const int gather_div = g.gather_div;
     const uint32_t gather_bytes = g.gather_bytes;
@@ -343,22 +351,34 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     const int len0 = hdr->len[0], len1 = hdr->len[1];
     const int slot = (blockIdx.x / kXcds) % 32, ls = hdr->light_slots;
     const bool light_first = ((slot + 1) * ls) / 32 > (slot * ls) / 32;
-    auto fetch_tile = [&]() -> int { // thread 0 only
+    // A draw has two parts (thread 0 only): the ticket of the workgroup's own stream and XCD, whose round trip runs under
+    // whatever stands between the two, and the tile it stands for; that counter is rarely spent, so it is taken unseen.
+    auto take_ticket = [&]() -> int {
+        // (an address the compiler takes for a per-lane one: for a uniform address it adds up the lanes' increments first,
+        // and waits for the answer on the spot)
+        uint32_t at = (uint32_t)((light_first ? kXcds : 0) + xcd);
+        asm volatile("" : "+v"(at));
+        return __hip_atomic_fetch_add(&hdr->next[0][0] + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto tile_of_ticket = [&](int ticket) -> int {
+        {
+            const int p = stream_position(xcd, ticket);
+            if (p < (light_first ? len1 : len0))
+                return (light_first ? len0 : 0) + p;
+        }
 #pragma unroll 1
         for (int k = 0; k < 2; ++k) {
             const int s = light_first ? 1 - k : k;
             const int len = s ? len1 : len0;
 #pragma unroll 1
-            for (int i = 0; i < kXcds && len > 0; ++i) {
+            for (int i = k == 0 ? 1 : 0; i < kXcds && len > 0; ++i) {
                 const int x = (xcd + i) % kXcds;
                 int32_t *ctr = &hdr->next[s][x];
-                if (k + i > 0) { // (the first choice is taken without looking: it is rarely spent)
-                    const int seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (stream_position(x, seen, patch) >= len)
-                        continue; // positions grow with the ticket: this counter is spent
-                }
+                const int seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (stream_position(x, seen) >= len)
+                    continue; // positions grow with the ticket: this counter is spent
                 const int j = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int p = stream_position(x, j, patch);
+                const int p = stream_position(x, j);
                 if (p < len)
                     return (s ? len0 : 0) + p;
             }
@@ -367,6 +387,15 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
     // a drawn tile travels as a word: -1 = none, else the table entry, plus (consumer) kReadyBit
     auto entry_of = [](int word) { return word & ~kReadyBit; };
+    // The table was written by an earlier launch: read through the scalar cache, so that a look at it is not a wait for
+    // every load and store in flight.
+    auto read_entry = [&](int word) {
+        typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
+        i32x4 v = {0, 0, 0, 0};
+        if (word >= 0)
+            v = reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uint64_t>(table))[entry_of(word)];
+        return TileEntry{v[0], v[1], v[2], v[3]};
+    };
     auto kind_of = [&](int word) { return kTwo && entry_of(word) >= len0 ? 1 : 0; };
     // consumer, thread 0 only: were the rows this tile reads complete at the time of the draw?
     const int32_t dep_epoch1 =
@@ -382,7 +411,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                 return tile;
             if (!all_done_seen)
                 all_done_seen = __hip_atomic_load(&g.hdr_dep->all_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == dep_epoch1;
-            if (!all_done_seen && !rows_complete(table[tile].m0))
+            if (!all_done_seen && !rows_complete(table[tile].m0)) // (thread 0 only: an ordinary load)
                 return tile;
             return tile | kReadyBit;
         } else {
@@ -444,22 +473,28 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         asm volatile("" : "+v"(lane));
         ld_row = lane / kChunks;
         const int ld_pc = lane % kChunks;
+        // Load group g of a wavefront fills tile rows (wave * groups + g) * kGroupRows + ld_row.  The key depends on the
+        // row modulo 16 and a wavefront's groups start at a multiple of it, so there are 16 / kGroupRows different
+        // chunks, and the rest of an offset is the same for every lane.  (Worked out for each group by itself, the
+        // offsets were some 150 instructions per output tile.)
+        constexpr int kKeys = 16 / Cfg::kGroupRows;
+        static_assert(Cfg::kAGroups % kKeys == 0 && Cfg::kBGroups % kKeys == 0, "groups start at a multiple of 16 rows");
+        const int row_bytes = Kdim * 2, row_off = ld_row * row_bytes;
+        int chunk_off[kKeys];
 #pragma unroll
-        for (int g = 0; g < Cfg::kAGroups; ++g) {
-            const int r = (wave * Cfg::kAGroups + g) * Cfg::kGroupRows + ld_row;
-            a_off[g] = ((kGather ? 0 : r * Kdim) + ((ld_pc ^ row_key<kChunks>(r)) * 8)) * 2;
-        }
+        for (int k = 0; k < kKeys; ++k)
+            chunk_off[k] = (ld_pc ^ row_key<kChunks>(k * Cfg::kGroupRows + ld_row)) * 16;
+#pragma unroll
+        for (int g = 0; g < Cfg::kAGroups; ++g)
+            a_off[g] = chunk_off[g % kKeys] + (kGather ? 0 : row_off + (wave * Cfg::kAGroups + g) * Cfg::kGroupRows * row_bytes);
 #pragma unroll
         for (int g = 0; g < Cfg::kBGroups; ++g) {
-            const int r = (wave * Cfg::kBGroups + g) * Cfg::kGroupRows + ld_row;
-            int col;
+            int col = (wave * Cfg::kBGroups + g) * Cfg::kGroupRows; // of the group's first row
             if (kSwiglu) {
-                const int w = r / Cfg::kWaveN, jj = r % Cfg::kWaveN, half = Cfg::kWaveN / 2;
+                const int w = col / Cfg::kWaveN, jj = col % Cfg::kWaveN, half = Cfg::kWaveN / 2;
                 col = w * half + (jj % half);
-            } else {
-                col = r;
             }
-            b_off[g] = (col * Kdim + ((ld_pc ^ row_key<kChunks>(r)) * 8)) * 2;
+            b_off[g] = chunk_off[g % kKeys] + row_off + col * row_bytes;
         }
         // operand reads: lane (i = lane%32, kg = lane/32) reads chunk (2*ks + kg) of row i of a block.
         // Block and wavefront offsets are multiples of 32 rows, so the key depends on i only, and
@@ -489,10 +524,9 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         int32_t ext; // rows beyond BM (tall tiles)
         int32_t k0;  // K tile the reduction starts with (it wraps around)
     };
-    auto operands_of = [&](int tile) {
+    auto operands_of = [&](int tile, const TileEntry &te) {
         Operands o = {A, B0, 0u, 0u, 0, 0, 0, 0, 0};
         if (tile >= 0) {
-            const TileEntry te = table[entry_of(tile)];
             const int col = te.n_tile & ((1 << kTileColBits) - 1);
             const int n0 = col * Cfg::kOutCols;
             if constexpr (kTurn)
@@ -680,13 +714,16 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
 
     f32x16 acc[Cfg::kBlkM][Cfg::kBlkN];
-    auto mfma_all = [&](int slot, auto act_tag) {
+    // kFirst: the sums start here (a constant addend, no accumulators to clear: 256 instructions a tile)
+    auto mfma_all = [&](int slot, auto act_tag, auto first_tag) {
         constexpr int kAct = decltype(act_tag)::value;
+        constexpr bool kFirst = decltype(first_tag)::value;
+        const f32x16 zero = {};
 #pragma unroll
         for (int i = 0; i < kAct; ++i)
 #pragma unroll
             for (int j = 0; j < Cfg::kBlkN; ++j) // weights first: the result block is [n][m]
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[slot][j], fa[slot][i], kFirst ? zero : acc[i][j], 0, 0, 0);
     };
 
     // Tall tiles: the extra block row of this wavefront.  The 256 accumulators above fill the
@@ -723,6 +760,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
 
     int u = 0; // ring position: A unit of the K tile to multiply next
+    TileEntry te_nxt = read_entry(nxt_t), te_after = {0, 0, 0, 0}; // entries of `nxt_t` and `after_next`
 
     // One output tile: K loop, then the epilogue.  On entry K tile 0 of `cur` is in LDS (everyone's
     // loads, behind a barrier) and the windows before it have issued what they should.
@@ -746,33 +784,36 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             }
             load_x_first(kHalf);
         }
+        if constexpr (kExt) {
 #pragma unroll
-        for (int i = 0; i < Cfg::kBlkM; ++i)
+            for (int i = 0; i < Cfg::kBlkM; ++i)
 #pragma unroll
-            for (int j = 0; j < Cfg::kBlkN; ++j)
+                for (int j = 0; j < Cfg::kBlkN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[i][j][r] = 0.0f;
+                    for (int r = 0; r < 16; ++r)
+                        acc[i][j][r] = 0.0f;
+        }
         read_frags(u, 0, 0, act);
 
         // k-step ks of K tile kt (not its last): position ks+1 of the window goes out, the operands
         // of k-step ks+1 are read, all under this step's MFMAs
-        auto kstep = [&](int kt, auto ks_tag, auto tail_tag) {
+        using no = std::integral_constant<bool, false>;
+        auto kstep = [&](int kt, auto ks_tag, auto tail_tag, auto first_tag) {
             constexpr int ks = decltype(ks_tag)::value;
             issue_position(kt - 1, wrap(u + kUnits - 2), std::integral_constant<int, ks + 1>{}, tail_tag);
             read_frags(u, ks + 1, (ks + 1) & 1, act);
-            mfma_all(ks & 1, act);
+            mfma_all(ks & 1, act, first_tag);
             if constexpr (kExt)
                 mfma_x(ks & 1, ks_tag, kt + 1, half_tag{});
             interleave_under_mfma<kMfma, kReads, loads_at(ks + 1)>();
         };
         // The body is branch free (a branch around the LDS reads would make the compiler wait for
         // them before MFMAs that do not need them).
-        auto ktile = [&](int kt, auto tail_tag) {
-            kstep(kt, std::integral_constant<int, 0>{}, tail_tag);
+        auto ktile = [&](int kt, auto tail_tag, auto first_tag) {
+            kstep(kt, std::integral_constant<int, 0>{}, tail_tag, first_tag);
             if constexpr (kKSteps > 2) {
-                kstep(kt, std::integral_constant<int, 1>{}, tail_tag);
-                kstep(kt, std::integral_constant<int, 2>{}, tail_tag);
+                kstep(kt, std::integral_constant<int, 1>{}, tail_tag, no{});
+                kstep(kt, std::integral_constant<int, 2>{}, tail_tag, no{});
             }
             __builtin_amdgcn_sched_barrier(0); // keep this k-step's MFMAs above the waits
             MOE_WAIT_LGKM0();                  // my reads of tile kt are complete
@@ -780,20 +821,26 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             lds_barrier();                     // ... and everyone's; the units of tile kt are free
             issue_position(kt, u, std::integral_constant<int, 0>{}, tail_tag);
             read_frags(wrap(u + 2), 0, 0, act); // past the last K tile: the next output tile's, read again there
-            mfma_all((kKSteps - 1) & 1, act);
+            mfma_all((kKSteps - 1) & 1, act, no{});
             if constexpr (kExt)
                 mfma_x((kKSteps - 1) & 1, std::integral_constant<int, kKSteps - 1>{}, kt + 1, half_tag{});
             interleave_under_mfma<kMfma, kReads, loads_at(0)>();
             u = wrap(u + 2);
         };
         // the last kDepth + kAhead K tiles look past the end of this tile's reduction
-        uint64_t slot_v = 0; // (sequence number 0: never a published one)
+        uint32_t after_lo = 0, after_hi = 0; // the tile after `nxt` and its sequence number (0: never a published one)
+        auto keep_slot = [&](uint64_t v) {
+            after_lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+            after_hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+        };
         if constexpr (kExt) {
             // one loop and nothing else between its K tiles, see xa; the next tile is looked up below
             if constexpr (kGather)
                 gather_offsets(nxt_row);
-            for (int kt = 0; kt < KT; ++kt)
-                ktile(kt, tail_yes{});
+            int kt = 0;
+            do
+                ktile(kt, tail_yes{}, no{});
+            while (++kt < KT);
             // the (empty) loads behind the last K tile still write xa: they must have done so before
             // the compiler, for which these registers are free from here on, puts anything else there
             {
@@ -801,30 +848,36 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                 asm volatile("s_waitcnt vmcnt(0)" : "+v"(d0), "+v"(d1), "+v"(d2), "+v"(d3));
             }
         } else {
-            const int k_split = KT - (kDepth + kAhead);
-            if (k_split > 0)
-                ktile(0, tail_no{});
-            else
-                ktile(0, tail_yes{});
-            // The tile after `nxt`: thread 0 stored it before it reached the barrier of K tile 0.  The
-            // load is left in flight and looked at after the K loop.
-            slot_v = read_slot();
+            using yes = std::integral_constant<bool, true>;
+            // (K tiles 0 and 1 in the form for the tail, which does for all: no branch, so that there is one place where
+            // the accumulators come from and the compiler keeps count of the loads)
+            ktile(0, tail_yes{}, yes{});
+            // The tile after `nxt`: thread 0 stored it before it reached the barrier of K tile 0.  The load is looked at
+            // behind K tile 1, whose own wait covers it (behind the K loop the compiler would wait for everything in
+            // flight, the next tile's operands included).
+            const uint64_t slot_v = read_slot();
             if constexpr (kGather)
                 gather_offsets(nxt_row); // looked up before K tile 0, long landed; needed from k_split on
-            for (int kt = 1; kt < k_split; ++kt)
-                ktile(kt, tail_no{});
-            for (int kt = (k_split > 1 ? k_split : 1); kt < KT; ++kt)
-                ktile(kt, tail_yes{});
+            // (A reduction of a single K tile multiplies zeros here: nothing is chained behind it, so loads past its end
+            // have no bytes.)
+            ktile(1, tail_yes{}, no{});
+            keep_slot(slot_v);
+            const int k_split = KT - (kDepth + kAhead);
+            for (int kt = 2; kt < k_split; ++kt)
+                ktile(kt, tail_no{}, no{});
+            for (int kt = (k_split > 2 ? k_split : 2); kt < KT; ++kt)
+                ktile(kt, tail_yes{}, no{});
         }
         // (if the store had not landed when the load ran, the sequence number is an older one)
-        while ((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(slot_v >> 32)) != seq)
-            slot_v = read_slot();
-        after_next = (int)__builtin_amdgcn_readfirstlane((uint32_t)slot_v);
-        // Thread 0 draws the tile that will follow `after_next` now, so that the counter's round trip
-        // runs under the epilogue; the tile is published after it.
-        drawn = -1;
-        if (tid == 0 && after_next >= 0)
-            drawn = with_ready_bit(fetch_tile());
+        while (after_hi != seq)
+            keep_slot(read_slot());
+        after_next = (int)after_lo;
+        te_after = read_entry(after_next); // (lands under the epilogue)
+        // Thread 0 draws the tile that will follow `after_next`: the counter's round trip runs under the epilogue.
+        const bool drawing = tid == 0 && after_next >= 0;
+        int ticket = 0;
+        if (drawing)
+            ticket = take_ticket();
 
         // ---- epilogue.  Block (i, j), register r of lane l:
         //      output row    m = i*32 + l%32               (within the wavefront's rows)
@@ -832,104 +885,126 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         // (acc_read is opaque to the compiler's hazard handling: the matrix pipe's last result may be
         // read 18 wait states after its instruction at the earliest)
         asm volatile("s_nop 15\n\ts_nop 3");
-        int m_lane = lane % 32, n_lane = (lane / 32) * 4;
-        // opaque to the optimiser: otherwise every column offset derived from them is kept in a
-        // register of its own across the whole persistent loop
-        asm volatile("" : "+v"(m_lane), "+v"(n_lane));
         constexpr int kOutBlkN = kSwiglu ? Cfg::kBlkN / 2 : Cfg::kBlkN;
-        // where row m of the result goes: row m of C, or (kScatter) its token's row of the fp32 sums
-        struct RowDst {
-            uint16_t *crow;
-            float *sums;
-            float w;
-        };
-        auto row_dst = [&](int64_t m) {
-            RowDst d = {nullptr, nullptr, 0.0f};
-            if constexpr (kScatter) {
-                const int32_t r = gather_rows[m];
-                d.w = scatter_w[r];
-                d.sums = reinterpret_cast<float *>(C) + (int64_t)(r / gather_div) * Ndim;
-            } else {
-                d.crow = C + m * Ndim;
-            }
-            return d;
-        };
-        auto put4 = [&](const RowDst &d, int col, const float (&v)[4]) {
-            if constexpr (kScatter) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    unsafeAtomicAdd(d.sums + col + t, d.w * v[t]);
-            } else if constexpr (kDep == 1 && MOE_DEP_STORE_THROUGH == 1) {
-                // device-scope store: written through this XCD's L2, which the other XCDs do not snoop
-                const uint64_t o = (uint64_t)pack_bf16x2(v[0], v[1]) | ((uint64_t)pack_bf16x2(v[2], v[3]) << 32);
-                __hip_atomic_store(reinterpret_cast<uint64_t *>(d.crow + col), o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                u32x2 o;
-                o[0] = pack_bf16x2(v[0], v[1]);
-                o[1] = pack_bf16x2(v[2], v[3]);
-                *reinterpret_cast<u32x2 *>(d.crow + col) = o;
-            }
-        };
-        // one 32-row block row of accumulators -> row m of the result
-        auto store_row = [&](int64_t m, const auto &blk, auto in_acc_regs) {
+        const int n_wave = cur.n0 + wn * (kOutBlkN * 32); // first column of this wavefront
+        // value r of column block j of a block row
+        auto value = [&](const auto &blk, int j, int r, auto in_acc_regs) {
             constexpr bool kAccRegs = decltype(in_acc_regs)::value;
-            if (m >= cur.m_end)
-                return;
-            const RowDst dst = row_dst(m);
-#pragma unroll
-            for (int j = 0; j < kOutBlkN; ++j) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = cur.n0 + wn * (kOutBlkN * 32) + j * 32 + q * 8 + n_lane;
-                    if (col >= Ndim)
-                        continue;
-                    float v[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const int r = q * 4 + t;
-                        if constexpr (kSwiglu)
-                            v[t] = kAccRegs ? silu_mul(acc_read(blk[j][r]), acc_read(blk[j + kOutBlkN][r]))
-                                            : silu_mul(blk[j][r], blk[j + kOutBlkN][r]);
-                        else
-                            v[t] = kAccRegs ? acc_read(blk[j][r]) : blk[j][r];
-                    }
-                    put4(dst, col, v);
-                }
-                // one block at a time: left alone, the scheduler first copies the whole tile out of the
-                // accumulation registers and needs some two hundred registers to hold it
-                __builtin_amdgcn_sched_barrier(0);
+            constexpr int kUp = !kAccRegs && kHalf ? kOutBlkN / 2 : kOutBlkN; // the up block of gate block j is j + kUp
+            auto get = [&](float a) { return kAccRegs ? acc_read(a) : a; };
+            if constexpr (kSwiglu) {
+                const float g = get(blk[j][r]);
+                return silu_mul(g, get(blk[j + kUp][r]));
+            } else {
+                return get(blk[j][r]);
             }
         };
+        if constexpr (kScatter) {
+            int m_lane = lane % 32, n_lane = (lane / 32) * 4;
+            // opaque to the optimiser: otherwise every column offset derived from them is kept in a
+            // register of its own across the whole persistent loop
+            asm volatile("" : "+v"(m_lane), "+v"(n_lane));
+            // row m of the result is added to its token's row of the fp32 sums; `first`, `step`: column blocks, as below
+            auto add_row = [&](int64_t m, const auto &blk, auto in_acc_regs, int first, int step, int n_blocks) {
+                if (m >= cur.m_end)
+                    return;
+                const int32_t r = gather_rows[m];
+                const float w = scatter_w[r];
+                float *const sums = reinterpret_cast<float *>(C) + (int64_t)(r / gather_div) * Ndim;
 #pragma unroll
-        for (int i = 0; i < kAct; ++i)
-            store_row((int64_t)cur.m0 + wm * Cfg::kWaveM + i * 32 + m_lane, acc[i], std::true_type{});
-        if constexpr (kExt) {
-            // the hand-written instructions are opaque to the compiler's hazard handling: a result of
-            // the matrix pipe may be read by the vector ALU 18 wait states after the instruction at
-            // the earliest; the last one was issued before the block rows above were stored
-            asm volatile("s_nop 15\n\ts_nop 3" : "+v"(accx[0]), "+v"(accx[1]), "+v"(accx[Cfg::kBlkN - 2]), "+v"(accx[Cfg::kBlkN - 1]));
-            if constexpr (!kHalf) {
-                store_row((int64_t)cur.m0 + BM + wm * 32 + m_lane, accx, std::false_type{});
-            } else {
-                // accx[jj] is column block wm + 2 jj of this wavefront column
-                const int64_t m = (int64_t)cur.m0 + BM + m_lane;
-                if (m < cur.m_end) {
-                    const RowDst dst = row_dst(m);
+                for (int j = 0; j < kOutBlkN; ++j) {
+                    if (j >= n_blocks)
+                        break;
 #pragma unroll
-                    for (int jo = 0; jo < (kSwiglu ? 1 : Cfg::kBlkN / 2); ++jo) {
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = n_wave + (first + j * step) * 32 + q * 8 + n_lane;
+                        if (col >= Ndim)
+                            continue;
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int col = cur.n0 + wn * (kOutBlkN * 32) + (wm + 2 * jo) * 32 + q * 8 + n_lane;
-                            if (col >= Ndim)
-                                continue;
-                            float v[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                v[t] = kSwiglu ? silu_mul(accx[0][q * 4 + t], accx[1][q * 4 + t]) : accx[jo][q * 4 + t];
-                            put4(dst, col, v);
-                        }
+                        for (int t = 0; t < 4; ++t)
+                            unsafeAtomicAdd(sums + col + t, w * value(blk, j, q * 4 + t, in_acc_regs));
                     }
+                    __builtin_amdgcn_sched_barrier(0); // one block at a time, see below
                 }
+            };
+#pragma unroll
+            for (int i = 0; i < kAct; ++i)
+                add_row((int64_t)cur.m0 + wm * Cfg::kWaveM + i * 32 + m_lane, acc[i], std::true_type{}, 0, 1, kOutBlkN);
+            if constexpr (kExt) {
+                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(accx[0]), "+v"(accx[1]), "+v"(accx[Cfg::kBlkN - 2]), "+v"(accx[Cfg::kBlkN - 1]));
+                if constexpr (kHalf) // accx[jj] is column block wm + 2 jj of this wavefront column
+                    add_row((int64_t)cur.m0 + BM + m_lane, accx, std::false_type{}, wm, 2, kOutBlkN / 2);
+                else
+                    add_row((int64_t)cur.m0 + BM + wm * 32 + m_lane, accx, std::false_type{}, 0, 1, kOutBlkN);
+            }
+        } else {
+            // A 32 x 32 block as two 16-byte stores of sixteen rows by 64 contiguous bytes each.  The accumulators give a
+            // lane four columns; lanes 32 apart trade halves (eight columns), then groups of sixteen lanes trade rows, so
+            // that lane l of store h holds row 16 h + l%16, columns 16 (l/16 % 2) + 8 (l/32) ...  + 8.  Rows past the
+            // segment and column blocks past Ndim lie past the byte counts: no branch, so that the number of stores is
+            // known and a wait for anything older does not become a wait for them.
+            // (8-byte stores to 32 rows each, a branch and 64-bit addresses for every one: 128 x 128 of a wavefront cost
+            // it some 7000 cycles.)
+            uint32_t lane_o = (uint32_t)lane;
+            asm volatile("" : "+v"(lane_o)); // (see lane_setup)
+            const int row_bytes = Ndim * 2;
+            const int voff = (int)(lane_o % 16) * row_bytes + (int)((lane_o / 16 % 2) * 16 + (lane_o / 32) * 8) * 2;
+            const int rows_left = cur.m_end - cur.m0;
+            const int tile_rows = rows_left < BM + Cfg::kExtra ? rows_left : BM + Cfg::kExtra;
+            uint16_t *const c_tile = C + (int64_t)cur.m0 * Ndim + n_wave;
+            const uint32_t c_bytes = (uint32_t)tile_rows * (uint32_t)row_bytes - (uint32_t)n_wave * 2u;
+            const int blocks_left = (Ndim - n_wave) / 32; // (Ndim is a multiple of 64)
+            constexpr int kAux = kDep == 1 && MOE_DEP_STORE_THROUGH == 1 ? 16 : 0; // 16: device scope, written through this XCD's L2, which the other XCDs do not snoop
+            // block row at row `r0` of the tile: column blocks first, first + step, ... of the wavefront
+            auto store_row = [&](int r0, const auto &blk, auto in_acc_regs, int first, auto step_tag, auto n_tag) {
+                constexpr int kStep = decltype(step_tag)::value, kN = decltype(n_tag)::value;
+                const int v0 = voff + r0 * row_bytes + first * 64, v1 = v0 + 16 * row_bytes;
+#pragma unroll
+                for (int j = 0; j < kN; ++j) {
+                    uint32_t p[8]; // [quarter][pair of columns]
+#pragma unroll
+                    for (int h = 0; h < 8; ++h) {
+                        const float lo = value(blk, j, 2 * h, in_acc_regs);
+                        p[h] = pack_bf16x2(lo, value(blk, j, 2 * h + 1, in_acc_regs));
+                    }
+                    auto swap32 = [&](uint32_t &x, uint32_t &y) {
+                        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+                        x = r[0], y = r[1];
+                    };
+                    auto swap16 = [&](uint32_t &x, uint32_t &y) {
+                        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+                        x = r[0], y = r[1];
+                    };
+                    swap32(p[0], p[2]), swap32(p[1], p[3]), swap32(p[4], p[6]), swap32(p[5], p[7]);
+                    u32x4 lo = {p[0], p[1], p[2], p[3]}, hi = {p[4], p[5], p[6], p[7]};
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        uint32_t x = lo[h], y = hi[h];
+                        swap16(x, y);
+                        lo[h] = x, hi[h] = y;
+                    }
+                    const auto rs = __builtin_amdgcn_make_buffer_rsrc(c_tile, 0, first + j * kStep < blocks_left ? c_bytes : 0u, 0x00020000);
+                    __builtin_amdgcn_raw_buffer_store_b128(lo, rs, v0 + j * kStep * 64, 0, kAux);
+                    __builtin_amdgcn_raw_buffer_store_b128(hi, rs, v1 + j * kStep * 64, 0, kAux);
+                    // one block at a time: left alone, the scheduler first copies the whole tile out of the
+                    // accumulation registers and needs some two hundred registers to hold it
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            using one = std::integral_constant<int, 1>;
+            using all = std::integral_constant<int, kOutBlkN>;
+#pragma unroll
+            for (int i = 0; i < kAct; ++i)
+                store_row(wm * Cfg::kWaveM + i * 32, acc[i], std::true_type{}, 0, one{}, all{});
+            if constexpr (kExt) {
+                // the hand-written instructions are opaque to the compiler's hazard handling: a result of
+                // the matrix pipe may be read by the vector ALU 18 wait states after the instruction at
+                // the earliest; the last one was issued before the block rows above were stored
+                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(accx[0]), "+v"(accx[1]), "+v"(accx[Cfg::kBlkN - 2]), "+v"(accx[Cfg::kBlkN - 1]));
+                if constexpr (kHalf) // accx[jj] is column block wm + 2 jj of this wavefront column
+                    store_row(BM, accx, std::false_type{}, wm, std::integral_constant<int, 2>{}, std::integral_constant<int, kOutBlkN / 2>{});
+                else
+                    store_row(BM + wm * 32, accx, std::false_type{}, 0, one{}, all{});
             }
         }
         if constexpr (kDep == 1 && MOE_DEP_STORE_THROUGH != 0) {
@@ -942,6 +1017,12 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             // (wait for the stores, write the L2's dirty lines back) before the counter is bumped.
             __hip_atomic_fetch_add(g.ready + cur.m0, lane == 0 ? 1 : 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
+        // (for every lane, so that this is where the compiler waits for the ticket, and for nothing younger: were it looked at
+        // by the drawing thread only, its register would count as in flight at the next tile's start)
+        asm volatile("" : "+v"(ticket));
+        drawn = -1;
+        if (drawing)
+            drawn = with_ready_bit(tile_of_ticket(ticket));
     };
 
     bool primed = false; // K tile 0 of `cur` is in LDS already
@@ -949,11 +1030,11 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         lane_setup();
         // the next tile's first K tiles ride behind this one's last
         const bool chain = warm && nxt_t >= 0 && kind_of(nxt_t) == Cfg::kKind && (kDep != 2 || (nxt_t & kReadyBit));
-        nxt = operands_of(chain ? nxt_t : -1);
+        nxt = operands_of(chain ? nxt_t : -1, te_nxt);
         if constexpr (kGather)
             gather_lookup(nxt, nxt_row);
         if (!primed) {
-            cur = operands_of(cur_t);
+            cur = operands_of(cur_t, read_entry(cur_t));
             if constexpr (kDep == 2) {
                 // The rows were not complete when this tile was drawn: wait for them now.  Nothing of the
                 // workgroup is in flight here and LDS is idle, so the first thread polls and tells the
@@ -1046,6 +1127,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             publish(drawn);
         cur_t = nxt_t;
         nxt_t = after_next;
+        te_nxt = te_after;
         if (chain) {
             cur = nxt; // its first K tiles are in LDS or on their way
             if constexpr (kGather) {
@@ -1087,7 +1169,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             int t = 0;
 #pragma unroll 1
             for (int w = 0; w < 3; ++w) {
-                t = t >= 0 && (w == 0 || !one_at_a_time) ? with_ready_bit(fetch_tile()) : -1;
+                t = t >= 0 && (w == 0 || !one_at_a_time) ? with_ready_bit(tile_of_ticket(take_ticket())) : -1;
                 if (w < 2)
                     __hip_atomic_store(my_ticket + w, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 else
