@@ -12,10 +12,7 @@
 
 namespace moe {
 
-constexpr int kTokensPerBlock = 4; // one wavefront each
-#ifndef MOE_COMBINE_U
-#define MOE_COMBINE_U 4 // 16-byte chunks of a row a lane gathers at a time (per k), at most
-#endif
+constexpr int kTokensPerBlock = 4; // one wavefront each (combine of long rows: one token, all four)
 
 // Value of lane k (k wave-uniform) whatever lanes are active: the chunk loops below run a different
 // number of times per lane, and a cross-lane read that honours the execution mask (__shfl) returns 0
@@ -26,6 +23,11 @@ __device__ __forceinline__ float lane_value(float v, int k)
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int32_t)__float_as_uint(v), k));
 }
 
+// x has just been read by the router and often still lies in the 256 MB memory-side cache, so its loads are ordinary ones;
+// kStream (xp larger than that cache): non-temporal stores, which leave x there.  A smaller xp is stored so that it stays for
+// the GEMM.  8192 tokens, H 7168, K 8 (1.06 GB): non-temporal loads, ordinary stores 221 us, this 187 us (5.7 TB/s); H 2880,
+// K 4 (236 MB): non-temporal loads 43, ordinary loads 39, non-temporal stores 42 us.
+template <bool kStream>
 __global__ __launch_bounds__(kWave *kTokensPerBlock) void permute_rows(
     const u32x4 *__restrict__ x, int chunks, int64_t N, int K,
     const int32_t *__restrict__ slot_of_row, u32x4 *__restrict__ xp)
@@ -37,41 +39,46 @@ __global__ __launch_bounds__(kWave *kTokensPerBlock) void permute_rows(
     // lane k keeps slot k of this token
     int32_t my_slot = (lane < K) ? slot_of_row[n * K + lane] : 0;
     const u32x4 *src = x + n * chunks;
+    auto put = [](u32x4 v, u32x4 *to) {
+        if constexpr (kStream)
+            __builtin_nontemporal_store(v, to);
+        else
+            *to = v;
+    };
     int c = lane;
     for (; c + 3 * kWave < chunks; c += 4 * kWave) {
-        u32x4 v0 = __builtin_nontemporal_load(src + c);
-        u32x4 v1 = __builtin_nontemporal_load(src + c + kWave);
-        u32x4 v2 = __builtin_nontemporal_load(src + c + 2 * kWave);
-        u32x4 v3 = __builtin_nontemporal_load(src + c + 3 * kWave);
+        const u32x4 v0 = src[c], v1 = src[c + kWave], v2 = src[c + 2 * kWave], v3 = src[c + 3 * kWave];
         for (int k = 0; k < K; ++k) {
             u32x4 *dst = xp + (int64_t)lane_value(my_slot, k) * chunks + c;
-            dst[0] = v0;
-            dst[kWave] = v1;
-            dst[2 * kWave] = v2;
-            dst[3 * kWave] = v3;
+            put(v0, dst);
+            put(v1, dst + kWave);
+            put(v2, dst + 2 * kWave);
+            put(v3, dst + 3 * kWave);
         }
     }
     for (; c < chunks; c += kWave) {
-        u32x4 v = __builtin_nontemporal_load(src + c);
+        const u32x4 v = src[c];
         for (int k = 0; k < K; ++k)
-            xp[(int64_t)lane_value(my_slot, k) * chunks + c] = v;
+            put(v, xp + (int64_t)lane_value(my_slot, k) * chunks + c);
     }
 }
 
-template <bool kBf16>
+// kWaves wavefronts per token: the chunks of a row are dealt to them in turn, so that a workgroup reads whole rows at a time
+// (long rows; 16384 tokens, H 7168, K 8: one wavefront per token 406 us, four 380 us, 5.6 TB/s).  A lane keeps four gathers
+// in flight, of four chunks of a row or, where a row has fewer per lane, of several rows.
+template <bool kBf16, int kWaves>
 __global__ __launch_bounds__(kWave *kTokensPerBlock) void combine_rows(
     const u32x4 *__restrict__ y, int chunks, int64_t N, int K,
     const int32_t *__restrict__ slot_of_row, const float *__restrict__ topk_w,
     u32x4 *__restrict__ out)
 {
+    constexpr int kStep = kWaves * kWave; // chunks from one of a lane's to its next
     const int lane = threadIdx.x % kWave;
-    const int64_t n = (int64_t)blockIdx.x * kTokensPerBlock + threadIdx.x / kWave;
+    const int64_t n = (int64_t)blockIdx.x * (kTokensPerBlock / kWaves) + threadIdx.x / kStep;
     if (n >= N)
         return;
     int32_t my_slot = (lane < K) ? slot_of_row[n * K + lane] : 0;
     float my_w = (lane < K) ? topk_w[n * K + lane] : 0.0f;
-    // kU chunks of a row at a time, so that kU gathers per lane are in flight (a single one leaves
-    // the small workloads, with only a few thousand wavefronts, waiting on memory latency)
     auto rows_of = [&](auto u_tag, int c) {
         constexpr int kU = decltype(u_tag)::value;
         float acc[kU][8];
@@ -80,27 +87,42 @@ __global__ __launch_bounds__(kWave *kTokensPerBlock) void combine_rows(
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 acc[u][i] = 0.0f;
-        for (int k = 0; k < K; ++k) { // ascending k: the order of the sum is part of the contract
-            const float w = lane_value(my_w, k);
-            const u32x4 *src = y + (int64_t)lane_value(my_slot, k) * chunks + c;
-            u32x4 v[kU];
+        auto rows = [&](auto count_tag, int k0) { // ascending k: the order of the sum is part of the contract
+            constexpr int kRows = decltype(count_tag)::value;
+            u32x4 v[kRows][kU];
 #pragma unroll
-            for (int u = 0; u < kU; ++u)
-                v[u] = __builtin_nontemporal_load(&src[u * kWave]); // read once: no need to keep it cached
+            for (int k = 0; k < kRows; ++k) {
+                const u32x4 *src = y + (int64_t)lane_value(my_slot, k0 + k) * chunks + c;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (kBf16) {
+                for (int u = 0; u < kU; ++u)
+                    v[k][u] = __builtin_nontemporal_load(&src[u * kStep]); // read once: no need to keep it cached
+            }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc[u][2 * i] = fmaf(w, bf16_bits_to_f32(v[u][i] & 0xFFFFu), acc[u][2 * i]);
-                        acc[u][2 * i + 1] = fmaf(w, __uint_as_float(v[u][i] & 0xFFFF0000u), acc[u][2 * i + 1]);
+            for (int k = 0; k < kRows; ++k) {
+                const float w = lane_value(my_w, k0 + k);
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    if (kBf16) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            acc[u][2 * i] = fmaf(w, bf16_bits_to_f32(v[k][u][i] & 0xFFFFu), acc[u][2 * i]);
+                            acc[u][2 * i + 1] = fmaf(w, __uint_as_float(v[k][u][i] & 0xFFFF0000u), acc[u][2 * i + 1]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            acc[u][i] = fmaf(w, __uint_as_float(v[k][u][i]), acc[u][i]);
                     }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        acc[u][i] = fmaf(w, __uint_as_float(v[u][i]), acc[u][i]);
                 }
             }
+        };
+        constexpr int kRows = 4 / kU;
+        int k = 0;
+        for (; k + kRows <= K; k += kRows)
+            rows(std::integral_constant<int, kRows>{}, k);
+        if constexpr (kRows > 1) {
+            for (; k < K; ++k)
+                rows(std::integral_constant<int, 1>{}, k);
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -114,19 +136,15 @@ __global__ __launch_bounds__(kWave *kTokensPerBlock) void combine_rows(
                 for (int i = 0; i < 4; ++i)
                     o[i] = __float_as_uint(acc[u][i]);
             }
-            __builtin_nontemporal_store(o, &out[n * chunks + c + u * kWave]);
+            __builtin_nontemporal_store(o, &out[n * chunks + c + u * kStep]);
         }
     };
-    int c = lane;
-#if MOE_COMBINE_U == 8
-    for (; c + 7 * kWave < chunks; c += 8 * kWave)
-        rows_of(std::integral_constant<int, 8>{}, c);
-#endif
-    for (; c + 3 * kWave < chunks; c += 4 * kWave)
+    int c = threadIdx.x % kStep;
+    for (; c + 3 * kStep < chunks; c += 4 * kStep)
         rows_of(std::integral_constant<int, 4>{}, c);
-    for (; c + kWave < chunks; c += 2 * kWave)
+    for (; c + kStep < chunks; c += 2 * kStep)
         rows_of(std::integral_constant<int, 2>{}, c);
-    for (; c < chunks; c += kWave)
+    for (; c < chunks; c += kStep)
         rows_of(std::integral_constant<int, 1>{}, c);
 }
 
@@ -135,26 +153,36 @@ int launch_permute(const void *x, int64_t row_bytes, int64_t N, int K, const int
 {
     const int chunks = (int)(row_bytes / 16);
     const unsigned blocks = (unsigned)ceil_div(N, kTokensPerBlock);
-    hipLaunchKernelGGL(permute_rows, dim3(blocks), dim3(kWave * kTokensPerBlock), 0, st,
+    constexpr int64_t kMemoryCache = (int64_t)256 << 20;
+    auto kern = N * K * row_bytes > kMemoryCache ? permute_rows<true> : permute_rows<false>;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kTokensPerBlock), 0, st,
                        static_cast<const u32x4 *>(x), chunks, N, K, slot_of_row,
                        static_cast<u32x4 *>(xp));
     return check_launch("moe_permute");
 }
 
+// rows from this many 16-byte chunks on: a workgroup per token (one chunk per lane or more); at 256 - 512 chunks both forms
+// are within 3 % of each other
+constexpr int kLongRow = 256;
+
+template <bool kBf16>
+static void launch_combine_of(const void *y, int64_t N, int chunks, int K, const int32_t *slot_of_row, const float *topk_w,
+                              void *out, hipStream_t st)
+{
+    const bool long_row = chunks >= kLongRow && N <= 0xFFFFFF; // (a grid holds fewer than 2^32 threads)
+    auto kern = long_row ? combine_rows<kBf16, 4> : combine_rows<kBf16, 1>;
+    const unsigned blocks = (unsigned)(long_row ? N : ceil_div(N, kTokensPerBlock));
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kTokensPerBlock), 0, st, static_cast<const u32x4 *>(y), chunks, N, K,
+                       slot_of_row, topk_w, static_cast<u32x4 *>(out));
+}
+
 int launch_combine(const void *y, int dtype, int64_t N, int64_t H, int K,
                    const int32_t *slot_of_row, const float *topk_w, void *out, hipStream_t st)
 {
-    const unsigned blocks = (unsigned)ceil_div(N, kTokensPerBlock);
-    const dim3 block(kWave * kTokensPerBlock);
-    if (dtype == MOE_BF16) {
-        hipLaunchKernelGGL(combine_rows<true>, dim3(blocks), block, 0, st,
-                           static_cast<const u32x4 *>(y), (int)(H * 2 / 16), N, K, slot_of_row,
-                           topk_w, static_cast<u32x4 *>(out));
-    } else {
-        hipLaunchKernelGGL(combine_rows<false>, dim3(blocks), block, 0, st,
-                           static_cast<const u32x4 *>(y), (int)(H * 4 / 16), N, K, slot_of_row,
-                           topk_w, static_cast<u32x4 *>(out));
-    }
+    if (dtype == MOE_BF16)
+        launch_combine_of<true>(y, N, (int)(H * 2 / 16), K, slot_of_row, topk_w, out, st);
+    else
+        launch_combine_of<false>(y, N, (int)(H * 4 / 16), K, slot_of_row, topk_w, out, st);
     return check_launch("moe_combine");
 }
 
