@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe_hub.so")
-SOURCES = ["api.hip", "route.hip", "layout.hip", "rowmove.hip", "ffn.hip", "ffn_f32.hip", "ffn_thin.hip"]
+SOURCES = ["ffn_both.hip", "ffn_both_narrow.hip", "ffn_down_scatter.hip", "ffn_gate_up.hip", "ffn_gate_up_gather.hip", "ffn_down.hip",
+           "ffn_down_narrow.hip", "api.hip", "route.hip", "layout.hip", "rowmove.hip", "ffn.hip", "ffn_f32.hip", "ffn_thin.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -72,7 +73,7 @@ def build(verbose: bool = True, defines=(), out: str = LIB) -> str:
     check_compiler()
     obj_dir = OBJ if out == LIB else OBJ + "_" + os.path.splitext(os.path.basename(out))[0]
     os.makedirs(obj_dir, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex: # (longest first)
         objs = list(ex.map(lambda src: _compile(src, defines, obj_dir), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out, *objs]
     subprocess.run(cmd, check=True)

@@ -21,8 +21,8 @@
 #include <atomic>
 
 #include "common.h"
+#include "ffn_gemm.h"
 #include "ffn_thin.h"
-#include "grouped_gemm.h"
 
 namespace moe {
 
@@ -30,19 +30,17 @@ namespace moe {
 // tile table
 // ------------------------------------------------------------------------
 constexpr int kSchedThreads = 256;
-// relative cost of a tile of a one-row-tile expert and of a full tile, for sharing out the workgroup slots
-constexpr int kLightCost = 3, kHeavyCost = 7;
+// relative cost of a light, a middle and a full tile, for sharing out the workgroup slots
+constexpr int kLightCost = 3, kMidCost = 6, kHeavyCost = 7;
 #ifndef MOE_ORDER_LONG_FIRST
 #define MOE_ORDER_LONG_FIRST 1
 #endif
 // experts with at most this many rows go through the shallow tile geometry
 constexpr int kLightRows = 64;
 
-// Experts come in two classes: "light" ones with at most `light_rows` rows, whose one row tile
-// streams its weights from memory once and mostly waits for them (the GEMM has a shallow, deeply
-// prefetching tile geometry for those), and the rest.  Each class forms a stream of tiles (order:
-// expert, then column tile, then row tile); the table holds stream 0 (the rest), then stream 1
-// (light).  The GEMM's persistent workgroups draw from both.
+// Experts come in four classes by their rows (geometries in ffn_gemm.h): several row tiles, one, middle, light.  The first two
+// form stream 0 of the table, the others stream 1; inside a class the order is expert, column tile, row tile.  The GEMM's
+// persistent workgroups draw from both streams.
 // Row tiles of an expert with `rows` rows: a remainder of at most `extra` rows rides with the last
 // full tile instead of forming a tile of its own.
 __device__ __forceinline__ int row_tiles(int32_t rows, int BM, int extra)
@@ -63,6 +61,7 @@ __device__ __forceinline__ int32_t clamped_rows(const int32_t *seg_offsets, int 
 // One launch builds the tables of both GEMMs: blockIdx.y picks the set of arguments.
 struct TableArgs {
     int BM, extra; // rows of a tile; rows beyond them that the last full one may take
+    int mid_rows;  // experts with more than light_rows and up to so many rows are one tile of the middle geometry
     int n_tiles, max_tiles, out_cols;
     TileTableHeader *hdr;
     TileEntry *table;
@@ -79,65 +78,75 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
     const int n_tiles = args.n_tiles, max_tiles = args.max_tiles, BM = args.BM, extra = args.extra;
     TileTableHeader *__restrict__ hdr = args.hdr;
     TileEntry *__restrict__ table = args.table;
-    __shared__ int32_t start[2][MOE_MAX_EXPERTS + 1]; // first tile of each expert in the heavy [0] / light [1] stream
-    __shared__ int32_t wave_tot[2][kSchedThreads / kWave];
+    // first tile of each expert among those of its class: several row tiles [0], one of them [1], middle [2], light [3]
+    __shared__ int32_t start[4][MOE_MAX_EXPERTS + 1];
+    __shared__ int32_t wave_tot[4][kSchedThreads / kWave];
+    const int mid_rows = args.mid_rows;
+    auto class_of = [&](int32_t rows) {
+        return rows <= light_rows ? 3 : rows <= mid_rows ? 2 : row_tiles(rows, BM, extra) == 1 ? 1 : 0;
+    };
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     // exclusive scans of tiles per expert; a thread owns a contiguous run of experts
     const int per = (E_local + kSchedThreads - 1) / kSchedThreads;
     const int e_lo = tid * per;
-    int32_t mine[2] = {0, 0};
+    int32_t mine[4] = {0, 0, 0, 0};
     for (int j = 0; j < per; ++j) {
         const int e = e_lo + j;
         if (e < E_local) {
             int64_t lo;
             const int32_t rows = clamped_rows(seg_offsets, e, M, lo);
-            mine[rows <= light_rows ? 1 : 0] += row_tiles(rows, BM, extra) * n_tiles;
+            mine[class_of(rows)] += row_tiles(rows, BM, extra) * n_tiles;
         }
     }
-    int32_t inc[2] = {mine[0], mine[1]};
+    int32_t inc[4] = {mine[0], mine[1], mine[2], mine[3]};
     for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t t0 = __shfl_up(inc[0], d), t1 = __shfl_up(inc[1], d);
-        if (lane >= d) {
-            inc[0] += t0;
-            inc[1] += t1;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int32_t t = __shfl_up(inc[c], d);
+            if (lane >= d)
+                inc[c] += t;
         }
     }
     if (lane == kWave - 1) {
-        wave_tot[0][wave] = inc[0];
-        wave_tot[1][wave] = inc[1];
+        for (int c = 0; c < 4; ++c)
+            wave_tot[c][wave] = inc[c];
     }
     __syncthreads();
-    int32_t run[2] = {inc[0] - mine[0], inc[1] - mine[1]};
+    int32_t run[4] = {inc[0] - mine[0], inc[1] - mine[1], inc[2] - mine[2], inc[3] - mine[3]};
     for (int w = 0; w < wave; ++w) {
-        run[0] += wave_tot[0][w];
-        run[1] += wave_tot[1][w];
+        for (int c = 0; c < 4; ++c)
+            run[c] += wave_tot[c][w];
     }
     for (int j = 0; j < per; ++j) {
         const int e = e_lo + j;
         if (e < E_local) {
             int64_t lo;
             const int32_t rows = clamped_rows(seg_offsets, e, M, lo);
-            start[0][e] = run[0];
-            start[1][e] = run[1];
-            run[rows <= light_rows ? 1 : 0] += row_tiles(rows, BM, extra) * n_tiles;
+            for (int c = 0; c < 4; ++c)
+                start[c][e] = run[c];
+            run[class_of(rows)] += row_tiles(rows, BM, extra) * n_tiles;
         }
     }
     if (tid == kSchedThreads - 1) { // the last thread's running sums are the totals
-        start[0][E_local] = run[0];
-        start[1][E_local] = run[1];
+        for (int c = 0; c < 4; ++c)
+            start[c][E_local] = run[c];
     }
     __syncthreads();
-    int32_t len[2] = {start[0][E_local], start[1][E_local]};
+    int32_t several = start[0][E_local], mid = start[2][E_local];
+    int32_t len[2] = {several + start[1][E_local], mid + start[3][E_local]};
     if (len[0] + len[1] > max_tiles) { // cannot happen for monotone offsets within [0, M]
         len[0] = len[0] < max_tiles ? len[0] : max_tiles;
         len[1] = max_tiles - len[0];
+        several = several < len[0] ? several : len[0];
+        mid = mid < len[1] ? mid : len[1];
     }
     if (blockIdx.x == 0 && tid == 0) {
         hdr->len[0] = len[0];
         hdr->len[1] = len[1];
-        // share of the workgroup slots that take the light stream first: the light tiles' share of
-        // the work, a light tile counted as kLightCost/kHeavyCost of a heavy one
-        const int64_t wl = (int64_t)len[1] * kLightCost, wh = (int64_t)len[0] * kHeavyCost;
+        hdr->several = several;
+        hdr->mid = mid;
+        // share of the workgroup slots that take stream 1 first: its tiles' share of the work
+        const int64_t wl = (int64_t)(len[1] - mid) * kLightCost + (int64_t)mid * kMidCost, wh = (int64_t)len[0] * kHeavyCost;
         hdr->light_slots = wl + wh > 0 ? (int32_t)((32 * wl + (wl + wh) / 2) / (wl + wh)) : 0;
         hdr->done = 0;
         hdr->error = 0;
@@ -152,8 +161,8 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
     }
     const int32_t total = len[0] + len[1];
     for (int L = blockIdx.x * kSchedThreads + tid; L < total; L += gridDim.x * kSchedThreads) {
-        const int c = L < len[0] ? 0 : 1;
-        const int32_t pos = L - (c ? len[0] : 0); // position in the stream
+        const int c = L < several ? 0 : L < len[0] ? 1 : L < len[0] + mid ? 2 : 3;
+        const int32_t pos = L - (c == 0 ? 0 : c == 1 ? several : c == 2 ? len[0] : len[0] + mid); // place among the tiles of its class
         int lo_e = 0, hi_e = E_local;             // last e with start[c][e] <= pos: the expert that owns it
         while (hi_e - lo_e > 1) {
             const int mid = (lo_e + hi_e) >> 1;
@@ -212,35 +221,12 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
 // ------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------
-// Geometries.  Big: 256x256x64 tile, ring of 5 units (all 160 KiB of LDS); per window the 8 B loads
-// of a wavefront go out under the first two k-steps after the barrier, the 8 A loads under the
-// other two.  An expert's last full tile also takes a remainder of up to 64 rows ("tall" tile).  Shallow: 64x256x64 tile for experts with few rows, four (A, B) unit pairs, so that
-// three K tiles of weights are in flight while one is multiplied. 
-// MOE_WEIGHTS_AHEAD: the operand that uses the ring's spare unit to run one K tile further ahead is the
-// weights (1) or the activations (0).
-#ifndef MOE_WEIGHTS_AHEAD
-#define MOE_WEIGHTS_AHEAD 1
-#endif
-template <bool kSwiglu>
-using BigTile = GemmCfg<256, 256, 2, 2, kSwiglu, 64, 5, (MOE_WEIGHTS_AHEAD ? 0x4400 : 0x0044),
-                        (MOE_WEIGHTS_AHEAD ? 0x0044 : 0x4400), 0, 64, (MOE_WEIGHTS_AHEAD != 0)>;
-#ifndef MOE_SHALLOW_UNITS
-#define MOE_SHALLOW_UNITS 8
-#endif
-template <bool kSwiglu> using ShallowTile = GemmCfg<64, 256, 1, 4, kSwiglu, 64, MOE_SHALLOW_UNITS, 0x1010, 0x2222, 1>;
-
-// The down projection with 128-column tiles, for launches with fewer tiles than compute units (few
-// tokens): every tile of such a launch streams its whole weight panel alone and the launch lasts as
-// long as one tile, so half as wide a panel on twice as many compute units halves it.  Where reductions
-// are not turned (turn_of below) every output element is the same sum in the same order as with the
-// 256-column tiles, so y has the same bits; a turned one starts at a K tile that depends on the tile's width.
-template <bool kSwiglu> using NarrowBig = GemmCfg<256, 128, 2, 2, kSwiglu, 64, 6, 0x2222, 0x1111, 0, 64>;
-template <bool kSwiglu> using NarrowShallow = GemmCfg<64, 128, 1, 4, kSwiglu, 64, 8, 0x1010, 0x1111, 1>;
 // upper bound of the down projection's 256-column tiles up to which the narrow form is used
 #ifndef MOE_NARROW_TILE_BOUND
 #define MOE_NARROW_TILE_BOUND 256
 #endif
 constexpr int kNarrowTileBound = MOE_NARROW_TILE_BOUND;
+
 
 struct FfnPlan {
     bool thin1, thin2; // GEMM1 / GEMM2 by ffn_thin.hip: that table holds row tiles only
@@ -361,36 +347,22 @@ static int compute_units()
     return n;
 }
 
-// workgroup slots of the device: compute units times the workgroups of this kernel a unit holds
-static int workgroup_slots(int per_cu)
+int workgroup_slots()
 {
-    const int cus = compute_units();
-    int g = cus * per_cu / kXcds * kXcds; // whole rounds over the XCDs
+    int g = compute_units() / kXcds * kXcds; // (LDS: one workgroup per compute unit)
     if (g > kMaxGemmWorkgroups)
         g = kMaxGemmWorkgroups / kXcds * kXcds;
     return g < kXcds ? kXcds : g;
 }
 
-// Raises the kernel's dynamic LDS limit once per device (idempotent, so a race only repeats it).
-template <class Kernel>
-static void allow_lds(Kernel kern, size_t lds_bytes, std::atomic<uint64_t> &raised)
+void allow_lds(const void *kern, size_t lds_bytes, std::atomic<uint64_t> &raised)
 {
     const int dev = current_device();
     if (dev < 0 || !(raised.load(std::memory_order_relaxed) >> dev & 1)) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds_bytes);
+        (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (dev >= 0)
             raised.fetch_or(uint64_t(1) << dev, std::memory_order_relaxed);
     }
-}
-
-template <class Main, class Light>
-static size_t lds_bytes_of()
-{
-    size_t b = Main::kLdsBytes;
-    if constexpr (!std::is_void<Light>::value)
-        b = b > Light::kLdsBytes ? b : Light::kLdsBytes;
-    return b;
 }
 
 // Weight rows a multiple of 4 KiB apart: workgroups that all start at column 0 ask the same few memory channels, and
@@ -424,33 +396,6 @@ static GemmArgs gemm_args(const uint16_t *A, int64_t M, int E_local, int Kdim, i
     g.gather_div = 1;
     g.k_turn = turn_of(M, E_local, Kdim, ceil_div(Ndim, out_cols));
     return g;
-}
-
-template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, bool kTurn>
-static void launch_gemm_form(const GemmArgs &g, hipStream_t st)
-{
-    auto kern = grouped_gemm_bf16<Main, Light, kSwiglu, kGather, kScatter, kTurn>;
-    const size_t lds_bytes = lds_bytes_of<Main, Light>();
-    static std::atomic<uint64_t> raised{0};
-    allow_lds(kern, lds_bytes, raised);
-    // persistent grid: the workgroups draw their tiles from the table's counters
-    const int grid = workgroup_slots(Main::kLdsBytes <= 80 * 1024 ? 2 : 1);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Main::kThreads), lds_bytes, st, g);
-}
-
-template <class Main, class Light, bool kSwiglu, bool kGather = false, bool kScatter = false>
-static void launch_gemm(const uint16_t *A, int64_t M, int E_local, int Kdim, int Ndim, const uint16_t *B0,
-                        const uint16_t *B1, uint16_t *C, TileTableHeader *hdr,
-                        const TileEntry *table, hipStream_t st,
-                        const int32_t *gather_rows = nullptr, int gather_div = 1, uint32_t gather_bytes = 0,
-                        const float *scatter_w = nullptr)
-{
-    GemmArgs g = gemm_args(A, M, E_local, Kdim, Ndim, B0, B1, C, hdr, table, Main::kOutCols);
-    g.gather_rows = gather_rows, g.gather_div = gather_div, g.gather_bytes = gather_bytes, g.scatter_w = scatter_w;
-    if (g.k_turn)
-        launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, true>(g, st);
-    else
-        launch_gemm_form<Main, Light, kSwiglu, kGather, kScatter, false>(g, st);
 }
 
 int check_ffn_shape(int dtype, int64_t H, int64_t F)
@@ -499,8 +444,8 @@ int launch_ffn_schedule(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     const int max_both = k.max1 > k.max2 ? k.max1 : k.max2;
     hipLaunchKernelGGL(build_tile_table, dim3((unsigned)ceil_div(max_both, kSchedThreads), 2),
                        dim3(kSchedThreads), 0, st, seg_offsets, E_local, M, kLightRows,
-                       TableArgs{p.thin1 ? kThinRows : p.BM, p.thin1 ? 0 : BigTile<true>::kExtra, p.n_tiles1, k.max1, p.out_cols1, k.hdr1, k.tab1},
-                       TableArgs{p.thin2 ? kThinRows : p.BM, p.thin2 ? 0 : BigTile<false>::kExtra, p.n_tiles2, k.max2, p.out_cols2, k.hdr2, k.tab2},
+                       TableArgs{p.thin1 ? kThinRows : p.BM, p.thin1 ? 0 : BigTile<true>::kExtra, p.thin1 ? 0 : kMidRows, p.n_tiles1, k.max1, p.out_cols1, k.hdr1, k.tab1},
+                       TableArgs{p.thin2 ? kThinRows : p.BM, p.thin2 ? 0 : BigTile<false>::kExtra, p.thin2 ? 0 : kMidRows, p.n_tiles2, k.max2, p.out_cols2, k.hdr2, k.tab2},
                        k.ready);
     return check_launch("moe_ffn_schedule");
 }
@@ -519,13 +464,17 @@ int launch_ffn_gate_up(const void *xp, int dtype, int64_t M, int64_t H, int64_t 
     const FfnWorkspace k = carve(p, ws);
     const uint16_t *xpb = static_cast<const uint16_t *>(xp);
     const uint16_t *wg = static_cast<const uint16_t *>(W_gate), *wu = static_cast<const uint16_t *>(W_up);
-    if (p.thin1)
+    if (p.thin1) {
         launch_thin_gate_up(xpb, M, H, F, wg, wu, k.a, k.hdr1, k.tab1, p.max_m_tiles1, p.out_cols1, gather_rows, K, (uint32_t)(N * H * 2), st);
-    else if (gather_rows)
-        launch_gemm<BigTile<true>, ShallowTile<true>, true, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1,
-                                                                  st, gather_rows, K, (uint32_t)(N * H * 2));
-    else
-        launch_gemm<BigTile<true>, ShallowTile<true>, true>(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, st);
+        return check_launch("moe_ffn_gate_up");
+    }
+    GemmArgs g = gemm_args(xpb, M, E_local, (int)H, (int)F, wg, wu, k.a, k.hdr1, k.tab1, p.out_cols1);
+    if (gather_rows) {
+        g.gather_rows = gather_rows, g.gather_div = K, g.gather_bytes = (uint32_t)(N * H * 2);
+        launch_gate_up_gather(g, st);
+    } else {
+        launch_gate_up(g, st);
+    }
     return check_launch("moe_ffn_gate_up");
 }
 
@@ -540,52 +489,19 @@ int launch_ffn_down(int dtype, int64_t M, int64_t H, int64_t F, int E_local,
     const FfnWorkspace k = carve(p, ws);
     const uint16_t *wd = static_cast<const uint16_t *>(W_down);
     uint16_t *yb = static_cast<uint16_t *>(y);
-    if (p.thin2)
+    if (p.thin2) {
         launch_thin_down(k.a, M, H, F, wd, yb, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, nullptr, 1, nullptr, st);
-    else if (p.narrow2)
-        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, st);
+        return check_launch("moe_ffn_down");
+    }
+    const GemmArgs g = gemm_args(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, p.out_cols2);
+    if (p.narrow2)
+        launch_down_narrow(g, st);
     else
-        launch_gemm<BigTile<false>, ShallowTile<false>, false>(k.a, M, E_local, (int)F, (int)H, wd, nullptr, yb, k.hdr2, k.tab2, st);
+        launch_down(g, st);
     return check_launch("moe_ffn_down");
 }
 
 // Both GEMMs in one launch, the second consuming the first's rows tile by tile (after launch_ffn_schedule).
-template <class Main2, class Light2, bool kTurn1, bool kTurn2>
-static void launch_both_form(const GemmArgs &g1, const GemmArgs &g2, hipStream_t st)
-{
-    using Main1 = BigTile<true>;
-    using Light1 = ShallowTile<true>;
-    auto kern = grouped_ffn_bf16<Main1, Light1, Main2, Light2, kTurn1, kTurn2>;
-    size_t lds_bytes = lds_bytes_of<Main1, Light1>();
-    lds_bytes = lds_bytes > lds_bytes_of<Main2, Light2>() ? lds_bytes : lds_bytes_of<Main2, Light2>();
-    static std::atomic<uint64_t> raised{0};
-    allow_lds(kern, lds_bytes, raised);
-    hipLaunchKernelGGL(kern, dim3(workgroup_slots(1)), dim3(Main1::kThreads), lds_bytes, st, g1, g2);
-}
-
-template <class Main2, class Light2>
-static void launch_both(const FfnPlan &p, const FfnWorkspace &k, const void *xp, int64_t M, int64_t H, int64_t F, int E_local,
-                        const void *W_gate, const void *W_up, const void *W_down, void *y, int64_t wait_limit,
-                        hipStream_t st)
-{
-    GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
-                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, p.out_cols1);
-    GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, p.out_cols2);
-    g1.ready = g2.ready = k.ready;
-    g1.hdr_dep = g2.hdr_dep = k.hdr1;
-    g1.ready_per_launch = g2.ready_per_launch = BigTile<true>::kWaves * p.n_tiles1;
-    g1.wait_limit = g2.wait_limit = wait_limit > 0 ? wait_limit : kDefaultWaitLimit;
-    if (g1.k_turn && g2.k_turn)
-        launch_both_form<Main2, Light2, true, true>(g1, g2, st);
-    else if (g1.k_turn)
-        launch_both_form<Main2, Light2, true, false>(g1, g2, st);
-    else if (g2.k_turn)
-        launch_both_form<Main2, Light2, false, true>(g1, g2, st);
-    else
-        launch_both_form<Main2, Light2, false, false>(g1, g2, st);
-}
-
 int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int E_local, const void *W_gate,
                             const void *W_up, const void *W_down, void *y, void *ws, int64_t wait_limit,
                             hipStream_t st)
@@ -596,10 +512,18 @@ int launch_ffn_gate_up_down(const void *xp, int64_t M, int64_t H, int64_t F, int
         const int rc = launch_ffn_gate_up(xp, MOE_BF16, M, H, F, E_local, nullptr, W_gate, W_up, ws, st, nullptr, 1, 0);
         return rc != MOE_OK ? rc : launch_ffn_down(MOE_BF16, M, H, F, E_local, nullptr, W_down, y, ws, st);
     }
+    GemmArgs g1 = gemm_args(static_cast<const uint16_t *>(xp), M, E_local, (int)H, (int)F, static_cast<const uint16_t *>(W_gate),
+                            static_cast<const uint16_t *>(W_up), k.a, k.hdr1, k.tab1, p.out_cols1);
+    GemmArgs g2 = gemm_args(k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
+                            static_cast<uint16_t *>(y), k.hdr2, k.tab2, p.out_cols2);
+    g1.ready = g2.ready = k.ready;
+    g1.hdr_dep = g2.hdr_dep = k.hdr1;
+    g1.ready_per_launch = g2.ready_per_launch = BigTile<true>::kWaves * p.n_tiles1;
+    g1.wait_limit = g2.wait_limit = wait_limit > 0 ? wait_limit : kDefaultWaitLimit;
     if (p.narrow2)
-        launch_both<NarrowBig<false>, NarrowShallow<false>>(p, k, xp, M, H, F, E_local, W_gate, W_up, W_down, y, wait_limit, st);
+        launch_gate_up_and_down_narrow(g1, g2, st);
     else
-        launch_both<BigTile<false>, ShallowTile<false>>(p, k, xp, M, H, F, E_local, W_gate, W_up, W_down, y, wait_limit, st);
+        launch_gate_up_and_down(g1, g2, st);
     return check_launch("moe_ffn_gate_up_down");
 }
 
@@ -660,17 +584,18 @@ int launch_ffn_down_combine(int64_t N, int K, int64_t H, int64_t F, int E_local,
     const int64_t n16 = N * H / 4, n8 = N * H / 8;
     hipLaunchKernelGGL(fill_zero_16B, dim3((unsigned)ceil_div(n16, 256)), dim3(256), 0, st,
                        reinterpret_cast<u32x4 *>(sums), n16);
-    if (p.thin2)
-        launch_thin_down(k.a, M, H, F, static_cast<const uint16_t *>(W_down), sums, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, row_of_slot,
-                         K, topk_w, st);
-    else if (p.narrow2)
-        launch_gemm<NarrowBig<false>, NarrowShallow<false>, false, false, true>(
-            k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, st, row_of_slot, K, 0u, topk_w);
-    else
-        launch_gemm<BigTile<false>, ShallowTile<false>, false, false, true>(
-            k.a, M, E_local, (int)F, (int)H, static_cast<const uint16_t *>(W_down), nullptr,
-            reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2, st, row_of_slot, K, 0u, topk_w);
+    const uint16_t *wd = static_cast<const uint16_t *>(W_down);
+    if (p.thin2) {
+        launch_thin_down(k.a, M, H, F, wd, sums, k.hdr2, k.tab2, p.max_m_tiles2, p.out_cols2, row_of_slot, K, topk_w, st);
+    } else {
+        GemmArgs g = gemm_args(k.a, M, E_local, (int)F, (int)H, wd, nullptr, reinterpret_cast<uint16_t *>(sums), k.hdr2, k.tab2,
+                               p.out_cols2);
+        g.gather_rows = row_of_slot, g.gather_div = K, g.scatter_w = topk_w;
+        if (p.narrow2)
+            launch_down_scatter_narrow(g, st);
+        else
+            launch_down_scatter(g, st);
+    }
     hipLaunchKernelGGL(round_sums_bf16, dim3((unsigned)ceil_div(n8, 256)), dim3(256), 0, st,
                        reinterpret_cast<const f32x4 *>(sums), static_cast<u32x4 *>(out), n8);
     return check_launch("moe_ffn_down_combine");

@@ -1,0 +1,8 @@
+// Expert computation: down projection with 128-column tiles (grouped_gemm.h; geometries and launches in ffn_gemm.h).
+#include "ffn_gemm.h"
+
+namespace moe {
+
+void launch_down_narrow(const GemmArgs &g, hipStream_t st) { launch_gemm<NarrowSet, false, false, false>(g, st); }
+
+}  // namespace moe

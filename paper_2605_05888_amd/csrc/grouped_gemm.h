@@ -39,14 +39,14 @@
 // waited for on the spot, vector loads of the table and 8-byte stores: 65536 rows over 8 experts,
 // H 7168, F 2048, down projection 1645 -> 1522 us; 32768 rows over 64, H 2048, F 1408: 244 -> 225.)
 // The table has
-// two streams of tiles, served by two tile geometries inside the one kernel: 256x256 tiles, and
-// 64x256 tiles four K tiles deep for experts with at most 64 rows, which do little arithmetic
-// and live on how many bytes they keep in flight.  A 256-row tile can be "tall": the last full
+// two streams of tiles, served by several tile geometries inside the one kernel (ffn_gemm.h): 256x256
+// tiles, and tiles that do less arithmetic and live on how many bytes they keep in flight.  A 256-row tile can be "tall": the last full
 // tile of an expert also computes a remainder of up to 64 rows, against the B tiles it has in LDS
 // anyway, with the extra rows' operand and accumulators in vector registers (see GemmCfg).
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -70,11 +70,14 @@ constexpr int kXcds = 8;
 constexpr int kMaxGemmWorkgroups = 896; // workgroups of the persistent grid (ticket words of a table)
 
 // Head of a tile table.  The table holds two streams of tiles, one after the other: stream 0 the
-// tiles of experts with two row tiles or more (their weight tiles are shared by several
-// workgroups and the matrix cores bound them), stream 1 the tiles of experts with one row tile
-// (they stream their weights from memory once and mostly wait for them).
+// 256-row tiles, those of experts with several of them (their weight tiles are shared by several
+// workgroups and the matrix cores bound them) before those of experts with one, stream 1 the tiles of
+// experts with up to 160 rows (they stream their weights from memory once and mostly wait for them),
+// the middle geometry's before the shallow one's.
 struct TileTableHeader {
     int32_t len[2];         // tiles in each stream; stream s starts at entry (s ? len[0] : 0)
+    int32_t several;        // of stream 0, how many belong to experts of several row tiles (they come first)
+    int32_t mid;            // of stream 1, how many are of the middle geometry (they come first)
     int32_t light_slots;    // of the 32 workgroup slots an XCD has, how many take stream 1 first
     int32_t done;           // workgroups that have left the kernel (the last one resets the counters)
     int32_t magic;          // kTableMagic once build_tile_table has filled the table ...
@@ -85,7 +88,7 @@ struct TileTableHeader {
     // dependency-driven launches (both GEMMs in one kernel), kept in GEMM1's header:
     int32_t epoch;          // such launches completed over this schedule
     int32_t all_done;       // epoch + 1 once every GEMM1 tile of the running launch is stored
-    int32_t pad2[6];
+    int32_t pad2[4];
     int32_t ticket[kMaxGemmWorkgroups][8]; // per workgroup: tiles drawn by its first thread for all of it
 };
 constexpr size_t kTileTableHeaderBytes = 32768;
@@ -285,9 +288,8 @@ struct GemmArgs {
 };
 
 // Persistent grouped GEMM, as a function: a kernel runs one of them, or (the dependency-driven expert
-// computation) the two GEMMs one after the other.  Main: the geometry of stream 0 (and of everything when there is no
-// second geometry); Light: the geometry of stream 1, tiles of experts with at most Light::BM rows,
-// or `void`.  Both geometries have the same workgroup size, BN and K tile.
+// computation) the two GEMMs one after the other.  Set: a geometry for each kind of tile (0: experts of several row
+// tiles, 3: of one such tile, 2: middle, 1: shallow), all of one workgroup size, BN and K tile.
 // kGather: row m of the A operand is row gather_rows[m] / gather_div of `A` (the dispatch's row
 // move done by the operand loads themselves) instead of row m.
 // kScatter: the result is not stored as row m of C.  `C` is an fp32 matrix of Ndim columns, and row
@@ -299,9 +301,13 @@ struct GemmArgs {
 #if defined(__HIP_DEVICE_COMPILE__) // the body uses device-only types (buffer resources); the host pass only needs the kernels' stubs
 // kTurn: the reduction of a tile starts at a K tile that depends on its column tile (g.k_turn; without it 0).  A form of
 // its own because the wrap costs the matrix-bound launches 0.4 %.
-template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, int kDep, bool kTurn>
+template <class Set, bool kSwiglu, bool kGather, bool kScatter, int kDep, bool kTurn>
 __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
 {
+    using Main = typename Set::Main;
+    using Single = typename Set::Single;
+    using Mid = typename Set::Mid;
+    using Light = typename Set::Light;
     const uint16_t *__restrict__ const A = g.A;
     const int64_t M = g.M;
     const int Kdim = g.Kdim, Ndim = g.Ndim;
@@ -315,12 +321,12 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     const float *__restrict__ const scatter_w = g.scatter_w;
     static_assert(!(kGather && kScatter) && !(kScatter && kSwiglu), "kScatter belongs to the down projection");
     static_assert(kDep == 0 || (!kGather && !kScatter), "the dependency-driven form is built for the plain GEMMs");
-    constexpr bool kTwo = !std::is_void<Light>::value;
-    if constexpr (kTwo)
-        static_assert(std::conditional_t<kTwo, Light, Main>::kBK == Main::kBK &&
-                          std::conditional_t<kTwo, Light, Main>::BN == Main::BN &&
-                          std::conditional_t<kTwo, Light, Main>::kThreads == Main::kThreads,
-                      "the two geometries share K tile, BN and workgroup size");
+    static_assert(Light::kBK == Main::kBK && Light::BN == Main::BN && Light::kThreads == Main::kThreads &&
+                      Mid::kBK == Main::kBK && Mid::BN == Main::BN && Mid::kThreads == Main::kThreads,
+                  "the geometries share K tile, BN and workgroup size");
+    static_assert(Main::kKind == 0 && Light::kKind == 1 && Mid::kKind == 2 && Single::kKind == 3 && Single::BM == Main::BM &&
+                      Single::kExtra == Main::kExtra,
+                  "kinds of tiles");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -348,7 +354,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     const uint64_t trace_c0 = __builtin_amdgcn_s_memtime(), trace_r0 = __builtin_amdgcn_s_memrealtime();
     uint32_t trace_ticks[4] = {0, 0, 0, 0}, trace_tiles[4] = {0, 0, 0, 0}; // full, tall, ragged, shallow
 #endif
-    const int len0 = hdr->len[0], len1 = hdr->len[1];
+    const int len0 = hdr->len[0], len1 = hdr->len[1], end_mid = len0 + hdr->mid, end_several = hdr->several;
     const int slot = (blockIdx.x / kXcds) % 32, ls = hdr->light_slots;
     const bool light_first = ((slot + 1) * ls) / 32 > (slot * ls) / 32;
     // A draw has two parts (thread 0 only): the ticket of the workgroup's own stream and XCD, whose round trip runs under
@@ -396,7 +402,10 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             v = reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uint64_t>(table))[entry_of(word)];
         return TileEntry{v[0], v[1], v[2], v[3]};
     };
-    auto kind_of = [&](int word) { return kTwo && entry_of(word) >= len0 ? 1 : 0; };
+    auto kind_of = [&](int word) {
+        const int e = entry_of(word);
+        return e < end_several ? 0 : e < len0 ? 3 : e < end_mid ? 2 : 1;
+    };
     // consumer, thread 0 only: were the rows this tile reads complete at the time of the draw?
     const int32_t dep_epoch1 =
         kDep != 0 ? __hip_atomic_load(&(kDep == 1 ? hdr : g.hdr_dep)->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 : 0;
@@ -428,7 +437,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
     auto read_slot = [&]() { return __hip_atomic_load(slot_of(seq), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
 
-    const int KT = Main::kBK > 0 ? Kdim / Main::kBK : 0;
+    const int KT = Kdim / Main::kBK;
     const int64_t b1_delta = kSwiglu ? B1 - B0 : 0;
     int cur_t, nxt_t;   // the tile being computed and the next one, as table entries (-1: none)
     int after_next = -1; // the tile after `nxt`, picked up from the ticket slot inside the K loop
@@ -478,15 +487,17 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         // chunks, and the rest of an offset is the same for every lane.  (Worked out for each group by itself, the
         // offsets were some 150 instructions per output tile.)
         constexpr int kKeys = 16 / Cfg::kGroupRows;
-        static_assert(Cfg::kAGroups % kKeys == 0 && Cfg::kBGroups % kKeys == 0, "groups start at a multiple of 16 rows");
+        static_assert(Cfg::kBGroups % kKeys == 0 && (Cfg::kAGroups % kKeys == 0 || kKeys == 2), "groups start at a multiple of 8 rows");
         const int row_bytes = Kdim * 2, row_off = ld_row * row_bytes;
         int chunk_off[kKeys];
 #pragma unroll
         for (int k = 0; k < kKeys; ++k)
             chunk_off[k] = (ld_pc ^ row_key<kChunks>(k * Cfg::kGroupRows + ld_row)) * 16;
+        // (an odd number of groups: an odd wavefront's first one starts 8 rows past a multiple of 16)
+        const int turn_keys = Cfg::kAGroups % kKeys ? wave % 2 : 0;
 #pragma unroll
         for (int g = 0; g < Cfg::kAGroups; ++g)
-            a_off[g] = chunk_off[g % kKeys] + (kGather ? 0 : row_off + (wave * Cfg::kAGroups + g) * Cfg::kGroupRows * row_bytes);
+            a_off[g] = (turn_keys ? chunk_off[(g + 1) % kKeys] : chunk_off[g % kKeys]) + (kGather ? 0 : row_off + (wave * Cfg::kAGroups + g) * Cfg::kGroupRows * row_bytes);
 #pragma unroll
         for (int g = 0; g < Cfg::kBGroups; ++g) {
             int col = (wave * Cfg::kBGroups + g) * Cfg::kGroupRows; // of the group's first row
@@ -648,11 +659,11 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t *>((here ? cur.b : nxt.b) + (up ? b1_delta : 0)), 0,
             here ? cur.b_bytes : nxt.b_bytes, 0x00020000);
-        // The weights of a light tile are read once by one workgroup: fetched with the non-temporal
+        // The weights of a light or middle tile are read once by one workgroup: fetched with the non-temporal
         // hint (aux bit 1) they do not push the other tiles' shared operands out of the caches.
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs, (lds_ptr)(lds + Cfg::unit_base(unit) + (wave * Cfg::kBGroups + g) * 1024), 16, b_off[g],
-            k_offset(here ? t : t - KT, here ? cur.k0 : nxt.k0), 0, Cfg::kKind == 1 ? MOE_LIGHT_AUX : 0);
+            k_offset(here ? t : t - KT, here ? cur.k0 : nxt.k0), 0, Cfg::kKind != 0 ? MOE_LIGHT_AUX : 0);
     };
 
     // ---- the ring.  K tile t keeps the rows of its "far" operand (the one whose loads run ahead in
@@ -850,23 +861,24 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             }
         } else {
             using yes = std::integral_constant<bool, true>;
-            // (K tiles 0 and 1 in the form for the tail, which does for all: no branch, so that there is one place where
-            // the accumulators come from and the compiler keeps count of the loads)
+            // (The first kDepth K tiles in the form for the tail, which does for all: no branch, so that there is one place
+            // where the accumulators come from and the compiler keeps count of the loads.)
             ktile(0, tail_yes{}, yes{});
             // The tile after `nxt`: thread 0 stored it before it reached the barrier of K tile 0.  The load is looked at
-            // behind K tile 1, whose own wait covers it (behind the K loop the compiler would wait for everything in
-            // flight, the next tile's operands included).
+            // behind K tile kDepth - 1, whose own wait covers it (behind the K loop the compiler would wait for everything
+            // in flight, the next tile's operands included).
             const uint64_t slot_v = read_slot();
             if constexpr (kGather)
                 gather_offsets(nxt_row); // looked up before K tile 0, long landed; needed from k_split on
-            // (A reduction of a single K tile multiplies zeros here: nothing is chained behind it, so loads past its end
-            // have no bytes.)
-            ktile(1, tail_yes{}, no{});
+            // (A reduction of fewer K tiles multiplies zeros here: nothing is chained behind it, so loads past its end have
+            // no bytes.)
+            [&]<int... I>(std::integer_sequence<int, I...>) { (ktile(I + 1, tail_yes{}, no{}), ...); }(
+                std::make_integer_sequence<int, kDepth - 1>{});
             keep_slot(slot_v);
             const int k_split = KT - (kDepth + kAhead);
-            for (int kt = 2; kt < k_split; ++kt)
+            for (int kt = kDepth; kt < k_split; ++kt)
                 ktile(kt, tail_no{}, no{});
-            for (int kt = (k_split > 2 ? k_split : 2); kt < KT; ++kt)
+            for (int kt = (k_split > kDepth ? k_split : kDepth); kt < KT; ++kt)
                 ktile(kt, tail_yes{}, no{});
         }
         // (if the store had not landed when the load ran, the sequence number is an older one)
@@ -1114,6 +1126,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             run_tile(std::integral_constant<int, 1>{}, ext_no{});
         else if (Cfg::kBlkM > 2 && active == 2)
             run_tile(std::integral_constant<int, (Cfg::kBlkM > 2 ? 2 : 1)>{}, ext_no{});
+        else if (Cfg::kBlkM > 4 && active == 4)
+            run_tile(std::integral_constant<int, (Cfg::kBlkM > 4 ? 4 : 1)>{}, ext_no{});
         else
             run_tile(std::integral_constant<int, (Cfg::kBlkM > 3 ? 3 : 1)>{}, ext_no{});
 
@@ -1185,14 +1199,15 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             __hip_atomic_load(my_ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         again = one_at_a_time && cur_t >= 0;
         while (cur_t >= 0) {
-            if constexpr (kTwo) {
-                if (kind_of(cur_t) == 1)
-                    engine(std::conditional_t<kTwo, Light, Main>{});
-                else
-                    engine(Main{});
-            } else {
+            const int kind = kind_of(cur_t);
+            if (kind == 1)
+                engine(Light{});
+            else if (kind == 2)
+                engine(Mid{});
+            else if (kind == 3)
+                engine(Single{});
+            else
                 engine(Main{});
-            }
         }
         MOE_WAIT_VMCNT(0);
     } while (again && !gave_up);
@@ -1227,13 +1242,13 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
 }
 #endif // __HIP_DEVICE_COMPILE__
 
-// One GEMM per launch.
-template <class Main, class Light, bool kSwiglu, bool kGather, bool kScatter, bool kTurn>
-__global__ __launch_bounds__(Main::kThreads, (Main::kLdsBytes <= 80 * 1024 ? 2 : 1)) void grouped_gemm_bf16(GemmArgs g)
+// One GEMM per launch.  Set: a geometry of each kind.
+template <class Set, bool kSwiglu, bool kGather, bool kScatter, bool kTurn>
+__global__ __launch_bounds__(Set::Main::kThreads, 1) void grouped_gemm_bf16(GemmArgs g)
 {
     static_assert(!(kGather && kScatter) && !(kScatter && kSwiglu), "kScatter belongs to the down projection");
 #if defined(__HIP_DEVICE_COMPILE__) // the body uses device-only types (buffer resources); the host pass only needs the stub
-    gemm_phase<Main, Light, kSwiglu, kGather, kScatter, 0, kTurn>(g);
+    gemm_phase<Set, kSwiglu, kGather, kScatter, 0, kTurn>(g);
 #endif
 }
 
@@ -1243,13 +1258,13 @@ __global__ __launch_bounds__(Main::kThreads, (Main::kLdsBytes <= 80 * 1024 ? 2 :
 // the head of the second overlap, and there is one launch instead of two.  kTurn1, kTurn2: of each phase by itself.  With
 // both phases always in the turned form, launches that turn nothing took 0.7 - 1.2 % longer (without -> with, us: 64
 // experts, H 2048, F 1408, 32768 rows 597 -> 602; 256 experts, H 7168, F 2048, 131072 rows 10140 -> 10262).
-template <class Main1, class Light1, class Main2, class Light2, bool kTurn1, bool kTurn2>
-__global__ __launch_bounds__(Main1::kThreads, 1) void grouped_ffn_bf16(GemmArgs g1, GemmArgs g2)
+template <class Set1, class Set2, bool kTurn1, bool kTurn2>
+__global__ __launch_bounds__(Set1::Main::kThreads, 1) void grouped_ffn_bf16(GemmArgs g1, GemmArgs g2)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    gemm_phase<Main1, Light1, true, false, false, 1, kTurn1>(g1);
+    gemm_phase<Set1, true, false, false, 1, kTurn1>(g1);
     __syncthreads(); // the ring is drained (every path out of a phase waits for its loads); LDS changes hands
-    gemm_phase<Main2, Light2, false, false, false, 2, kTurn2>(g2);
+    gemm_phase<Set2, false, false, false, 2, kTurn2>(g2);
 #endif
 }
 
