@@ -4,6 +4,11 @@ from __future__ import annotations
 import ctypes
 import os
 
+try:
+    import torch
+except ImportError:  # the library's path, its symbols and last_error() need no torch
+    torch = None
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 # MOE_HUB_LIBRARY selects another build of the same library (A/B timing of two builds)
 _LIB_PATH = os.environ.get("MOE_HUB_LIBRARY") or os.path.join(HERE, "libmoe_hub.so")
@@ -100,7 +105,6 @@ def _ptr(t):
 def _stream():
     # the handle itself where this torch hands it out (the name is private to it); torch.cuda.current_stream() builds a
     # Stream object around it at every call
-    import torch
     try:
         raw = torch._C._cuda_getCurrentRawStream
     except AttributeError:
@@ -109,7 +113,6 @@ def _stream():
 
 
 def _dtype_code(t) -> int:
-    import torch
     if t.dtype == torch.bfloat16:
         return BF16
     if t.dtype == torch.float32:
@@ -120,6 +123,22 @@ def _dtype_code(t) -> int:
 def _need(t, dtype, name):
     if not t.is_cuda or not t.is_contiguous() or t.dtype != dtype:
         raise TypeError(f"{name} must be a contiguous device tensor of {dtype}")
+
+
+def _need_layout(E, G, R, *arrays):
+    # One pass without a call per array where all is well: a layer of one token is bound by the host.  With torch imported once
+    # and pointers taken without a call, 256 fp32 rows (five calls) take 32.2 us instead of 33.4, 13.2 -> 12.0 of them here.
+    i32 = torch.int32
+    sizes = (E, E + 1, G, G + 1, R, R)
+    for t, n in zip(arrays, sizes):
+        if t.dtype != i32 or not t.is_cuda or not t.is_contiguous() or t.numel() != n:
+            break
+    else:
+        return
+    names = ("expert_counts", "expert_offsets", "dest_counts", "dest_offsets", "slot_of_row", "row_of_slot")
+    for name, t, n in zip(names, arrays, sizes):
+        _need(t, i32, name)
+        assert t.numel() == n, name
 
 
 def workspace_bytes(op: int, N: int = 0, H: int = 0, E: int = 0, K: int = 0, G: int = 1, F: int = 0,
@@ -134,7 +153,6 @@ def _ws_args(ws):
 
 
 def moe_route(x, W_r, bias, K: int, score_mode: int, topk_idx, topk_w, logits=None, ws=None):
-    import torch
     N, H = x.shape
     E = W_r.shape[1]
     _need(W_r, torch.float32, "W_r")
@@ -144,62 +162,48 @@ def moe_route(x, W_r, bias, K: int, score_mode: int, topk_idx, topk_w, logits=No
     assert topk_idx.numel() == N * K and topk_w.numel() == N * K
     assert logits is None or (logits.numel() == N * E and logits.dtype == torch.float32)
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_route(_ptr(x), _dtype_code(x), N, H, _ptr(W_r), _ptr(bias), E, K, score_mode,
-                                    _ptr(topk_idx), _ptr(topk_w), _ptr(logits), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_route(x.data_ptr(), _dtype_code(x), N, H, W_r.data_ptr(), _ptr(bias), E, K, score_mode,
+                         topk_idx.data_ptr(), topk_w.data_ptr(), _ptr(logits), wp, wb, _stream()))
 
 
 def moe_dispatch_layout(topk_idx, E: int, G: int, expert_counts, expert_offsets, dest_counts, dest_offsets,
                         slot_of_row, row_of_slot, ws):
-    import torch
     N, K = topk_idx.shape
-    for name, t, n in (("expert_counts", expert_counts, E), ("expert_offsets", expert_offsets, E + 1),
-                       ("dest_counts", dest_counts, G), ("dest_offsets", dest_offsets, G + 1),
-                       ("slot_of_row", slot_of_row, N * K), ("row_of_slot", row_of_slot, N * K)):
-        _need(t, torch.int32, name)
-        assert t.numel() == n, name
+    _need_layout(E, G, N * K, expert_counts, expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot)
     _need(topk_idx, torch.int32, "topk_idx")
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_dispatch_layout(_ptr(topk_idx), N, K, E, G, _ptr(expert_counts),
-                                              _ptr(expert_offsets), _ptr(dest_counts), _ptr(dest_offsets),
-                                              _ptr(slot_of_row), _ptr(row_of_slot), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_dispatch_layout(topk_idx.data_ptr(), N, K, E, G, expert_counts.data_ptr(),
+                                   expert_offsets.data_ptr(), dest_counts.data_ptr(), dest_offsets.data_ptr(),
+                                   slot_of_row.data_ptr(), row_of_slot.data_ptr(), wp, wb, _stream()))
 
 
 def moe_dispatch_layout_static(topk_idx, E: int, G: int, expert_counts, expert_offsets, dest_counts,
                                dest_offsets, slot_of_row, row_of_slot):
-    import torch
     N, K = topk_idx.shape
-    for name, t, n in (("expert_counts", expert_counts, E), ("expert_offsets", expert_offsets, E + 1),
-                       ("dest_counts", dest_counts, G), ("dest_offsets", dest_offsets, G + 1),
-                       ("slot_of_row", slot_of_row, N * K), ("row_of_slot", row_of_slot, N * K)):
-        _need(t, torch.int32, name)
-        assert t.numel() == n, name
+    _need_layout(E, G, N * K, expert_counts, expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot)
     _need(topk_idx, torch.int32, "topk_idx")
-    _check(load_library().moe_dispatch_layout_static(_ptr(topk_idx), N, K, E, G, _ptr(expert_counts),
-                                                     _ptr(expert_offsets), _ptr(dest_counts),
-                                                     _ptr(dest_offsets), _ptr(slot_of_row),
-                                                     _ptr(row_of_slot), _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_dispatch_layout_static(topk_idx.data_ptr(), N, K, E, G, expert_counts.data_ptr(),
+                                          expert_offsets.data_ptr(), dest_counts.data_ptr(), dest_offsets.data_ptr(),
+                                          slot_of_row.data_ptr(), row_of_slot.data_ptr(), _stream()))
 
 
 def moe_dispatch_layout_arrival(topk_idx, E: int, G: int, expert_counts, expert_offsets, dest_counts,
                                 dest_offsets, slot_of_row, row_of_slot):
-    import torch
     N, K = topk_idx.shape
-    for name, t, n in (("expert_counts", expert_counts, E), ("expert_offsets", expert_offsets, E + 1),
-                       ("dest_counts", dest_counts, G), ("dest_offsets", dest_offsets, G + 1),
-                       ("slot_of_row", slot_of_row, N * K), ("row_of_slot", row_of_slot, N * K)):
-        _need(t, torch.int32, name)
-        assert t.numel() == n, name
+    _need_layout(E, G, N * K, expert_counts, expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot)
     _need(topk_idx, torch.int32, "topk_idx")
-    _check(load_library().moe_dispatch_layout_arrival(_ptr(topk_idx), N, K, E, G, _ptr(expert_counts),
-                                                      _ptr(expert_offsets), _ptr(dest_counts),
-                                                      _ptr(dest_offsets), _ptr(slot_of_row),
-                                                      _ptr(row_of_slot), _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_dispatch_layout_arrival(topk_idx.data_ptr(), N, K, E, G, expert_counts.data_ptr(),
+                                           expert_offsets.data_ptr(), dest_counts.data_ptr(), dest_offsets.data_ptr(),
+                                           slot_of_row.data_ptr(), row_of_slot.data_ptr(), _stream()))
 
 
 def moe_route_resolve_arrival(x, W_r, bias, K: int, G: int, score_mode: int, topk_idx, topk_w, expert_counts,
                               expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot, logits=None,
                               ws=None):
-    import torch
     N, H = x.shape
     E = W_r.shape[1]
     _need(W_r, torch.float32, "W_r")
@@ -208,28 +212,26 @@ def moe_route_resolve_arrival(x, W_r, bias, K: int, G: int, score_mode: int, top
     assert W_r.shape[0] == H and x.is_contiguous()
     assert topk_idx.numel() == N * K and topk_w.numel() == N * K
     assert logits is None or (logits.numel() == N * E and logits.dtype == torch.float32)
-    for name, t, n in (("expert_counts", expert_counts, E), ("expert_offsets", expert_offsets, E + 1),
-                       ("dest_counts", dest_counts, G), ("dest_offsets", dest_offsets, G + 1),
-                       ("slot_of_row", slot_of_row, N * K), ("row_of_slot", row_of_slot, N * K)):
-        _need(t, torch.int32, name)
-        assert t.numel() == n, name
+    _need_layout(E, G, N * K, expert_counts, expert_offsets, dest_counts, dest_offsets, slot_of_row, row_of_slot)
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_route_resolve_arrival(
-        _ptr(x), _dtype_code(x), N, H, _ptr(W_r), _ptr(bias), E, K, G, score_mode, _ptr(topk_idx), _ptr(topk_w),
-        _ptr(logits), _ptr(expert_counts), _ptr(expert_offsets), _ptr(dest_counts), _ptr(dest_offsets),
-        _ptr(slot_of_row), _ptr(row_of_slot), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_route_resolve_arrival(x.data_ptr(), _dtype_code(x), N, H, W_r.data_ptr(), _ptr(bias), E, K, G,
+                                         score_mode, topk_idx.data_ptr(), topk_w.data_ptr(), _ptr(logits),
+                                         expert_counts.data_ptr(), expert_offsets.data_ptr(), dest_counts.data_ptr(),
+                                         dest_offsets.data_ptr(), slot_of_row.data_ptr(), row_of_slot.data_ptr(), wp,
+                                         wb, _stream()))
 
 
 def moe_permute(x, K: int, slot_of_row, row_of_slot, xp):
     N, H = x.shape
     assert x.is_contiguous() and xp.is_contiguous() and xp.dtype == x.dtype and xp.numel() == N * K * H
     assert slot_of_row.numel() == N * K and row_of_slot.numel() == N * K
-    _check(load_library().moe_permute(_ptr(x), _dtype_code(x), N, H, K, _ptr(slot_of_row), _ptr(row_of_slot),
-                                      _ptr(xp), _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_permute(x.data_ptr(), _dtype_code(x), N, H, K, slot_of_row.data_ptr(), row_of_slot.data_ptr(),
+                           xp.data_ptr(), _stream()))
 
 
 def moe_grouped_ffn(xp, seg_offsets, W_gate, W_up, W_down, y, ws):
-    import torch
     M, H = xp.shape
     E_local, F, H2 = W_gate.shape
     assert H2 == H and tuple(W_up.shape) == (E_local, F, H) and tuple(W_down.shape) == (E_local, H, F)
@@ -239,18 +241,18 @@ def moe_grouped_ffn(xp, seg_offsets, W_gate, W_up, W_down, y, ws):
     _need(seg_offsets, torch.int32, "seg_offsets")
     assert seg_offsets.numel() == E_local + 1 and y.numel() == M * H
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_grouped_ffn(_ptr(xp), _dtype_code(xp), M, H, F, E_local, _ptr(seg_offsets),
-                                          _ptr(W_gate), _ptr(W_up), _ptr(W_down), _ptr(y), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_grouped_ffn(xp.data_ptr(), _dtype_code(xp), M, H, F, E_local, seg_offsets.data_ptr(),
+                               W_gate.data_ptr(), W_up.data_ptr(), W_down.data_ptr(), y.data_ptr(), wp, wb, _stream()))
 
 
 def moe_ffn_schedule(dtype: int, M: int, H: int, F: int, seg_offsets, ws):
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_schedule(dtype, M, H, F, seg_offsets.numel() - 1, _ptr(seg_offsets), wp, wb,
-                                           _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_schedule(dtype, M, H, F, seg_offsets.numel() - 1, seg_offsets.data_ptr(), wp, wb, _stream()))
 
 
 def moe_ffn_gate_up_down(xp, seg_offsets, W_gate, W_up, W_down, y, ws, wait_limit: int = 0):
-    import torch
     M, H = xp.shape
     E_local, F, H2 = W_gate.shape
     assert H2 == H and tuple(W_up.shape) == (E_local, F, H) and tuple(W_down.shape) == (E_local, H, F)
@@ -260,15 +262,17 @@ def moe_ffn_gate_up_down(xp, seg_offsets, W_gate, W_up, W_down, y, ws, wait_limi
     _need(seg_offsets, torch.int32, "seg_offsets")
     assert seg_offsets.numel() == E_local + 1 and y.numel() == M * H
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_gate_up_down(_ptr(xp), _dtype_code(xp), M, H, F, E_local, _ptr(seg_offsets),
-                                               _ptr(W_gate), _ptr(W_up), _ptr(W_down), _ptr(y), wp, wb,
-                                               wait_limit, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_gate_up_down(xp.data_ptr(), _dtype_code(xp), M, H, F, E_local, seg_offsets.data_ptr(),
+                                    W_gate.data_ptr(), W_up.data_ptr(), W_down.data_ptr(), y.data_ptr(), wp, wb,
+                                    wait_limit, _stream()))
 
 
 def moe_ffn_status(dtype: int, M: int, H: int, F: int, E_local: int, ws):
     """Waits for the current stream; raises MoEHubError(MOE_ERR_STATE) if a GEMM step found no schedule."""
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_status(dtype, M, H, F, E_local, wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_status(dtype, M, H, F, E_local, wp, wb, _stream()))
 
 
 def moe_ffn_gate_up(xp, seg_offsets, W_gate, W_up, ws):
@@ -278,12 +282,12 @@ def moe_ffn_gate_up(xp, seg_offsets, W_gate, W_up, ws):
     assert xp.is_contiguous() and W_gate.is_contiguous() and W_up.is_contiguous()
     assert seg_offsets.numel() == E_local + 1
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_gate_up(_ptr(xp), _dtype_code(xp), M, H, F, E_local, _ptr(seg_offsets),
-                                          _ptr(W_gate), _ptr(W_up), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_gate_up(xp.data_ptr(), _dtype_code(xp), M, H, F, E_local, seg_offsets.data_ptr(),
+                               W_gate.data_ptr(), W_up.data_ptr(), wp, wb, _stream()))
 
 
 def moe_ffn_gate_up_gather(x, K: int, seg_offsets, row_of_slot, W_gate, W_up, ws):
-    import torch
     N, H = x.shape
     E_local, F, _ = W_gate.shape
     assert tuple(W_up.shape) == tuple(W_gate.shape) and W_gate.shape[2] == H
@@ -292,8 +296,9 @@ def moe_ffn_gate_up_gather(x, K: int, seg_offsets, row_of_slot, W_gate, W_up, ws
     _need(row_of_slot, torch.int32, "row_of_slot")
     assert row_of_slot.numel() == N * K
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_gate_up_gather(_ptr(x), _dtype_code(x), N, K, H, F, E_local, _ptr(seg_offsets),
-                                                 _ptr(row_of_slot), _ptr(W_gate), _ptr(W_up), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_gate_up_gather(x.data_ptr(), _dtype_code(x), N, K, H, F, E_local, seg_offsets.data_ptr(),
+                                      row_of_slot.data_ptr(), W_gate.data_ptr(), W_up.data_ptr(), wp, wb, _stream()))
 
 
 def moe_ffn_down(seg_offsets, W_down, y, ws):
@@ -302,12 +307,12 @@ def moe_ffn_down(seg_offsets, W_down, y, ws):
     assert H2 == H and y.is_contiguous() and W_down.is_contiguous() and W_down.dtype == y.dtype
     assert seg_offsets.numel() == E_local + 1
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_down(_dtype_code(y), M, H, F, E_local, _ptr(seg_offsets), _ptr(W_down),
-                                       _ptr(y), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_down(_dtype_code(y), M, H, F, E_local, seg_offsets.data_ptr(), W_down.data_ptr(), y.data_ptr(),
+                            wp, wb, _stream()))
 
 
 def moe_ffn_down_combine(K: int, seg_offsets, W_down, row_of_slot, topk_w, sums, out, ws):
-    import torch
     N, H = out.shape
     E_local, H2, F = W_down.shape
     assert H2 == H and out.is_contiguous() and W_down.is_contiguous() and W_down.dtype == out.dtype
@@ -317,16 +322,17 @@ def moe_ffn_down_combine(K: int, seg_offsets, W_down, row_of_slot, topk_w, sums,
     _need(sums, torch.float32, "sums")
     assert row_of_slot.numel() == N * K and topk_w.numel() == N * K and sums.numel() == N * H
     wp, wb = _ws_args(ws)
-    _check(load_library().moe_ffn_down_combine(_dtype_code(out), N, K, H, F, E_local, _ptr(seg_offsets),
-                                               _ptr(W_down), _ptr(row_of_slot), _ptr(topk_w), _ptr(sums),
-                                               _ptr(out), wp, wb, _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_ffn_down_combine(_dtype_code(out), N, K, H, F, E_local, seg_offsets.data_ptr(), W_down.data_ptr(),
+                                    row_of_slot.data_ptr(), topk_w.data_ptr(), sums.data_ptr(), out.data_ptr(), wp, wb,
+                                    _stream()))
 
 
 def moe_combine(y, K: int, slot_of_row, topk_w, out):
-    import torch
     N, H = out.shape
     assert y.is_contiguous() and out.is_contiguous() and y.dtype == out.dtype and y.numel() == N * K * H
     _need(topk_w, torch.float32, "topk_w")
     assert slot_of_row.numel() == N * K and topk_w.numel() == N * K
-    _check(load_library().moe_combine(_ptr(y), _dtype_code(y), N, H, K, _ptr(slot_of_row), _ptr(topk_w),
-                                      _ptr(out), _stream()))
+    lib = _lib or load_library()
+    _check(lib.moe_combine(y.data_ptr(), _dtype_code(y), N, H, K, slot_of_row.data_ptr(), topk_w.data_ptr(),
+                           out.data_ptr(), _stream()))
