@@ -339,7 +339,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     //      Thread 0 draws for the whole workgroup and passes the tile on through global memory
     //      (LDS is full and a register cannot cross wavefronts): {tile, sequence number}, stored
     //      and loaded as one 8-byte unit.  A reader that finds an older sequence number reads
-    //      again, so nobody waits for the store to land and nobody acts on a stale tile.
+    //      again, so nobody waits for the store to land and nobody acts on a stale tile (a launch
+    //      starts with sequence numbers of its own in both pairs, see below).
     if (hdr->magic != kTableMagic || hdr->rows != (int32_t)M || hdr->out_cols != Main::kOutCols) {
         // no schedule for these rows in this workspace: nothing to go by.  The host is not waiting for
         // this kernel, so all it can do is leave a word that moe_ffn_status finds.
@@ -1160,7 +1161,9 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     }; // engine
 
     // ---- the workgroup's first three tiles.  The words still hold what an earlier launch left
-    //      there, so these stores have to be in memory before anyone looks.
+    //      there, so these stores have to be in memory before anyone looks.  That goes for the pair
+    //      that nothing is published in yet as well: the second draw's store is not waited for, and
+    //      an earlier launch in which the workgroup had one tile left sequence number 2 there too.
     //      A launch with about one tile per workgroup draws one tile at a time instead: the first
     //      workgroups to start would otherwise take three tiles each and leave others without.  So
     //      does a consumer phase with only a few tiles per workgroup, whose workgroups arrive one
@@ -1190,6 +1193,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                 else
                     publish(t);
             }
+            __hip_atomic_store(slot_of(0), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         MOE_WAIT_VMCNT(0);
         __syncthreads();
