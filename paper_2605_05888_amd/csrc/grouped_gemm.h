@@ -961,18 +961,20 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             // it some 7000 cycles.)
             uint32_t lane_o = (uint32_t)lane;
             asm volatile("" : "+v"(lane_o)); // (see lane_setup)
-            const int row_bytes = Ndim * 2;
-            const int voff = (int)(lane_o % 16) * row_bytes + (int)((lane_o / 16 % 2) * 16 + (lane_o / 32) * 8) * 2;
+            const uint32_t row_bytes = (uint32_t)Ndim * 2u;
+            const uint32_t voff = lane_o % 16 * row_bytes + ((lane_o / 16 % 2) * 16 + (lane_o / 32) * 8) * 2;
             const int rows_left = cur.m_end - cur.m0;
-            const int tile_rows = rows_left < BM + Cfg::kExtra ? rows_left : BM + Cfg::kExtra;
+            // (of this tile, no more: 256 rows of 16 MB are just below what a byte count can hold, as in `a_bytes`)
+            constexpr int kTileRows = BM + (kHalf ? Cfg::kExtra / 2 : kExt ? Cfg::kExtra : 0);
+            const int tile_rows = rows_left < kTileRows ? rows_left : kTileRows;
             uint16_t *const c_tile = C + (int64_t)cur.m0 * Ndim + n_wave;
-            const uint32_t c_bytes = (uint32_t)tile_rows * (uint32_t)row_bytes - (uint32_t)n_wave * 2u;
+            const uint32_t c_bytes = (uint32_t)tile_rows * row_bytes - (uint32_t)n_wave * 2u;
             const int blocks_left = (Ndim - n_wave) / 32; // (Ndim is a multiple of 64)
             constexpr int kAux = kDep == 1 && MOE_DEP_STORE_THROUGH == 1 ? 16 : 0; // 16: device scope, written through this XCD's L2, which the other XCDs do not snoop
             // block row at row `r0` of the tile: column blocks first, first + step, ... of the wavefront
             auto store_row = [&](int r0, const auto &blk, auto in_acc_regs, int first, auto step_tag, auto n_tag) {
                 constexpr int kStep = decltype(step_tag)::value, kN = decltype(n_tag)::value;
-                const int v0 = voff + r0 * row_bytes + first * 64, v1 = v0 + 16 * row_bytes;
+                const uint32_t v0 = voff + (uint32_t)r0 * row_bytes + (uint32_t)first * 64, v1 = v0 + 16 * row_bytes;
 #pragma unroll
                 for (int j = 0; j < kN; ++j) {
                     uint32_t p[8]; // [quarter][pair of columns]
@@ -998,8 +1000,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                         lo[h] = x, hi[h] = y;
                     }
                     const auto rs = __builtin_amdgcn_make_buffer_rsrc(c_tile, 0, first + j * kStep < blocks_left ? c_bytes : 0u, 0x00020000);
-                    __builtin_amdgcn_raw_buffer_store_b128(lo, rs, v0 + j * kStep * 64, 0, kAux);
-                    __builtin_amdgcn_raw_buffer_store_b128(hi, rs, v1 + j * kStep * 64, 0, kAux);
+                    __builtin_amdgcn_raw_buffer_store_b128(lo, rs, (int)v0 + j * kStep * 64, 0, kAux);
+                    __builtin_amdgcn_raw_buffer_store_b128(hi, rs, (int)v1 + j * kStep * 64, 0, kAux);
                     // one block at a time: left alone, the scheduler first copies the whole tile out of the
                     // accumulation registers and needs some two hundred registers to hold it
                     __builtin_amdgcn_sched_barrier(0);
