@@ -522,8 +522,8 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     // end of a tile's reduction fetch the first K tiles of the workgroup's next tile (if that is
     // of the same kind), so that tile starts with its operands in LDS.  (Shorter reductions
     // start every tile from scratch.)
-    // (kGather: one K tile more.  The rows of the next tile become offsets behind K tile 0, whose last loads would need them.)
-    const bool warm = KT >= kDepth + kAhead + (kGather ? 1 : 0);
+    // (kGather: the rows of the next tile become offsets behind K tile 0, so K tile 0 must not fetch rows of it yet.)
+    const bool warm = KT >= kDepth + kAhead && (!kGather || KT > kAheadOfA);
 
     // What the loads of a tile need.  Rows past the end of the segment (and columns past Ndim) lie
     // beyond the byte counts: the bounds check returns zeros for them without touching memory; a
