@@ -38,9 +38,9 @@ constexpr int kLightCost = 3, kMidCost = 6, kHeavyCost = 7;
 // experts with at most this many rows go through the shallow tile geometry
 constexpr int kLightRows = 64;
 
-// Experts come in four classes by their rows (geometries in ffn_gemm.h): several row tiles, one, middle, light.  The first two
-// form stream 0 of the table, the others stream 1; inside a class the order is expert, column tile, row tile.  The GEMM's
-// persistent workgroups draw from both streams.
+// Experts come in three classes by their rows (geometries in ffn_gemm.h): full tiles, middle, light.  The first forms stream 0
+// of the table, the others stream 1; inside a class the order is expert, column tile, row tile.  The GEMM's persistent
+// workgroups draw from both streams.
 // Row tiles of an expert with `rows` rows: a remainder of at most `extra` rows rides with the last
 // full tile instead of forming a tile of its own.
 __device__ __forceinline__ int row_tiles(int32_t rows, int BM, int extra)
@@ -78,18 +78,17 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
     const int n_tiles = args.n_tiles, max_tiles = args.max_tiles, BM = args.BM, extra = args.extra;
     TileTableHeader *__restrict__ hdr = args.hdr;
     TileEntry *__restrict__ table = args.table;
-    // first tile of each expert among those of its class: several row tiles [0], one of them [1], middle [2], light [3]
-    __shared__ int32_t start[4][MOE_MAX_EXPERTS + 1];
-    __shared__ int32_t wave_tot[4][kSchedThreads / kWave];
+    // first tile of each expert among those of its class: full [0], middle [1], light [2]
+    constexpr int kClasses = 3;
+    __shared__ int32_t start[kClasses][MOE_MAX_EXPERTS + 1];
+    __shared__ int32_t wave_tot[kClasses][kSchedThreads / kWave];
     const int mid_rows = args.mid_rows;
-    auto class_of = [&](int32_t rows) {
-        return rows <= light_rows ? 3 : rows <= mid_rows ? 2 : row_tiles(rows, BM, extra) == 1 ? 1 : 0;
-    };
+    auto class_of = [&](int32_t rows) { return rows <= light_rows ? 2 : rows <= mid_rows ? 1 : 0; };
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     // exclusive scans of tiles per expert; a thread owns a contiguous run of experts
     const int per = (E_local + kSchedThreads - 1) / kSchedThreads;
     const int e_lo = tid * per;
-    int32_t mine[4] = {0, 0, 0, 0};
+    int32_t mine[kClasses] = {0, 0, 0};
     for (int j = 0; j < per; ++j) {
         const int e = e_lo + j;
         if (e < E_local) {
@@ -98,23 +97,23 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
             mine[class_of(rows)] += row_tiles(rows, BM, extra) * n_tiles;
         }
     }
-    int32_t inc[4] = {mine[0], mine[1], mine[2], mine[3]};
+    int32_t inc[kClasses] = {mine[0], mine[1], mine[2]};
     for (int d = 1; d < kWave; d <<= 1) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < kClasses; ++c) {
             const int32_t t = __shfl_up(inc[c], d);
             if (lane >= d)
                 inc[c] += t;
         }
     }
     if (lane == kWave - 1) {
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < kClasses; ++c)
             wave_tot[c][wave] = inc[c];
     }
     __syncthreads();
-    int32_t run[4] = {inc[0] - mine[0], inc[1] - mine[1], inc[2] - mine[2], inc[3] - mine[3]};
+    int32_t run[kClasses] = {inc[0] - mine[0], inc[1] - mine[1], inc[2] - mine[2]};
     for (int w = 0; w < wave; ++w) {
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < kClasses; ++c)
             run[c] += wave_tot[c][w];
     }
     for (int j = 0; j < per; ++j) {
@@ -122,31 +121,28 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
         if (e < E_local) {
             int64_t lo;
             const int32_t rows = clamped_rows(seg_offsets, e, M, lo);
-            for (int c = 0; c < 4; ++c)
+            for (int c = 0; c < kClasses; ++c)
                 start[c][e] = run[c];
             run[class_of(rows)] += row_tiles(rows, BM, extra) * n_tiles;
         }
     }
     if (tid == kSchedThreads - 1) { // the last thread's running sums are the totals
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < kClasses; ++c)
             start[c][E_local] = run[c];
     }
     __syncthreads();
-    int32_t several = start[0][E_local], mid = start[2][E_local];
-    int32_t len[2] = {several + start[1][E_local], mid + start[3][E_local]};
-    if (len[0] + len[1] > max_tiles) { // cannot happen for monotone offsets within [0, M]
-        len[0] = len[0] < max_tiles ? len[0] : max_tiles;
-        len[1] = max_tiles - len[0];
-        several = several < len[0] ? several : len[0];
-        mid = mid < len[1] ? mid : len[1];
-    }
+    // ends of the classes in the table (the bound cannot be reached by monotone offsets within [0, M])
+    auto end_of = [&](int32_t tiles) { return tiles < max_tiles ? tiles : max_tiles; };
+    const int32_t end_full = end_of(start[0][E_local]), end_mid = end_of(end_full + start[1][E_local]);
+    const int32_t total = end_of(end_mid + start[2][E_local]);
     if (blockIdx.x == 0 && tid == 0) {
-        hdr->len[0] = len[0];
-        hdr->len[1] = len[1];
-        hdr->several = several;
-        hdr->mid = mid;
+        hdr->len[0] = end_full;
+        hdr->len[1] = total - end_full;
+        hdr->end_full = end_full;
+        hdr->end_mid = end_mid;
         // share of the workgroup slots that take stream 1 first: its tiles' share of the work
-        const int64_t wl = (int64_t)(len[1] - mid) * kLightCost + (int64_t)mid * kMidCost, wh = (int64_t)len[0] * kHeavyCost;
+        const int64_t wl = (int64_t)(total - end_mid) * kLightCost + (int64_t)(end_mid - end_full) * kMidCost;
+        const int64_t wh = (int64_t)end_full * kHeavyCost;
         hdr->light_slots = wl + wh > 0 ? (int32_t)((32 * wl + (wl + wh) / 2) / (wl + wh)) : 0;
         hdr->done = 0;
         hdr->error = 0;
@@ -159,10 +155,9 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
             for (int x = 0; x < kXcds; ++x)
                 hdr->next[s][x] = 0;
     }
-    const int32_t total = len[0] + len[1];
     for (int L = blockIdx.x * kSchedThreads + tid; L < total; L += gridDim.x * kSchedThreads) {
-        const int c = L < several ? 0 : L < len[0] ? 1 : L < len[0] + mid ? 2 : 3;
-        const int32_t pos = L - (c == 0 ? 0 : c == 1 ? several : c == 2 ? len[0] : len[0] + mid); // place among the tiles of its class
+        const int c = L < end_full ? 0 : L < end_mid ? 1 : 2;
+        const int32_t pos = L - (c == 0 ? 0 : c == 1 ? end_full : end_mid); // place among the tiles of its class
         int lo_e = 0, hi_e = E_local;             // last e with start[c][e] <= pos: the expert that owns it
         while (hi_e - lo_e > 1) {
             const int mid = (lo_e + hi_e) >> 1;

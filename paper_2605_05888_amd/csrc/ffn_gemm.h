@@ -14,23 +14,25 @@ namespace moe {
 //   65 - 160: Mid, 160x256x64, three pairs, every wavefront all rows of 64 columns.  Such a tile waits for memory; in Big, whose
 //     A rows are fetched less than a K tile ahead and return in order behind the weights, a K tile took 2 us of which 1 was
 //     arithmetic.  160 rows is the most three pairs have room for.
-//   161 - 320, one row tile: Big with the weights as below.
 //   more: Big, 256x256x64, ring of 5 units (all 160 KiB of LDS); per window the 8 B loads of a wavefront go out under the first
 //     two k-steps after the barrier, the 8 A loads under the other two.  An expert's last full tile also takes a remainder of up
 //     to 64 rows ("tall" tile).
-// Weights that one workgroup reads once (all but the last class) are fetched with the non-temporal hint: they do not push out
-// what is shared.  Experts of several row tiles share them in L2 and lose with it (256 experts of 425 - 616 rows, layer 11.6 ->
+// The weights of the first two, which one workgroup reads once, are fetched with the non-temporal hint: they do not push out what
+// is shared.  Experts of several row tiles share them in L2 and lose with it (256 experts of 425 - 616 rows, layer 11.6 ->
 // 12.2 ms).  Gate/up, down, us, 16 experts, H 4096, F 6400, Big and ordinary loads -> Big and non-temporal -> as it is:
-// 72 rows 350, 167 -> 342, 159 -> 317, 155; 128 rows 373, 177 -> 354, 168 -> 332, 166; 160 rows 382, 183 -> 363, 173 -> 343, 171;
-// 176 rows 396, 190 -> 380, 180; 256 rows 450, 210 -> 419, 196; 300 rows 521, 240 -> 500, 230.
+// 72 rows 350, 167 -> 342, 159 -> 317, 155; 128 rows 373, 177 -> 354, 168 -> 332, 166; 160 rows 382, 183 -> 363, 173 -> 343, 171.
+// Experts of 161 - 320 rows, one Big tile, read their weights once too.  As a class of their own with the hint they took 0.98 of
+// the time in 26 random launches of nothing larger and more than 512 MB of weights (64 experts of 170 rows, K 5696, N 960 178 ->
+// 153 us), but 1.02 below that, 1.03 beside larger experts (a workgroup starts cold where the class changes) and 1.07 where the
+// weights stay in the memory-side cache, which the hint passes by (438 launches, up to 1.3): ordinary loads.
 // MOE_WEIGHTS_AHEAD: the operand that uses the ring's spare unit to run one K tile further ahead is the
 // weights (1) or the activations (0).
 #ifndef MOE_WEIGHTS_AHEAD
 #define MOE_WEIGHTS_AHEAD 1
 #endif
-template <bool kSwiglu, int kKind = 0>
+template <bool kSwiglu>
 using BigTile = GemmCfg<256, 256, 2, 2, kSwiglu, 64, 5, (MOE_WEIGHTS_AHEAD ? 0x4400 : 0x0044),
-                        (MOE_WEIGHTS_AHEAD ? 0x0044 : 0x4400), kKind, 64, (MOE_WEIGHTS_AHEAD != 0)>;
+                        (MOE_WEIGHTS_AHEAD ? 0x0044 : 0x4400), 0, 64, (MOE_WEIGHTS_AHEAD != 0)>;
 #ifndef MOE_SHALLOW_UNITS
 #define MOE_SHALLOW_UNITS 8
 #endif
@@ -41,7 +43,7 @@ template <bool kSwiglu> using ShallowTile = GemmCfg<64, 256, 1, 4, kSwiglu, 64, 
 // long as one tile, so half as wide a panel on twice as many compute units halves it.  Where reductions
 // are not turned (turn_of below) every output element is the same sum in the same order as with the
 // 256-column tiles, so y has the same bits; a turned one starts at a K tile that depends on the tile's width.
-template <bool kSwiglu, int kKind = 0> using NarrowBig = GemmCfg<256, 128, 2, 2, kSwiglu, 64, 6, 0x2222, 0x1111, kKind, 64>;
+template <bool kSwiglu> using NarrowBig = GemmCfg<256, 128, 2, 2, kSwiglu, 64, 6, 0x2222, 0x1111, 0, 64>;
 template <bool kSwiglu> using NarrowShallow = GemmCfg<64, 128, 1, 4, kSwiglu, 64, 8, 0x1010, 0x1111, 1>;
 template <bool kSwiglu> using MidTile = GemmCfg<160, 256, 1, 4, kSwiglu, 64, 6, 0x1121, 0x2222, 2>;
 template <bool kSwiglu> using NarrowMid = GemmCfg<160, 128, 1, 4, kSwiglu, 64, 8, 0x1121, 0x1111, 2>;
@@ -51,13 +53,11 @@ static_assert(MidTile<false>::BM == kMidRows && NarrowMid<false>::BM == kMidRows
 // a geometry of each kind
 template <bool kSwiglu> struct WideSet {
     using Main = BigTile<kSwiglu>;
-    using Single = BigTile<kSwiglu, 3>;
     using Mid = MidTile<kSwiglu>;
     using Light = ShallowTile<kSwiglu>;
 };
 struct NarrowSet {
     using Main = NarrowBig<false>;
-    using Single = NarrowBig<false, 3>;
     using Mid = NarrowMid<false>;
     using Light = NarrowShallow<false>;
 };

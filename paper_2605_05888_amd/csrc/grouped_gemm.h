@@ -69,15 +69,13 @@ constexpr int kOrderRows = MOE_ORDER_ROWS, kOrderCols = MOE_ORDER_COLS; // block
 constexpr int kXcds = 8;
 constexpr int kMaxGemmWorkgroups = 896; // workgroups of the persistent grid (ticket words of a table)
 
-// Head of a tile table.  The table holds two streams of tiles, one after the other: stream 0 the
-// 256-row tiles, those of experts with several of them (their weight tiles are shared by several
-// workgroups and the matrix cores bound them) before those of experts with one, stream 1 the tiles of
-// experts with up to 160 rows (they stream their weights from memory once and mostly wait for them),
-// the middle geometry's before the shallow one's.
+// Head of a tile table.  The table holds the 256-row tiles, then the middle geometry's, then the shallow
+// one's, as two streams: stream 0 the 256-row tiles (the matrix cores bound them), stream 1 the tiles of
+// experts with up to 160 rows (they stream their weights from memory once and mostly wait for them).
 struct TileTableHeader {
     int32_t len[2];         // tiles in each stream; stream s starts at entry (s ? len[0] : 0)
-    int32_t several;        // of stream 0, how many belong to experts of several row tiles (they come first)
-    int32_t mid;            // of stream 1, how many are of the middle geometry (they come first)
+    int32_t end_full;       // the entry behind the last 256-row tile ...
+    int32_t end_mid;        // ... and behind the last tile of the middle geometry
     int32_t light_slots;    // of the 32 workgroup slots an XCD has, how many take stream 1 first
     int32_t done;           // workgroups that have left the kernel (the last one resets the counters)
     int32_t magic;          // kTableMagic once build_tile_table has filled the table ...
@@ -102,7 +100,7 @@ constexpr int kReadyBit = 1 << 30;                 // in a drawn tile word: the 
 // of microseconds each, the launch takes twice as long); 2 = ordinary stores and no write-back: NOT
 // coherent, for timing experiments only.
 #ifndef MOE_LIGHT_AUX
-#define MOE_LIGHT_AUX 2 // cache policy of a shallow tile's weight loads: 2 = non-temporal
+#define MOE_LIGHT_AUX 2 // cache policy of a shallow or middle tile's weight loads: 2 = non-temporal
 #endif
 #ifndef MOE_DEP_STORE_THROUGH
 #define MOE_DEP_STORE_THROUGH 1
@@ -288,8 +286,8 @@ struct GemmArgs {
 };
 
 // Persistent grouped GEMM, as a function: a kernel runs one of them, or (the dependency-driven expert
-// computation) the two GEMMs one after the other.  Set: a geometry for each kind of tile (0: experts of several row
-// tiles, 3: of one such tile, 2: middle, 1: shallow), all of one workgroup size, BN and K tile.
+// computation) the two GEMMs one after the other.  Set: a geometry for each kind of tile (0: 256 rows, 2: middle,
+// 1: shallow), all of one workgroup size, BN and K tile.
 // kGather: row m of the A operand is row gather_rows[m] / gather_div of `A` (the dispatch's row
 // move done by the operand loads themselves) instead of row m.
 // kScatter: the result is not stored as row m of C.  `C` is an fp32 matrix of Ndim columns, and row
@@ -305,7 +303,6 @@ template <class Set, bool kSwiglu, bool kGather, bool kScatter, int kDep, bool k
 __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
 {
     using Main = typename Set::Main;
-    using Single = typename Set::Single;
     using Mid = typename Set::Mid;
     using Light = typename Set::Light;
     const uint16_t *__restrict__ const A = g.A;
@@ -324,9 +321,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     static_assert(Light::kBK == Main::kBK && Light::BN == Main::BN && Light::kThreads == Main::kThreads &&
                       Mid::kBK == Main::kBK && Mid::BN == Main::BN && Mid::kThreads == Main::kThreads,
                   "the geometries share K tile, BN and workgroup size");
-    static_assert(Main::kKind == 0 && Light::kKind == 1 && Mid::kKind == 2 && Single::kKind == 3 && Single::BM == Main::BM &&
-                      Single::kExtra == Main::kExtra,
-                  "kinds of tiles");
+    static_assert(Main::kKind == 0 && Light::kKind == 1 && Mid::kKind == 2, "kinds of tiles");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -355,7 +350,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     const uint64_t trace_c0 = __builtin_amdgcn_s_memtime(), trace_r0 = __builtin_amdgcn_s_memrealtime();
     uint32_t trace_ticks[4] = {0, 0, 0, 0}, trace_tiles[4] = {0, 0, 0, 0}; // full, tall, ragged, shallow
 #endif
-    const int len0 = hdr->len[0], len1 = hdr->len[1], end_mid = len0 + hdr->mid, end_several = hdr->several;
+    const int len0 = hdr->len[0], len1 = hdr->len[1], end_full = hdr->end_full, end_mid = hdr->end_mid;
     const int slot = (blockIdx.x / kXcds) % 32, ls = hdr->light_slots;
     const bool light_first = ((slot + 1) * ls) / 32 > (slot * ls) / 32;
     // A draw has two parts (thread 0 only): the ticket of the workgroup's own stream and XCD, whose round trip runs under
@@ -405,7 +400,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
     };
     auto kind_of = [&](int word) {
         const int e = entry_of(word);
-        return e < end_several ? 0 : e < len0 ? 3 : e < end_mid ? 2 : 1;
+        return e < end_full ? 0 : e < end_mid ? 2 : 1;
     };
     // consumer, thread 0 only: were the rows this tile reads complete at the time of the draw?
     const int32_t dep_epoch1 =
@@ -660,7 +655,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t *>((here ? cur.b : nxt.b) + (up ? b1_delta : 0)), 0,
             here ? cur.b_bytes : nxt.b_bytes, 0x00020000);
-        // The weights of a light or middle tile are read once by one workgroup: fetched with the non-temporal
+        // The weights of a shallow or middle tile are read once by one workgroup: fetched with the non-temporal
         // hint (aux bit 1) they do not push the other tiles' shared operands out of the caches.
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs, (lds_ptr)(lds + Cfg::unit_base(unit) + (wave * Cfg::kBGroups + g) * 1024), 16, b_off[g],
@@ -1210,8 +1205,6 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                 engine(Light{});
             else if (kind == 2)
                 engine(Mid{});
-            else if (kind == 3)
-                engine(Single{});
             else
                 engine(Main{});
         }
