@@ -30,17 +30,24 @@ namespace moe {
 // tile table
 // ------------------------------------------------------------------------
 constexpr int kSchedThreads = 256;
-// relative cost of a light, a middle and a full tile, for sharing out the workgroup slots
-constexpr int kLightCost = 3, kMidCost = 6, kHeavyCost = 7;
+// relative cost of a light, a middle and a full tile, for sharing out the workgroup slots (middle: by its time; 246 random launches
+// with all three take 0.995, 0.998, 1, 1.003 of the time with 4, 5, 6, 7)
+constexpr int kLightCost = 3, kMidCost = 5, kHeavyCost = 7;
 #ifndef MOE_ORDER_LONG_FIRST
 #define MOE_ORDER_LONG_FIRST 1
 #endif
 // experts with at most this many rows go through the shallow tile geometry
 constexpr int kLightRows = 64;
 
-// Experts come in three classes by their rows (geometries in ffn_gemm.h): full tiles, middle, light.  The first forms stream 0
-// of the table, the others stream 1; inside a class the order is expert, column tile, row tile.  The GEMM's persistent
-// workgroups draw from both streams.
+// Experts come in three classes by their rows (geometries in ffn_gemm.h): full tiles, middle, light; the table holds them in this
+// order, and inside a class by expert, column tile, row tile.  The GEMM's persistent workgroups draw from two streams: full and
+// middle tiles, and light ones; without full tiles, middle tiles go with the light ones.
+// Middle tiles wait for memory as light ones do, but as part of stream 1 next to full tiles they took 1.04 of the time in the mean
+// of 134 random launches and up to 1.33 (16 experts of 329 rows in the mean, K 2240, N 3968: 128 -> 178 us): a stream of few
+// tiles, which the XCDs take in runs of kPatch, leaves XCDs without tiles of their own, whose workgroups search the other
+// counters one after the other, while the slots set aside for it are missing where the full tiles lie.  Behind the full tiles
+// they are the shorter tiles at the launch's end.  (Middle and light tiles alone, in one stream: 0.85 of the time with 256-row
+// tiles in place of the middle ones, 36 random launches.)
 // Row tiles of an expert with `rows` rows: a remainder of at most `extra` rows rides with the last
 // full tile instead of forming a tile of its own.
 __device__ __forceinline__ int row_tiles(int32_t rows, int BM, int extra)
@@ -136,14 +143,15 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
     const int32_t end_full = end_of(start[0][E_local]), end_mid = end_of(end_full + start[1][E_local]);
     const int32_t total = end_of(end_mid + start[2][E_local]);
     if (blockIdx.x == 0 && tid == 0) {
-        hdr->len[0] = end_full;
-        hdr->len[1] = total - end_full;
+        const int32_t len0 = end_full > 0 ? end_mid : 0;
+        hdr->len[0] = len0;
+        hdr->len[1] = total - len0;
         hdr->end_full = end_full;
         hdr->end_mid = end_mid;
         // share of the workgroup slots that take stream 1 first: its tiles' share of the work
-        const int64_t wl = (int64_t)(total - end_mid) * kLightCost + (int64_t)(end_mid - end_full) * kMidCost;
-        const int64_t wh = (int64_t)end_full * kHeavyCost;
-        hdr->light_slots = wl + wh > 0 ? (int32_t)((32 * wl + (wl + wh) / 2) / (wl + wh)) : 0;
+        const int64_t wl = (int64_t)(total - end_mid) * kLightCost;
+        const int64_t wh = (int64_t)end_full * kHeavyCost + (int64_t)(end_mid - end_full) * kMidCost;
+        hdr->light_slots = len0 > 0 ? (int32_t)((32 * wl + (wl + wh) / 2) / (wl + wh)) : 32;
         hdr->done = 0;
         hdr->error = 0;
         hdr->epoch = 0;

@@ -69,9 +69,9 @@ constexpr int kOrderRows = MOE_ORDER_ROWS, kOrderCols = MOE_ORDER_COLS; // block
 constexpr int kXcds = 8;
 constexpr int kMaxGemmWorkgroups = 896; // workgroups of the persistent grid (ticket words of a table)
 
-// Head of a tile table.  The table holds the 256-row tiles, then the middle geometry's, then the shallow
-// one's, as two streams: stream 0 the 256-row tiles (the matrix cores bound them), stream 1 the tiles of
-// experts with up to 160 rows (they stream their weights from memory once and mostly wait for them).
+// Head of a tile table.  The table holds the 256-row tiles (the matrix cores bound them), then the middle
+// geometry's, then the shallow one's (they stream their weights from memory once and mostly wait for them),
+// as two streams: stream 1 the shallow ones and, where there are no 256-row tiles, the middle ones.
 struct TileTableHeader {
     int32_t len[2];         // tiles in each stream; stream s starts at entry (s ? len[0] : 0)
     int32_t end_full;       // the entry behind the last 256-row tile ...
