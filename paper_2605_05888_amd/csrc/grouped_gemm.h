@@ -959,17 +959,20 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             const uint32_t row_bytes = (uint32_t)Ndim * 2u;
             const uint32_t voff = lane_o % 16 * row_bytes + ((lane_o / 16 % 2) * 16 + (lane_o / 32) * 8) * 2;
             const int rows_left = cur.m_end - cur.m0;
-            // (of this tile, no more: 256 rows of 16 MB are just below what a byte count can hold, as in `a_bytes`)
-            constexpr int kTileRows = BM + (kHalf ? Cfg::kExtra / 2 : kExt ? Cfg::kExtra : 0);
-            const int tile_rows = rows_left < kTileRows ? rows_left : kTileRows;
             uint16_t *const c_tile = C + (int64_t)cur.m0 * Ndim + n_wave;
-            const uint32_t c_bytes = (uint32_t)tile_rows * row_bytes - (uint32_t)n_wave * 2u;
             const int blocks_left = (Ndim - n_wave) / 32; // (Ndim is a multiple of 64)
             constexpr int kAux = kDep == 1 && MOE_DEP_STORE_THROUGH == 1 ? 16 : 0; // 16: device scope, written through this XCD's L2, which the other XCDs do not snoop
             // block row at row `r0` of the tile: column blocks first, first + step, ... of the wavefront
             auto store_row = [&](int r0, const auto &blk, auto in_acc_regs, int first, auto step_tag, auto n_tag) {
                 constexpr int kStep = decltype(step_tag)::value, kN = decltype(n_tag)::value;
-                const uint32_t v0 = voff + (uint32_t)r0 * row_bytes + (uint32_t)first * 64, v1 = v0 + 16 * row_bytes;
+                // (a base for every block row: those of a whole tile can take more than the 4 GiB a byte count holds; worked
+                // out here, not ahead of the tile, where it would be kept in scalar registers that there are none of)
+                int row0 = r0;
+                asm volatile("" : "+s"(row0));
+                uint16_t *const c_row = c_tile + (int64_t)row0 * Ndim;
+                const int rows = rows_left - row0 < 32 ? rows_left - row0 : 32;
+                const uint32_t c_bytes = rows > 0 ? (uint32_t)rows * row_bytes - (uint32_t)n_wave * 2u : 0u;
+                const uint32_t v0 = voff + (uint32_t)first * 64, v1 = v0 + 16 * row_bytes;
 #pragma unroll
                 for (int j = 0; j < kN; ++j) {
                     uint32_t p[8]; // [quarter][pair of columns]
@@ -994,7 +997,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
                         swap16(x, y);
                         lo[h] = x, hi[h] = y;
                     }
-                    const auto rs = __builtin_amdgcn_make_buffer_rsrc(c_tile, 0, first + j * kStep < blocks_left ? c_bytes : 0u, 0x00020000);
+                    const auto rs = __builtin_amdgcn_make_buffer_rsrc(c_row, 0, first + j * kStep < blocks_left ? c_bytes : 0u, 0x00020000);
                     __builtin_amdgcn_raw_buffer_store_b128(lo, rs, (int)v0 + j * kStep * 64, 0, kAux);
                     __builtin_amdgcn_raw_buffer_store_b128(hi, rs, (int)v1 + j * kStep * 64, 0, kAux);
                     // one block at a time: left alone, the scheduler first copies the whole tile out of the

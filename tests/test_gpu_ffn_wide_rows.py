@@ -1,15 +1,19 @@
-"""Down projection into rows so wide that 320 of them take more than 4 GiB (256 take less): the byte count that bounds a tile's
-stores is that of the rows the tile has."""
+"""Down projection into rows so wide that those of one tile take more than 4 GiB, more than the byte count that bounds its stores
+can hold."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-def test_rows_of_13_megabytes():
+@pytest.mark.parametrize("M,H", [(330, 64 * 105469),    # a full row tile and one of 74 rows; 318 rows fit into 4 GiB
+                                 (320, 64 * 105469),    # a tall tile with two block rows more
+                                 (288, 64 * 116600),    # one block row more
+                                 (300, 64 * 131073)])   # 256 rows do not fit
+def test_rows_of_13_megabytes(M, H):
     import torch
     import paper_2605_05888_amd as hub
-    M, H, F = 330, 64 * 105469, 64               # a full row tile and one of 74 rows
-    assert 256 * H * 2 < 2 ** 32 < 320 * H * 2
+    F = 64
+    assert M * H * 2 > 2 ** 32
     print("wide rows", M, H, F, flush=True)
     g = torch.Generator(device="cuda").manual_seed(51)
     Wd = torch.empty((1, H, F), dtype=torch.bfloat16, device="cuda").normal_(0.0, F ** -0.5, generator=g)
