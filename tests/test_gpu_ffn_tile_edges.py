@@ -45,7 +45,7 @@ EDGES = [64, 65, 95, 96, 97, 128, 159, 160, 161, 192, 193, 256, 257, 288, 289, 3
                                  (512, 320),   # with 128-column tiles
                                  (64, 4096), (128, 2048)])
 def test_rows_at_the_edges_of_the_geometries(H, F):
-    """Against 64-bit arithmetic; and reversed, gathered and in one launch: the same bits."""
+    """Against 64-bit arithmetic; and reversed, gathered, added into the tokens' sums and in one launch: the same bits."""
     import torch
     import paper_2605_05888_amd as hub
     print("geometry edges", H, F, flush=True)
@@ -73,6 +73,10 @@ def test_rows_at_the_edges_of_the_geometries(H, F):
     hub.moe_ffn_gate_up_gather(x, 1, dseg, rev.to(torch.int32), Wg, Wu, ws)
     hub.moe_ffn_down(dseg, Wd, y2, ws)
     assert torch.equal(y2, y)
+    # added to their tokens' sums (top-1, weight 2: exact doubles); the rows of `a` are still those of xp
+    sums, out = torch.empty(M, H, device="cuda"), torch.full_like(y, float("nan"))
+    hub.moe_ffn_down_combine(1, dseg, Wd, rev.to(torch.int32), torch.full((M, 1), 2.0, device="cuda"), sums, out, ws)
+    assert torch.equal(out[rev], (2.0 * y.float()).to(torch.bfloat16))
     y2.fill_(float("nan"))
     hub.moe_ffn_schedule(hub.BF16, M, H, F, dseg, ws)
     hub.moe_ffn_gate_up_down(xp, dseg, Wg, Wu, Wd, y2, ws)

@@ -1,11 +1,12 @@
 """Reductions that start past the first column and wrap around (rows of the weights a multiple of 4 KiB apart, up to 8192
-columns), in every form of tile: shallow, ragged, tall by a shared and by an own block row, several row tiles."""
+columns), in every form of tile: shallow, of 160 rows, ragged, full, tall by a shared and by an own block row, several row tiles."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 ROWS = [300, 20, 64, 65, 276, 1, 0, 530]
+BLOCKS = [97, 129, 160, 161, 256]  # tiles of 160 rows with four and five block rows, single tiles of 256
 # H, F, how often ROWS (reductions are turned from 192 column tiles on, of all experts together)
 SIZES = [(2048, 128 * 17 + 64, 1),  # too few tiles: not turned
          (2048, 128 * 17 + 64, 2),  # gate/up turned: shallow tiles at 0 and 1 K tiles of 16, others from column tile 8 on
@@ -15,12 +16,12 @@ SIZES = [(2048, 128 * 17 + 64, 1),  # too few tiles: not turned
          (6144, 1216, 4)]           # a number of K tiles that 16 does not divide evenly into turns
 
 
-@pytest.mark.parametrize("H,F,times", SIZES)
-def test_turned_reduction(H, F, times):
+@pytest.mark.parametrize("H,F,times,more", [(*size, []) for size in SIZES] + [(4096, 4096, 1, BLOCKS)])
+def test_turned_reduction(H, F, times, more):
     import torch
     import paper_2605_05888_amd as hub
-    print("turned", H, F, times, flush=True)
-    rows_of = ROWS * times
+    print("turned", H, F, times, len(more), flush=True)
+    rows_of = ROWS * times + more
     E, M = len(rows_of), sum(rows_of)
     seg = np.concatenate([[0], np.cumsum(rows_of)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(11)
@@ -52,15 +53,20 @@ def test_turned_reduction(H, F, times):
 
 
 # narrow column tiles in the down projection (up to 256 tiles of 256 columns) and wide ones; gate/up, down or both turned
-@pytest.mark.parametrize("H,F,times", [(2048, 320, 1), (320, 2048, 1), (2048, 4096, 1), (6144, 1216, 1), (5696, 2048, 1), (6144, 4096, 1),
-                                       (2048, 320, 8), (320, 2048, 8), (2048, 4096, 2), (6144, 1216, 4), (5696, 2048, 2)])
-def test_turned_reduction_in_the_other_forms(H, F, times):
+FORMS = [(2048, 320, 1), (320, 2048, 1), (2048, 4096, 1), (6144, 1216, 1), (5696, 2048, 1), (6144, 4096, 1),
+         (2048, 320, 8), (320, 2048, 8), (2048, 4096, 2), (6144, 1216, 4), (5696, 2048, 2)]
+
+
+@pytest.mark.parametrize("H,F,times,more", [(*form, []) for form in FORMS] +
+                         [(2048, 320, 8, BLOCKS), (320, 2048, 8, BLOCKS),   # gate/up, narrow down projection turned
+                          (6144, 4096, 1, BLOCKS)])                         # both
+def test_turned_reduction_in_the_other_forms(H, F, times, more):
     """Both GEMMs in one launch, the combine in the down projection's epilogue, and every segment reversed (so that a
     remainder of rows that rode with a full tile is an ordinary part of it): the bits of the separate launches."""
     import torch
     import paper_2605_05888_amd as hub
-    print("turned, other forms", H, F, times, flush=True)
-    rows_of = ROWS * times
+    print("turned, other forms", H, F, times, len(more), flush=True)
+    rows_of = ROWS * times + more
     E, M = len(rows_of), sum(rows_of)
     seg = np.concatenate([[0], np.cumsum(rows_of)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(12)
