@@ -230,10 +230,9 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
 #endif
 constexpr int kNarrowTileBound = MOE_NARROW_TILE_BOUND;
 
-
 struct FfnPlan {
     bool thin1, thin2; // GEMM1 / GEMM2 by ffn_thin.hip: that table holds row tiles only
-    bool narrow2; // the down projection runs with NarrowBig / NarrowShallow
+    bool narrow2; // the down projection runs with NarrowSet
     int BM, out_cols1, out_cols2;
     int n_tiles1, n_tiles2, max_m_tiles1, max_m_tiles2;
     size_t off_a, off_hdr1, off_tab1, off_hdr2, off_tab2, off_ready, total;

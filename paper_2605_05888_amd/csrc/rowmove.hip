@@ -23,11 +23,9 @@ __device__ __forceinline__ float lane_value(float v, int k)
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int32_t)__float_as_uint(v), k));
 }
 
-// x has just been read by the router and often still lies in the 256 MB memory-side cache, so its loads are ordinary ones;
-// kStream (xp larger than that cache): non-temporal stores, which leave x there.  A smaller xp is stored so that it stays for
-// the GEMM.  8192 tokens, H 7168, K 8 (1.06 GB): non-temporal loads, ordinary stores 221 us, this 187 us (5.7 TB/s); H 2880,
-// K 4 (236 MB): non-temporal loads 43, ordinary loads 39, non-temporal stores 42 us.
-template <bool kStream>
+// x has just been read by the router and may still lie in the 256 MB memory-side cache, and xp is read next.  kPassX, kPassXp:
+// non-temporal loads of x, stores of xp, which leave that cache to the other (launch_permute says when).
+template <bool kPassX, bool kPassXp>
 __global__ __launch_bounds__(kWave *kTokensPerBlock) void permute_rows(
     const u32x4 *__restrict__ x, int chunks, int64_t N, int K,
     const int32_t *__restrict__ slot_of_row, u32x4 *__restrict__ xp)
@@ -39,15 +37,21 @@ __global__ __launch_bounds__(kWave *kTokensPerBlock) void permute_rows(
     // lane k keeps slot k of this token
     int32_t my_slot = (lane < K) ? slot_of_row[n * K + lane] : 0;
     const u32x4 *src = x + n * chunks;
+    auto get = [](const u32x4 *from) {
+        if constexpr (kPassX)
+            return __builtin_nontemporal_load(from);
+        else
+            return *from;
+    };
     auto put = [](u32x4 v, u32x4 *to) {
-        if constexpr (kStream)
+        if constexpr (kPassXp)
             __builtin_nontemporal_store(v, to);
         else
             *to = v;
     };
     int c = lane;
     for (; c + 3 * kWave < chunks; c += 4 * kWave) {
-        const u32x4 v0 = src[c], v1 = src[c + kWave], v2 = src[c + 2 * kWave], v3 = src[c + 3 * kWave];
+        const u32x4 v0 = get(src + c), v1 = get(src + c + kWave), v2 = get(src + c + 2 * kWave), v3 = get(src + c + 3 * kWave);
         for (int k = 0; k < K; ++k) {
             u32x4 *dst = xp + (int64_t)lane_value(my_slot, k) * chunks + c;
             put(v0, dst);
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(kWave *kTokensPerBlock) void permute_rows(
         }
     }
     for (; c < chunks; c += kWave) {
-        const u32x4 v = src[c];
+        const u32x4 v = get(src + c);
         for (int k = 0; k < K; ++k)
             put(v, xp + (int64_t)lane_value(my_slot, k) * chunks + c);
     }
@@ -153,8 +157,19 @@ int launch_permute(const void *x, int64_t row_bytes, int64_t N, int K, const int
 {
     const int chunks = (int)(row_bytes / 16);
     const unsigned blocks = (unsigned)ceil_div(N, kTokensPerBlock);
+    // What is to stay in the memory-side cache has to fit: x and xp, or x only, or xp only (an eighth more than fits: the rest of it
+    // still is there).  270 random launches, x read before and xp after; MiB, us of the move and the read of xp (of which the move),
+    // nothing past the cache -> x -> xp -> both: x 44, xp 176: 118 (39) -> 126 (47) -> 159 (53) -> 159 (53); x 180, xp 180: 173 (62)
+    // -> 140 (61) -> 167 (59) -> 167 (59); x 44, xp 266: 223 (57) -> 199 (56) -> 212 (59) -> 211 (59); x 151, xp 302: 266 (79) ->
+    // 268 (81) -> 244 (73) -> 244 (73); x 85, xp 687: 552 (143) -> 554 (141) -> 516 (144) -> 517 (145); x 396, xp 396: 381 (145) ->
+    // 375 (129) -> 386 (166) -> 357 (137).  Rows that share lines of 128 bytes write those in two parts past the cache: below 4 KiB
+    // 1.01 of the time (the move 1.2 - 1.5), above 0.95 (1.1), whole lines 0.92 (1.0).
     constexpr int64_t kMemoryCache = (int64_t)256 << 20;
-    auto kern = N * K * row_bytes > kMemoryCache ? permute_rows<true> : permute_rows<false>;
+    const int64_t x_bytes = N * row_bytes, xp_bytes = x_bytes * K;
+    const bool pass_xp = xp_bytes > kMemoryCache / 8 * 9 && (row_bytes % 128 == 0 || row_bytes > 4096);
+    const bool pass_x = x_bytes + (pass_xp ? 0 : xp_bytes) > kMemoryCache;
+    auto kern = pass_xp ? (pass_x ? permute_rows<true, true> : permute_rows<false, true>)
+                        : (pass_x ? permute_rows<true, false> : permute_rows<false, false>);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kTokensPerBlock), 0, st,
                        static_cast<const u32x4 *>(x), chunks, N, K, slot_of_row,
                        static_cast<u32x4 *>(xp));

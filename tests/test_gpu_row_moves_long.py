@@ -1,5 +1,5 @@
 """Row moves of long rows: the combine with a workgroup per token (from 256 chunks of 16 bytes on; remainders of the chunks
-per lane, K that four rows at a time do not divide) and the permute that streams its stores (xp above 256 MB)."""
+per lane, K that four rows at a time do not divide) and the permute that moves x, xp or both past the 256 MB memory-side cache."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +40,8 @@ def test_long_rows(chunks, K, bf16):
     assert bool(((out.double() - want).abs() <= bound + 1e-30).all())
 
 
-def test_streamed_permute():
+# in MiB: xp 262, x 33 | x and xp 134 | xp 300, x 38 | x and xp 297 | xp 301 of short rows that share lines
+@pytest.mark.parametrize("N,H,K", [(2100, 8200, 8), (8600, 8200, 1), (2400, 8200, 8), (19000, 8200, 1), (12000, 824, 16)])
+def test_permute_past_the_cache(N, H, K):
     import torch
-    moves(2100, 8200, 8, torch.bfloat16)  # 275 MB; rows of 1025 chunks
+    moves(N, H, K, torch.bfloat16)
