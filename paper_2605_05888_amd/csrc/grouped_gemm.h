@@ -966,7 +966,7 @@ __device__ __forceinline__ void gemm_phase(const GemmArgs &g)
             // block row at row `r0` of the tile: column blocks first, first + step, ... of the wavefront
             auto store_row = [&](int r0, const auto &blk, auto in_acc_regs, int first, auto step_tag, auto n_tag) {
                 constexpr int kStep = decltype(step_tag)::value, kN = decltype(n_tag)::value;
-                // (a base for every block row: those of a whole tile can take more than the 4 GiB a byte count holds; worked
+                // (a base for every block row, whose 32 rows have to fit into the 4 GiB a byte count holds; worked
                 // out here, not ahead of the tile, where it would be kept in scalar registers that there are none of)
                 int row0 = r0;
                 asm volatile("" : "+s"(row0));
