@@ -40,14 +40,14 @@ constexpr int kLightCost = 3, kMidCost = 5, kHeavyCost = 7;
 constexpr int kLightRows = 64;
 
 // Experts come in three classes by their rows (geometries in ffn_gemm.h): full tiles, middle, light; the table holds them in this
-// order, and inside a class by expert, column tile, row tile.  The GEMM's persistent workgroups draw from two streams: full and
-// middle tiles, and light ones; without full tiles, middle tiles go with the light ones.
-// Middle tiles wait for memory as light ones do, but as part of stream 1 next to full tiles they took 1.04 of the time in the mean
-// of 134 random launches and up to 1.33 (16 experts of 329 rows in the mean, K 2240, N 3968: 128 -> 178 us): a stream of few
-// tiles, which the XCDs take in runs of kPatch, leaves XCDs without tiles of their own, whose workgroups search the other
-// counters one after the other, while the slots set aside for it are missing where the full tiles lie.  Behind the full tiles
-// they are the shorter tiles at the launch's end.  (Middle and light tiles alone, in one stream: 0.85 of the time with 256-row
-// tiles in place of the middle ones, 36 random launches.)
+// order, and inside a class by expert, column tile, row tile.  The GEMM's persistent workgroups draw from two streams: full tiles,
+// and light ones.  Middle tiles wait for memory as light ones do, and without full tiles they go with them (0.85 of the time with
+// 256-row tiles in their place, 36 random launches).  Next to full tiles they do so where at least a sixth of all tiles are light:
+// then a good part of the workgroups streams from the start (41 experts, 13 / 14 / 14 of the classes, K 3840, N 1216: 317 -> 244
+// us).  With fewer light tiles they end the full tiles' stream, as the shorter ones (44 experts, 7 middle, 37 full, K 2688, N 1280:
+// 249 -> 203).  211 random launches with middle and full tiles, time over that without middle tiles: always with the light ones
+// 0.934, up to 1.24; always behind the full ones 0.915, up to 1.14; this 0.918, up to 1.08.
+constexpr int kMidWithLight = 6;
 // Row tiles of an expert with `rows` rows: a remainder of at most `extra` rows rides with the last
 // full tile instead of forming a tile of its own.
 __device__ __forceinline__ int row_tiles(int32_t rows, int BM, int extra)
@@ -143,14 +143,15 @@ __global__ __launch_bounds__(kSchedThreads) void build_tile_table(
     const int32_t end_full = end_of(start[0][E_local]), end_mid = end_of(end_full + start[1][E_local]);
     const int32_t total = end_of(end_mid + start[2][E_local]);
     if (blockIdx.x == 0 && tid == 0) {
-        const int32_t len0 = end_full > 0 ? end_mid : 0;
+        const int32_t len0 = end_full > 0 && (int64_t)(total - end_mid) * kMidWithLight < total ? end_mid : end_full;
         hdr->len[0] = len0;
         hdr->len[1] = total - len0;
         hdr->end_full = end_full;
         hdr->end_mid = end_mid;
         // share of the workgroup slots that take stream 1 first: its tiles' share of the work
-        const int64_t wl = (int64_t)(total - end_mid) * kLightCost;
-        const int64_t wh = (int64_t)end_full * kHeavyCost + (int64_t)(end_mid - end_full) * kMidCost;
+        const int64_t w_mid = (int64_t)(end_mid - end_full) * kMidCost;
+        const int64_t wl = (int64_t)(total - end_mid) * kLightCost + (len0 == end_full ? w_mid : 0);
+        const int64_t wh = (int64_t)end_full * kHeavyCost + (len0 == end_full ? 0 : w_mid);
         hdr->light_slots = len0 > 0 ? (int32_t)((32 * wl + (wl + wh) / 2) / (wl + wh)) : 32;
         hdr->done = 0;
         hdr->error = 0;

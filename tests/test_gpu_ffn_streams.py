@@ -8,7 +8,9 @@ TABLE_MAGIC = 0x4D6F4554  # word 6 of a tile table's header
 
 
 # full tiles of 256 rows, middle ones of up to 160, light ones of up to 64; (stream 0, stream 1, full, full and middle) in row tiles
-@pytest.mark.parametrize("rows,want", [([600, 161, 100, 160, 64, 1], (6, 2, 4, 6)),   # middle tiles behind the full ones
+@pytest.mark.parametrize("rows,want", [([600, 600, 600, 100, 160, 64], (11, 1, 9, 11)), # few light tiles: middle ones behind the full ones
+                                       ([600, 600, 600, 100, 64, 1], (9, 3, 9, 10)),    # a sixth: with the light ones
+                                       ([600, 161, 100, 160, 64, 1], (4, 4, 4, 6)),
                                        ([100, 65, 64, 1, 40], (0, 5, 0, 2)),           # no full tile: with the light ones
                                        ([320, 321, 512, 0], (5, 0, 5, 5)),
                                        ([300, 20, 10], (1, 2, 1, 1)),
