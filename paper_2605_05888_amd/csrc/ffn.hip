@@ -276,6 +276,10 @@ static bool use_thin(int64_t M, int64_t experts, int64_t tiles, int tile_rows, i
 // experts, F 14336, 1 row: 85 -> 92; 128 of them, K 14336: 49 -> 81).
 static bool wide_thin(int64_t M, int64_t experts, int64_t workgroups) { return M > 4 * experts && workgroups >= 384; }
 
+// From so many columns on 32 rows, whose bytes bound the tiled form's stores, take 4 GiB, more than a byte count holds.  The thin
+// form stores to 64-bit addresses and takes any number of rows (a pass over the weights for 64 of them).
+constexpr int64_t kThinCols = (int64_t)1 << 26;
+
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 static FfnPlan make_plan(int64_t M, int64_t H, int64_t F, int E_local)
@@ -305,8 +309,8 @@ static FfnPlan make_plan(int64_t M, int64_t H, int64_t F, int E_local)
     // (the workspace's layout is the tiled form's, so that its size keeps growing with M)
     const int thin_tiles = (int)(M / kThinRows + E_local < M ? M / kThinRows + E_local : M);
     const int64_t experts = E_local < M ? E_local : M;
-    p.thin1 = use_thin(M, experts, experts * p.n_tiles1, 256, H) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
-    p.thin2 = use_thin(M, experts, experts * p.n_tiles2, p.out_cols2, F) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
+    p.thin1 = (F >= kThinCols || use_thin(M, experts, experts * p.n_tiles1, 256, H)) && thin_tiles <= p.max_m_tiles1 * p.n_tiles1;
+    p.thin2 = (H >= kThinCols || use_thin(M, experts, experts * p.n_tiles2, p.out_cols2, F)) && thin_tiles <= p.max_m_tiles2 * p.n_tiles2;
     if (p.thin1) {
         p.max_m_tiles1 = thin_tiles, p.n_tiles1 = 1;
         p.out_cols1 = wide_thin(M, experts, experts * ceil_div(F, 32)) ? 32 : 16;
